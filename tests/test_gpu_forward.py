@@ -148,6 +148,18 @@ def test_bf16_paths(name, plain):
     _compare(model, host, states, bs, L, 2e-2, f"{name}/mask{plain}")
 
 
+@pytest.mark.parametrize("name,N", [("small-2l", 33), ("small-2l", 65), ("small-2l", 127), ("small-2l", 197), ("small-2l", 20),
+                                    ("gqa-bias", 141), ("gqa-bias", 257), ("gqa-bias", 30)])
+def test_sequences_of_no_round_length_run_on_the_matrix_core_attention(name, N):
+    """Lengths that are no multiple of 8 or 16: partial query and key tiles at every edge (one past a tile, one short of it,
+    less than one), several sequences so that a sequence's neighbours in memory must not leak into its last tile."""
+    from tests.gpu_common import make_models
+    shape, L = SHAPES[name][0], 12
+    host, model = make_models(shape, N)
+    states = [_state(shape, N, N - L, L, 70 + s, 4 * s) for s in range(3)]
+    _compare(model, host, states, N - L, L, 2e-2, f"{name} N={N}")
+
+
 @pytest.mark.parametrize("name,N,S", [("small-2l", 192, 1), ("small-2l", 48, 11), ("small-2l", 384, 4), ("gqa-bias", 144, 1),
                                       ("gqa-bias", 272, 5), ("gqa-bias", 1280, 2)])
 def test_rotary_and_value_transpose_in_the_qkv_epilogue_change_no_bit(name, N, S):
