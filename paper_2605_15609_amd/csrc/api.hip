@@ -886,9 +886,14 @@ int32_t psd_kv_prefill(psd_handle *h, const int32_t *tokens, int32_t B, int32_t 
     a.capacity = capacity;
     a.seqs_per_cache = 1;
     a.append = true;
-    for (int start = 0; start < n_prompt; start += L) {   // block by block: each sees the blocks before it
+    // as many blocks per pass as the workspace holds: a pass over one block of few rows is a stream of all weights, over
+    // several hundred rows it is not much longer (8B shape, 512 positions: 77.9 ms block by block, 9.2 ms in one pass)
+    int at_once = n_prompt / L;
+    while (at_once > 1 && plan_forward(h->cfg, B, (int64_t)at_once * L, L).total > ws_bytes) at_once = (at_once + 1) / 2;
+    for (int start = 0; start < n_prompt; start += at_once * L) {
         a.len = start;
-        CHECK(run_forward_cached(h, tokens, nullptr, B, N, start, L, a, ws, ws_bytes, (hipStream_t)stream));
+        const int rows = std::min(at_once * L, n_prompt - start);
+        CHECK(run_forward_cached(h, tokens, nullptr, B, N, start, L, a, ws, ws_bytes, (hipStream_t)stream, rows));
     }
     return PSD_OK;
 }

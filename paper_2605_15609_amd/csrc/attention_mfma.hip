@@ -40,17 +40,23 @@ typedef __attribute__((address_space(3))) void lds_void;
 //
 // pre: keys and values that precede the sequence's own N rows (a KV cache of pre.len positions, shared by
 // pre.seqs_per_cache consecutive sequences).  Every query sees all of them and all N own keys: with the own rows
-// being one block, that is context-causal block attention.  pre.len = 0: plain bidirectional attention.
+// being one block, that is context-causal block attention.  pre.len = 0: plain bidirectional attention.  vT = NULL: no own
+// keys, the cache holds those of the queries' own rows too.
 //
 // KSP > 1 (= NW): key-split mode for a single block of 32 queries.  The NW wavefronts all take the same queries
 // and deal the key tiles round-robin; each runs the tile loop on its own, with a ring of its own in LDS (no
 // barrier inside the loop), and the partial (max, sum, O^T) are merged in wavefront order at the end.  A lone
 // wavefront per (sequence, head) walks its tiles as one serial chain of fetch, MFMA, softmax, MFMA; the split
 // shortens that chain, which is all the time there is on the block-row path.
-template <int DH, int NW, int NSTG, int KSP = 1>
+//
+// CAUSAL: context-causal blocks over several blocks of a sequence at once (a prompt on its way into the KV cache).  All keys,
+// the queries' own among them, sit in the cache; query i is at position pos0 + i and sees the keys before the end of its
+// block.  A workgroup walks the tiles its last query sees, a wavefront computes those that one of its own queries sees.
+template <int DH, int NW, int NSTG, int KSP = 1, bool CAUSAL = false>
 __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__restrict__ qkv, int ld_qkv,
                                                             const bf16_t *__restrict__ vT, int ld_vt, int N, int n_heads,
-                                                            int n_kv_heads, bf16_t *__restrict__ out, KvPrefix pre) {
+                                                            int n_kv_heads, bf16_t *__restrict__ out, KvPrefix pre, int pos0,
+                                                            int block_len) {
     constexpr int KROW = DH * 2;                 // bytes per K row in LDS
     constexpr int K_BYTES = BKV * KROW;
     constexpr int VROW = BKV * 2;                // bytes per V^T row in LDS (128)
@@ -112,9 +118,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
     // key(row) = kkey(row) for K rows and (row >> 1) & 7 for the 128-byte V^T rows.  Row groups are dealt round-robin to the wavefronts.  Keys past the end of
     // the sequence are rejected by the descriptor (K); value slots past it are zeroed in registers in the last tile.
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t *>(seq) + (n_heads + kvh) * DH, 0, (int)(((int64_t)N * row_w - (n_heads + kvh) * DH) * 2), 0x00020000);
+        const_cast<bf16_t *>(seq) + (n_heads + kvh) * DH, 0, vT ? (int)(((int64_t)N * row_w - (n_heads + kvh) * DH) * 2) : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t *>(vT) + ((int64_t)s * n_kv_heads + kvh) * DH * (int64_t)ld_vt, 0, DH * ld_vt * 2, 0x00020000);
+        const_cast<bf16_t *>(vT) + ((int64_t)s * n_kv_heads + kvh) * DH * (int64_t)ld_vt, 0, vT ? DH * ld_vt * 2 : 0, 0x00020000);
     // the prefix (cache) of this sequence; empty descriptors when there is none
     const int n_pre = (pre.len + BKV - 1) / BKV;
     const int64_t cache = n_pre ? (pre.seq_rows ? pre.seq_rows[s] : s) / pre.seqs_per_cache : 0;
@@ -144,7 +150,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
 // tile tt of the key sequence: prefix tiles first, then the own rows
 #define PSD_ATT_DMA(stage, tt)                                                                                   \
     {                                                                                                            \
-        if ((tt) < n_pre) PSD_ATT_DMA_FROM(stage, rk_pre, pre.ld_k, rv_pre, pre.ld_vt, (tt) * BKV)               \
+        if (CAUSAL || (tt) < n_pre) PSD_ATT_DMA_FROM(stage, rk_pre, pre.ld_k, rv_pre, pre.ld_vt, (tt) * BKV)               \
         else PSD_ATT_DMA_FROM(stage, rk, row_w, rv, ld_vt, ((tt) - n_pre) * BKV)                                 \
     }
 #define PSD_ATT_SYNC()                                                                                           \
@@ -167,7 +173,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
     // returns in issue order: once at most (NSTG - 2) tiles' worth of this wavefront's fetches are in flight,
     // the next tile has landed.
     static_assert(NSTG >= 2 && (NSTG - 1) * (KG + VG) <= 63, "DMA groups in flight must fit the vmcnt counter");
-    const int n_tiles = n_pre + (N + BKV - 1) / BKV;
+    int n_tiles = n_pre + (vT ? (N + BKV - 1) / BKV : 0);
+    // CAUSAL: end of the visible keys for this lane's query, for the first and for the last query of the wavefront
+    int lim_q = 0, lim_lo = 0, lim_hi = 0;
+    if constexpr (CAUSAL) {
+        static_assert(KSP == 1, "one wavefront per 32 queries");
+        auto end_of = [&](int q) { return (pos0 + min(q, N - 1)) / block_len * block_len + block_len; };
+        lim_q = end_of(q_base + lrow);
+        lim_lo = end_of(q_base);
+        lim_hi = end_of(q_base + 31);
+        n_tiles = (end_of(qblk * (32 * NW) + 32 * NW - 1) + BKV - 1) / BKV;
+    }
     // this wavefront's tiles: all of them, or every KSP-th one
     constexpr int TSTEP = KSP;
     const int t_first = KSP > 1 ? wave_id : 0;
@@ -178,12 +194,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
     int stage = 0;
     for (int t = t_first; t < n_tiles; t += TSTEP) {
         // first key of the tile within its segment, and the number of keys that segment has
-        const int k0 = (t < n_pre ? t : t - n_pre) * BKV, limit = t < n_pre ? pre.len : N;
+        const int k0 = (CAUSAL || t < n_pre ? t : t - n_pre) * BKV, limit = CAUSAL || t < n_pre ? pre.len : N;
         // refill the slot every wavefront left at the last barrier; past the last tile the fetch is rejected or
         // reads padding and is never consumed
         const int fill = (stage == 0) ? NSTG - 1 : stage - 1;
         PSD_ATT_DMA(fill, t + (NSTG - 1) * TSTEP)
         const unsigned char *sk = lds + stage * STAGE, *sv = sk + K_BYTES;
+        if (CAUSAL && k0 >= lim_hi) {   // none of this wavefront's queries sees the tile
+            PSD_ATT_SYNC()
+            stage = (stage + 1 == NSTG) ? 0 : stage + 1;
+            continue;
+        }
 
         // scores, transposed: acc_s[kt][v] <-> key 32*kt + 8*(v/4) + 4*half + v%4, query lrow
         floatx16 acc_s[2];
@@ -199,14 +220,14 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
                 acc_s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], acc_s[kt], 0, 0, 0);
             }
         }
-        // keys past the end of the segment do not exist
-        if (k0 + BKV > limit) {
+        // keys past the end of the segment do not exist, those past the end of a query's block are hidden from it
+        if (k0 + BKV > (CAUSAL ? lim_lo : limit)) {
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int key = k0 + kt * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3);
-                    if (key >= limit) acc_s[kt][v] = -INFINITY;
+                    if (key >= (CAUSAL ? lim_q : limit)) acc_s[kt][v] = -INFINITY;
                 }
         }
         // online softmax for this lane's query
@@ -392,19 +413,19 @@ void launch_rope_transpose_v(bf16_t *qkv, int ld_qkv, int S, int N, int pos0, in
                        pos0, n_heads, n_kv_heads, d_head, cos_t, sin_t, vT, (int)vt_row_stride(N), tokens, tiles_i, tiles_c);
 }
 
-template <int DH, int NW, int NSTG, int KSP = 1>
+template <int DH, int NW, int NSTG, int KSP = 1, bool CAUSAL = false>
 static void launch_att(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int n_heads, int n_kv_heads, bf16_t *out,
-                       const KvPrefix &pre, hipStream_t st) {
+                       const KvPrefix &pre, hipStream_t st, int pos0 = 0, int block_len = 1) {
     constexpr int smem = KSP * NSTG * (BKV * DH * 2 + DH * BKV * 2);
     static_assert(smem <= 160 * 1024, "LDS rings exceed the 160 KB of a CU");
     static_assert(KSP == 1 || (2 + DH / 32 * 16) * 64 * 4 <= NSTG * (BKV * DH * 2 + DH * BKV * 2), "merge data fit a ring");
-    auto kern = attention_kernel<DH, NW, NSTG, KSP>;
+    auto kern = attention_kernel<DH, NW, NSTG, KSP, CAUSAL>;
     static std::atomic<uint64_t> lds_raised{0};   // one per instantiation
     ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem, lds_raised);
     constexpr int q_per_wg = KSP > 1 ? 32 : 32 * NW;
     dim3 grid((N + q_per_wg - 1) / q_per_wg, n_heads, S);
     hipLaunchKernelGGL(kern, grid, dim3(NW * 64), smem, st, qkv, ld_qkv, vT, (int)vt_row_stride(N), N, n_heads, n_kv_heads, out,
-                       pre);
+                       pre, pos0, block_len);
 }
 
 // LDS ring depth of the K / V^T tiles; deeper rings (3, 4 stages) were measured 3-7 % slower: the kernel is not
@@ -425,4 +446,20 @@ void launch_attention_bf16(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int 
         else if (small) launch_att<64, 2, NSTG>(qkv, ld_qkv, vT, S, N, n_heads, n_kv_heads, out, pre, st);
         else launch_att<64, 4, NSTG>(qkv, ld_qkv, vT, S, N, n_heads, n_kv_heads, out, pre, st);
     }
+}
+
+// Prompts: 128 queries per workgroup when that fills the CUs, 64 otherwise (as above; the tiles a workgroup walks grow with
+// its queries' positions, so the smaller one also spreads the work better)
+void launch_attention_causal_bf16(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int n_kv_heads, int d_head, bf16_t *out,
+                                  const KvPrefix &cache, int pos0, int block_len, hipStream_t st) {
+    const bool small = (int64_t)((N + 127) / 128) * n_heads * S < 512;
+    auto go = [&](auto dh, auto nw) {
+        launch_att<decltype(dh)::value, decltype(nw)::value, NSTG, 1, true>(qkv, ld_qkv, nullptr, S, N, n_heads, n_kv_heads, out, cache, st,
+                                                                            pos0, block_len);
+    };
+    using std::integral_constant;
+    if (d_head == 128)
+        small ? go(integral_constant<int, 128>(), integral_constant<int, 2>()) : go(integral_constant<int, 128>(), integral_constant<int, 4>());
+    else
+        small ? go(integral_constant<int, 64>(), integral_constant<int, 2>()) : go(integral_constant<int, 64>(), integral_constant<int, 4>());
 }

@@ -72,8 +72,14 @@ struct QkvArgs {
     int v_start;          // columns [0, v_start) are q and k heads, [v_start, Nout) V heads; a multiple of BN
     int N, pos0;          // rows per sequence (a multiple of 16) and the rotary position of a sequence's first row
     const float *cos_t, *sin_t;   // [positions, d_head / 2]
-    bf16_t *vT;           // [sequences][Nout - v_start][ld_vt]
+    bf16_t *vT;           // value column c, key i of sequence s at vT[s * vt_seq + c * ld_vt + slot(i)]
     int ld_vt;
+    int64_t vt_seq;
+    // k heads (columns [k_start, v_start)): k_dst = NULL: into `out` next to q; otherwise into a KV cache, row i of sequence s
+    // at k_dst[s * k_seq + i * ld_k + column - k_start]
+    bf16_t *k_dst;
+    int ld_k, k_start;
+    int64_t k_seq;
 };
 
 // Swizzle key of an LDS row: 64 banks x 4 bytes = 256 bytes per bank line, rows are 128 bytes, so rows r and r+1 cover
@@ -468,6 +474,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16_t 
                 uint4 ra, rb;
                 rope_rotate8(a, b, c0, c1, s0, s1, ra, rb);
                 bf16_t *dst = out + (int64_t)m * ldo + n;
+                if (qa.k_dst && n >= qa.k_start) dst = qa.k_dst + (m / qa.N) * qa.k_seq + (int64_t)(m % qa.N) * qa.ld_k + (n - qa.k_start);
                 *reinterpret_cast<uint4 *>(dst) = ra;
                 *reinterpret_cast<uint4 *>(dst + half) = rb;
             }
@@ -491,7 +498,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16_t 
                 }
             __syncthreads();
             constexpr int G16 = BM / 16;
-            const int n_v = Nout - qa.v_start;
             for (int u = tid; u < BN * G16 * 2; u += NT) {
                 const int h = u & 1, g = (u >> 1) % G16, col = u / (2 * G16);
                 const int m = m0 + g * 16, n = n0 + col;
@@ -499,7 +505,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16_t 
                 const unsigned char *src = lds + col * LDT + (g * 16 + 4 * h) * 2;
                 const uint2 lo = *reinterpret_cast<const uint2 *>(src), hi = *reinterpret_cast<const uint2 *>(src + 16);
                 const int sq = m / qa.N, i0 = m % qa.N;   // N % 16 == 0: the 16 keys belong to one sequence
-                bf16_t *dst = qa.vT + ((int64_t)sq * n_v + (n - qa.v_start)) * qa.ld_vt + i0 + 8 * h;
+                bf16_t *dst = qa.vT + sq * qa.vt_seq + (int64_t)(n - qa.v_start) * qa.ld_vt + i0 + 8 * h;
                 *reinterpret_cast<uint4 *>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
         }

@@ -182,7 +182,7 @@ int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_pe
 
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
-                          bf16_t *vT, int ld_vt, int tile, hipStream_t st) {
+                          const KvDest &kv, int tile, hipStream_t st) {
     Top1Args none = {};
     QkvArgs qa;
     qa.d_head = d_head;
@@ -191,8 +191,13 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
     qa.pos0 = pos0;
     qa.cos_t = cos_t;
     qa.sin_t = sin_t;
-    qa.vT = vT;
-    qa.ld_vt = ld_vt;
+    qa.vT = kv.vT;
+    qa.ld_vt = kv.ld_vt;
+    qa.vt_seq = kv.vt_seq;
+    qa.k_dst = kv.k;
+    qa.ld_k = kv.ld_k;
+    qa.k_start = kv.k_start;
+    qa.k_seq = kv.k_seq;
     const int m = (int)M;
     switch (tile) {
         case 1:   // (the 16x16x32 MFMA form: see dispatch)

@@ -165,8 +165,9 @@ int32_t run_head_confidence(psd_handle *h, const int32_t *tokens, const int32_t 
                             void *ws, hipStream_t st, int plan_N = -1 /* sequence length the workspace was planned
                             for, if not N (the cached forward plans for L rows per sequence) */);
 // forward over the L block rows of S sequences against their KV caches (context-causal block attention)
+// rows > 0 (kv.append only): the rows/L consecutive blocks from block_start on in one pass, each seeing the ones before it
 int32_t run_forward_cached(psd_handle *h, const int32_t *tokens, const int32_t *seq_rows, int S, int N, int block_start, int L,
-                           const KvCacheArg &kv, void *ws, int64_t ws_bytes, hipStream_t st);
+                           const KvCacheArg &kv, void *ws, int64_t ws_bytes, hipStream_t st, int rows = 0);
 int32_t run_head_logits(psd_handle *h, int S, int N, int L, float *logits, void *ws, hipStream_t st);
 // debug: layer `layer` alone on the caller's residual stream [S*N, d_model] (in place); see psd_debug_layer
 int32_t run_debug_layer(psd_handle *h, int layer, float *hidden, int S, int N, int L, int stop_after, void *ws, int64_t ws_bytes,
@@ -207,7 +208,8 @@ inline KvLayout kv_layout(const psd_model_config &c, int capacity) {
 struct KvCacheArg {
     void *base = nullptr;      // NULL: no cache (the call runs over whole sequences)
     int capacity = 0, len = 0, seqs_per_cache = 1;
-    bool append = false;       // store the rows' keys and values behind position len (seqs_per_cache must be 1)
+    bool append = false;       // store the rows' keys and values behind position len (seqs_per_cache must be 1); that is all such
+                               // a call is for: nothing behind the last layer's keys and values runs
     bool dual = false;         // approximate cache of a bidirectional model: the len = N - L entries are the positions
                                // OUTSIDE the block (prefix, then suffix), frozen by the whole-sequence call that
                                // entered the block; the block rows keep their positions block_start ..
@@ -287,9 +289,20 @@ int gemm_bf16_tile_count();
 // to pass on, or -1 when the shape has no tile that holds whole heads of one kind (then the two-pass form runs).
 // rows_per_seq: rows of A per sequence (a multiple of 16); v_start: first V column; pos0: position of a sequence's row 0.
 int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_per_seq);
+// Where the keys and the transposed values of that projection go: k = NULL: keys next to the queries in qkv, otherwise
+// straight into the sequences' KV caches (row i of sequence s at k[s * k_seq + i * ld_k], columns from k_start on); values at
+// vT[s * vt_seq + column * ld_vt + slot], slot the permuted key order of vt_key_slot.
+struct KvDest {
+    bf16_t *vT = nullptr;
+    int ld_vt = 0;
+    int64_t vt_seq = 0;
+    bf16_t *k = nullptr;
+    int ld_k = 0, k_start = 0;
+    int64_t k_seq = 0;
+};
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
-                          bf16_t *vT, int ld_vt, int tile, hipStream_t st);
+                          const KvDest &kv, int tile, hipStream_t st);
 // K-split of a residual contraction (1 = none).  With s > 1 parts, launch_gemm_bf16_split adds part 0 into
 // resid and stores parts 1..s-1 to partial [s-1][M][Nout] fp32; the next reader of resid adds them in order.
 int gemm_bf16_splits(int64_t M, int Nout, int Kin);
@@ -306,9 +319,13 @@ void launch_mfma_rate(const void *operands, int n_vec16, int iters, void *sink, 
 // A [M, Kin] with row stride lda, W / W2 [Nout, Kin] with row stride ldw (elements)
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,
                       const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st);
-// attention_mfma.hip (bf16, d_head 64 or 128): q, k from qkv (rotary applied), values from vT
+// attention_mfma.hip (bf16, d_head 64 or 128): q, k from qkv (rotary applied), values from vT (NULL: all keys are in the prefix)
 void launch_attention_bf16(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int n_heads, int n_kv_heads, int d_head,
                            bf16_t *out, const KvPrefix &pre, hipStream_t st);
+// context-causal blocks: the N queries of a sequence sit at positions pos0 .. (a multiple of block_len) and see the keys of
+// their own block and of everything before it, all of them (their own included) in the cache
+void launch_attention_causal_bf16(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int n_kv_heads, int d_head, bf16_t *out,
+                                  const KvPrefix &cache, int pos0, int block_len, hipStream_t st);
 // lm_head.hip (bf16): LM-head fused with the online top-1 / sum-exp reduction
 int64_t head_partial_bytes(int rows, int V);
 // fragment-order copies: [ceil(R/32)][K/16][64 lanes][8 bf16]

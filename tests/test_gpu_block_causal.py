@@ -279,6 +279,46 @@ def test_bf16_cached_call_at_128_and_256_rows_agrees_to_rounding():
     assert rel <= np.expm1(2 * 2e-2)
 
 
+@pytest.mark.parametrize("name", list(BF16))
+@pytest.mark.parametrize("L,blocks,B", [(16, 3, 1), (16, 9, 2), (32, 2, 3), (32, 7, 1), (48, 5, 1), (64, 1, 2), (64, 4, 1)])
+def test_prompt_in_one_pass_and_in_chunks_fills_the_same_cache(name, L, blocks, B):
+    """The prompt goes into the cache as many blocks at a time as the workspace holds: all at once, two at a time, one at a
+    time.  Blocks of 16 and 48 share key tiles and query tiles with their neighbours, and the unfilled cache holds NaNs.  The
+    first layer's keys and values are per-row products: the same bits however the prompt is cut.  The block behind the
+    prompt must give the oracle's logits within the bf16 bound every time."""
+    import ctypes as C
+
+    import paper_2605_15609_amd as psd
+    shape = BF16[name]
+    P, N = blocks * L, (blocks + 1) * L
+    host = inp.draw_model(shape, N)
+    model = psd.Model.from_host(host, DEV)
+    states = [_state(shape, N, P, L, 0, 50 + b, 3 + b) for b in range(B)]
+    d = _dev(np.stack([t for t, _ in states]))
+    first = []
+    for at_once in sorted({1, min(2, blocks), blocks}):
+        cache = psd.KvCache(model, B, N)
+        cache.mem.fill_(0xff)
+        need = model.lib.psd_workspace_bytes(C.byref(model.cfg), B, at_once * L, L)
+        ws = model.workspace(need)
+        rc = model.lib.psd_kv_prefill(model.handle, C.c_void_p(d.data_ptr()), B, N, P, L, C.c_void_p(cache.mem.data_ptr()), N,
+                                      C.c_void_p(ws.data_ptr()), need, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        per_seq = model.lib.psd_kv_cache_bytes(C.byref(model.cfg), N)
+        w, ld_vt = shape.n_kv_heads * shape.d_head, (N + 63) // 64 * 64
+        for b in range(B):
+            layer0 = cache.mem[b * per_seq:][: 2 * (N * w + w * ld_vt)].view(torch.int16)
+            keys, values = layer0[: N * w].view(N, w)[:P], layer0[N * w:].view(w, ld_vt)[:, : P]
+            first.append((b, torch.cat([keys.flatten(), values.flatten()]).cpu()))
+        top1, conf, logits = psd.psd_forward_confidence_cached(model, d, P, L, cache, want_logits=True)
+        logits = logits.cpu().numpy().reshape(B, L, -1)
+        for b, (t, _) in enumerate(states):
+            _check(shape, host, logits[b], top1[b].cpu().numpy(), conf[b].cpu().numpy(), t, P, L, 2e-2,
+                   f"{name} L={L} {at_once} of {blocks} blocks at once, seq {b}")
+    for b, bits in first:
+        assert torch.equal(bits, first[b][1]), "the first layer's keys and values depend on how the prompt is cut"
+
+
 def test_empty_prefix_full_cache_and_argument_errors():
     import paper_2605_15609_amd as psd
     shape = FP32
