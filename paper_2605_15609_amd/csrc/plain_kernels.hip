@@ -1,6 +1,8 @@
 // Debug path: plain kernels for any shape and either storage type, fp32 arithmetic, no
 // MFMA.  The fp32 model configuration runs entirely on these; for bf16 models they are the
 // on-device cross-check of the MFMA kernels (same rounding points, different algorithm).
+#include <type_traits>
+
 #include "psd_internal.h"
 #include "device_types.h"
 
@@ -64,6 +66,79 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(const T *__restrict__ A
             else
                 out[m * ldo + n] = from_float<TO>(v);
         }
+    }
+}
+
+// fp32 contraction of the fp32 models on v_mfma_f32_32x32x2_f32 (full fp32 products and sums).  Bound by latency at the sizes of
+// these models: one workgroup per 32x32 outputs, its four wavefronts deal the 8-k chunks of K among them and fetch straight into
+// registers, eight chunks in one memory round trip, without LDS or barriers until the four partial sums are added in wavefront
+// order.  (The tiled kernel above walks 16 k per two barriers and one round trip: 54 -> 5 us at 48 x 64 outputs, K = 256.)
+// A lane holds row lane % 32 and the k's 4 * (lane / 32) + 0..3 of a chunk; MFMA e of a chunk contracts k = e and 4 + e.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <bool DUAL>
+__global__ __launch_bounds__(256) void fp32_gemm_kernel(const float *__restrict__ A, const float *__restrict__ W,
+                                                        const float *__restrict__ W2, int64_t M, int Nout, int Kin, int lda, int ldw,
+                                                        int epi, const float *__restrict__ bias, float scale, float *__restrict__ out,
+                                                        float *__restrict__ resid, int ldo) {
+    constexpr int NP = DUAL ? 2 : 1, CH = 8;
+    __shared__ float part[NP][4][16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 31, lhalf = lane >> 5;
+    const int64_t m0 = (int64_t)blockIdx.y * 32;
+    const int n0 = blockIdx.x * 32;
+    const bool am = m0 + lrow < M, wn = n0 + lrow < Nout;
+    const float *ap = A + (m0 + lrow) * lda + 4 * lhalf, *wp = W + (int64_t)(n0 + lrow) * ldw + 4 * lhalf;
+    const float *wp2 = DUAL ? W2 + (int64_t)(n0 + lrow) * ldw + 4 * lhalf : nullptr;
+    f32x16 acc[NP];
+    for (int p = 0; p < NP; ++p)
+        for (int v = 0; v < 16; ++v) acc[p][v] = 0.f;
+    const int chunks = Kin / 8;
+    for (int c0 = wave; c0 < chunks; c0 += 4 * CH) {
+        f32x4 a[CH], w[NP][CH];
+#pragma unroll
+        for (int u = 0; u < CH; ++u) {
+            const int c = c0 + 4 * u;
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            a[u] = w[0][u] = zero;
+            if (am && c < chunks) a[u] = *reinterpret_cast<const f32x4 *>(ap + 8 * c);
+            if (wn && c < chunks) w[0][u] = *reinterpret_cast<const f32x4 *>(wp + 8 * c);
+            if constexpr (DUAL) {
+                w[1][u] = zero;
+                if (wn && c < chunks) w[1][u] = *reinterpret_cast<const f32x4 *>(wp2 + 8 * c);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][e], w[p][u][e], acc[p], 0, 0, 0);
+    }
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[p][wave][v][lane] = acc[p][v];
+    __syncthreads();
+    const int n = n0 + lrow;
+    if (n >= Nout) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // this wavefront's 4 of the 16 result rows per lane
+        const int64_t m = m0 + 8 * wave + 4 * lhalf + i;
+        if (m >= M) continue;
+        float s[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            s[p] = part[p][0][4 * wave + i][lane];
+            for (int w = 1; w < 4; ++w) s[p] += part[p][w][4 * wave + i][lane];
+        }
+        float v = s[0] * scale;
+        if (epi == EPI_BIAS) v += bias[n];
+        if (DUAL) v = v / (1.0f + expf(-v)) * s[NP - 1];
+        if (epi == EPI_RESIDUAL)
+            resid[m * ldo + n] += v;
+        else
+            out[m * ldo + n] = v;
     }
 }
 
@@ -198,6 +273,17 @@ __global__ void head_finish_kernel(const float *__restrict__ row_sum, const int3
 template <typename T, typename TO>
 void launch_plain_gemm(const T *A, const T *W, const T *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi, const float *bias,
                        float scale, TO *out, float *resid, int ldo, hipStream_t st) {
+    if constexpr (std::is_same_v<T, float> && std::is_same_v<TO, float>) {
+        // 16-byte fetches of whole 8-k chunks; anything else stays on the general kernel
+        const bool dual = epi == EPI_SWIGLU;
+        const uintptr_t ptrs = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(W) | (dual ? reinterpret_cast<uintptr_t>(W2) : 0);
+        if (Kin % 8 == 0 && lda % 4 == 0 && ldw % 4 == 0 && (ptrs & 15) == 0 && (M + 31) / 32 <= 65535) {
+            const dim3 tiles((Nout + 31) / 32, (unsigned)((M + 31) / 32));
+            if (dual) hipLaunchKernelGGL(fp32_gemm_kernel<true>, tiles, dim3(256), 0, st, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, scale, out, resid, ldo);
+            else hipLaunchKernelGGL(fp32_gemm_kernel<false>, tiles, dim3(256), 0, st, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, scale, out, resid, ldo);
+            return;
+        }
+    }
     dim3 grid((Nout + GT - 1) / GT, (unsigned)((M + GT - 1) / GT));
     hipLaunchKernelGGL((plain_gemm_kernel<T, TO>), grid, dim3(256), 0, st, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, scale, out,
                        resid, ldo);

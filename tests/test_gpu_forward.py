@@ -132,6 +132,19 @@ def test_fp32_debug_path_config1():
     _compare(model, host, states, 16, 32, 1e-4, "cfg1-fp32")
 
 
+@pytest.mark.parametrize("d,heads,kv,dh,ffn,vocab,N,S", [(72, 3, 1, 16, 88, 101, 33, 3),      # partial tiles, 8-k chunks for some wavefronts only
+                                                         (8, 1, 1, 8, 8, 33, 5, 1),            # one chunk: three wavefronts have nothing
+                                                         (264, 4, 2, 64, 520, 300, 65, 2),     # more than eight chunks a wavefront
+                                                         (36, 3, 1, 12, 48, 50, 20, 2)])       # K no multiple of 8: the general kernel
+def test_fp32_contractions_at_the_edges_of_their_tiles(d, heads, kv, dh, ffn, vocab, N, S):
+    from tests.gpu_common import make_models
+    shape = inp.cut_down(inp.WORKLOADS[1].shape, d_model=d, n_heads=heads, n_kv_heads=kv, d_head=dh, d_ffn=ffn, vocab=vocab, seed=31)
+    host, model = make_models(shape, N)
+    L = min(12, N - 1)
+    states = [_state(shape, N, N - L, L, 90 + s, s) for s in range(S)]
+    _compare(model, host, states, N - L, L, 1e-4, f"fp32 d={d} N={N}")
+
+
 @pytest.mark.parametrize("name", list(SHAPES))
 @pytest.mark.parametrize("plain", [7, 6, 5, 3, 0], ids=["all-plain", "mfma-gemm", "mfma-attn", "fused-head", "all-mfma"])
 def test_bf16_paths(name, plain):
