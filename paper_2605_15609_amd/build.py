@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpsd.so")
-SOURCES = ["api.hip", "forward.hip", "decide.hip", "elementwise.hip", "plain_kernels.hip", "gemm_mfma.hip",
+SOURCES = ["api.hip", "forward.hip", "decide.hip", "elementwise.hip", "plain_kernels.hip", "gemm_mfma.hip", "gemm_stream.hip",
            "attention_mfma.hip", "lm_head.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

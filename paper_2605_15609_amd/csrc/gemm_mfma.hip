@@ -80,6 +80,7 @@ bool tile_fits(int tile, int epi) { return epi != EPI_SWIGLU || tile == 0 || til
 
 }   // namespace
 
+static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 static int g_force_tile = -1, g_force_splits = 0, g_group_m = 4;
 // tile < 0: automatic.  Otherwise bits 0-7 the tile, bits 8-15 the K-split of the residual hook, bits 16-23 the band
 // height of the tile order (0 = leave it)
@@ -138,29 +139,23 @@ int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
     return best;
 }
 
-// A residual contraction over at most 128 rows is a weight stream with one row tile and few column tiles: far too
-// few workgroups to keep HBM busy.  It is cut along K instead, one 128x128 workgroup (rings 4/4) per (column tile,
-// K part), up to 256 workgroups; every part keeps at least 8 K stages.  Part 0 adds into resid, the others store
-// partial sums that the next reader of resid adds in order (at most 7 * 128 rows: cheap at this size; for taller
-// contractions the extra pass costs more than the split gains, measured).
+// A residual contraction over at most 128 rows is cut along K as the streaming kernel plans it: part 0 adds into resid, the
+// others store partial sums that the next reader of resid adds in order.
 int gemm_bf16_splits(int64_t M, int Nout, int Kin) {
     int splits = 1;
-    if (g_force_splits > 0) {
-        splits = g_force_splits;
-    } else if (g_force_tile < 0 && M <= 128) {
-        const int64_t tiles = (Nout + 127) / 128;
-        for (int s = 8; s >= 2; s >>= 1)
-            if (tiles * s <= 256 && Kin / s >= 8 * BK && Kin % (s * BK) == 0) {
-                splits = s;
-                break;
-            }
-    }
+    if (g_force_splits > 0) splits = g_force_splits;
+    else if (g_force_tile < 0 && M <= 128) splits = stream_plan(M, Nout, Kin, EPI_RESIDUAL, 1, 8).splits;
     if (splits > 8 || splits < 1 || Kin % (splits * BK) != 0) splits = 1;
     return splits;
 }
 
 void launch_gemm_bf16_split(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, float *resid, int ldo,
                             float *partial, int splits, hipStream_t st) {
+    if (g_force_splits == 0 && g_force_tile < 0) {
+        const StreamPlan plan = stream_plan(M, Nout, Kin, EPI_RESIDUAL, splits, splits);
+        if (plan.tiles && ldo % 4 == 0 && aligned16(resid) && aligned16(partial))
+            return launch_gemm_stream(plan, A, W, nullptr, M, Nout, Kin, lda, ldw, EPI_RESIDUAL, nullptr, nullptr, resid, ldo, partial, st);
+    }
     Top1Args none = {};
     launch_cfg<128, 128, 2, 2, EPI_RESIDUAL, 4, 4, S4>(A, W, nullptr, (int)M, Nout, Kin, lda, ldw, nullptr, nullptr, resid, ldo, none, st,
                                                      splits, partial);
@@ -214,6 +209,10 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,
                       const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st) {
     const int m = (int)M;
+    if (M <= 128 && g_force_tile < 0 && ldo % 4 == 0 && (aligned16(epi == EPI_RESIDUAL ? (void *)resid : (void *)out)) && (epi != EPI_BIAS || aligned16(bias))) {
+        const StreamPlan plan = stream_plan(M, Nout, Kin, epi, 1, 1);
+        if (plan.tiles) return launch_gemm_stream(plan, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, nullptr, st);
+    }
     switch (epi) {
         case EPI_STORE: dispatch<EPI_STORE>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
         case EPI_BIAS: dispatch<EPI_BIAS>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;

@@ -309,6 +309,14 @@ int gemm_bf16_splits(int64_t M, int Nout, int Kin);
 void launch_gemm_bf16_split(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, float *resid, int ldo,
                             float *partial, int splits, hipStream_t st);
 void launch_fold_partials(float *resid, int64_t rows, int cols, int ldo, const float *partial, int n_partial, hipStream_t st);
+// gemm_stream.hip: contractions over at most 128 rows.  tiles 16-row tiles of weights per workgroup (0: not for this kernel), K cut
+// into `splits` parts (partial sums as above)
+struct StreamPlan {
+    int tiles = 0, splits = 1;
+};
+StreamPlan stream_plan(int64_t M, int Nout, int Kin, int epi, int min_splits, int max_splits);
+void launch_gemm_stream(const StreamPlan &p, const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda,
+                        int ldw, int epi, const float *bias, bf16_t *out, float *resid, int ldo, float *partial, hipStream_t st);
 const char *gemm_bf16_tile_name(int tile);
 // debug, process-wide (not per handle; not for use while another thread launches): -1 = automatic; otherwise bits 0-7
 // the tile (0xff = automatic), bits 8-15 the K-split of residual contractions (0 = automatic), bits 16-23 the band

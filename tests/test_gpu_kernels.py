@@ -140,6 +140,40 @@ def test_gemm_residual_split_along_k(label, M, N, K, splits):
         assert np.array_equal(outs[0], outs[1]), f"{label} k_splits={s}: two runs differ"
 
 
+@pytest.mark.parametrize("epi", [0, 1, 2, 3], ids=["store", "bias", "residual", "swiglu"])
+def test_gemm_few_rows(epi):
+    """The streaming kernel of contractions over at most 128 rows: every row class (32, 64, 128) full, one over and one short of the
+    class below, slices of every width the plan gives (from a few to thousands of outputs, ragged last ones), K of one stage (the
+    ring is longer than K), of an odd number of stages, and long enough that the ring wraps several times."""
+    from paper_2605_15609_amd import binding as B
+    for M, N, K in [(1, 64, 64), (31, 832, 64), (32, 4160, 192), (33, 9024, 320), (64, 12352, 128), (65, 832, 1152), (100, 16448, 448),
+                    (127, 20544, 192), (128, 12288, 704)]:
+        print(f"[kernels] few rows M={M} N={N} K={K} epi={epi}", flush=True)
+        rng = np.random.default_rng(M + N + K)
+        A = bf16_round_trip(rng.standard_normal((M, K), dtype=np.float32))
+        W = bf16_round_trip(rng.standard_normal((N, K), dtype=np.float32) * 0.05)
+        W2 = bf16_round_trip(rng.standard_normal((N, K), dtype=np.float32) * 0.05) if epi == 3 else None
+        bias = rng.standard_normal(N).astype(np.float32)
+        resid0 = rng.standard_normal((M, N)).astype(np.float32)
+        a = A.astype(np.float64)
+        ref = a @ W.astype(np.float64).T
+        if epi == 1:
+            ref += bias
+        if epi == 3:
+            ref = orc.silu(ref) * (a @ W2.astype(np.float64).T)
+        if epi == 2:
+            ref += resid0
+            d_res = torch.from_numpy(resid0).to(DEV)
+            B.kernel_gemm_bf16(dev_bf16(A), dev_bf16(W), epi, resid=d_res)
+            got, tol = d_res.cpu().numpy().astype(np.float64), 1e-3 * np.sqrt(K / 4096) + 1e-6 * np.abs(ref)
+        else:
+            got = host_f64(B.kernel_gemm_bf16(dev_bf16(A), dev_bf16(W), epi, W2=None if W2 is None else dev_bf16(W2),
+                                              bias=torch.from_numpy(bias).to(DEV) if epi == 1 else None))
+            tol = 2.0 ** -8 * np.abs(ref) + 2e-3 * np.sqrt(K / 4096)
+        err = np.abs(got - ref)
+        assert (err <= tol).all(), f"M={M} N={N} K={K}: max err {err.max():.3e} at {np.unravel_index(err.argmax(), err.shape)}"
+
+
 ATTN_CASES = [("c3v", 4, 512, 32, 32, 128), ("c4v-gqa", 6, 1024, 28, 4, 128), ("c2v", 4, 384, 8, 8, 64),
               ("c5-len", 2, 1280, 32, 32, 128), ("ragged", 3, 200, 4, 2, 64)]
 
