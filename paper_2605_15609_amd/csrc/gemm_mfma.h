@@ -215,6 +215,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16_t 
     const int voff_y = (lane / LPR) * ldy * 2 + (((lane % LPR) ^ dma_key) << 4);
     constexpr int GA = BM / RPI / NW, GB = BN / RPI / NW;   // row groups per wavefront, A and B tile
     constexpr int NLD = GA + GB;                      // DMA instructions per wavefront per stage
+    constexpr bool SPLIT_GROUPS = DUAL && (BN / 2) % (RPI * NW) != 0;   // one fetch instruction of the wavefronts holds gate and up rows
     typedef __attribute__((address_space(3))) void lds_void;
 
 // global -> LDS: one stage of the X tile / of the Y tile, K position k0, into ring slot `slot`
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) void gemm_bf16_kernel(const bf16_t 
             unsigned char *sb_ = lds + B_RING + (slot) * B_BYTES + uw_ * 1024;                                \
             _Pragma("unroll") for (int j = 0; j < GB; ++j) {                                                  \
                 if (!((half) < 0 || (j < (GB + 1) / 2) == ((half) == 0))) continue;                           \
-                if (DUAL && j * (RPI * NW) >= BN / 2)                                                         \
+                if (DUAL && (SPLIT_GROUPS ? (j * NW + uw_) * RPI >= BN / 2 : j * (RPI * NW) >= BN / 2))       \
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_y2, (lds_void *)(sb_ + j * (NW * 1024)), 16, voff_y, \
                                                              (((j * NW + uw_) * RPI - BN / 2) * ldy + (k0)) * 2, 0, 0); \
                 else                                                                                          \

@@ -33,7 +33,7 @@ constexpr TileCfg kTiles[] = {
     {128, 64, "128x64, 4 wavefronts, LDS rings 4/4"},     // lone workgroup per CU: fetches several stages ahead
     {128, 128, "128x128, 4 wavefronts, LDS rings 4/4"},
     {64, 64, "64x64, 4 wavefronts, LDS rings 4/4"},
-    {256, 128, "256x128, 8 wavefronts, LDS rings 2/4"},   // one full round of 256 workgroups for 2048 x 4096 outputs
+    {256, 128, "256x128, 8 wavefronts, LDS rings 3/4"},   // one full round of 256 workgroups for 2048 x 4096 outputs
     {256, 256, "256x256, 8 wavefronts, 16x16x32 MFMAs, LDS rings 2/3"},
     {128, 128, "128x128, 4 wavefronts, 16x16x32 MFMAs, LDS rings 2/3"},
 };
@@ -46,13 +46,19 @@ void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nou
     const int tile = gemm_bf16_tile(M, Nout, EPI, Kin);
     // SwiGLU needs an even number of 32-column subtiles per wavefront (gate and up halves); gemm_bf16_tile
     // never returns the others for it
+    if constexpr (EPI == EPI_SWIGLU) {
+        if (tile == 2) return launch_cfg<256, 192, 4, 2, EPI, 2, 4, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
+    }
     if constexpr (EPI != EPI_SWIGLU) {
         switch (tile) {
             case 2: return launch_cfg<256, 192, 4, 2, EPI, 2, 4, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
             case 3: return launch_cfg<128, 192, 2, 2, EPI, 2, 2, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
             case 4: return launch_cfg<128, 64, 2, 2, EPI, 4, 4, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
             case 6: return launch_cfg<64, 64, 2, 2, EPI, 4, 4, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            case 7: return launch_cfg<256, 128, 4, 2, EPI, 2, 4, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
+            case 7:   // (the faster MFMA form of each, as for tile 1)
+                if (EPI != EPI_RESIDUAL || Kin <= 4096)
+                    return launch_cfg<256, 128, 4, 2, EPI, 3, 4, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
+                return launch_cfg<256, 128, 4, 2, EPI, 3, 4, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
             default: break;
         }
     }
@@ -76,7 +82,7 @@ void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nou
     }
 }
 
-bool tile_fits(int tile, int epi) { return epi != EPI_SWIGLU || tile == 0 || tile == 1 || tile == 5 || tile == 8 || tile == 9; }
+bool tile_fits(int tile, int epi) { return epi != EPI_SWIGLU || tile == 0 || tile == 1 || tile == 2 || tile == 5 || tile == 8 || tile == 9; }
 
 }   // namespace
 
@@ -102,7 +108,14 @@ int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
     // SwiGLU reads two weight operands against one activation tile: the big tile as soon as it
     // reaches half of the CUs
     // (a single row tile is a pure weight stream: the deep equal rings keep more of it in flight)
-    if (dual) return tiles(256, 256) >= 128 ? 1 : (M <= 128 ? 5 : 0);
+    // A partial round costs a whole one, and a round of 256x192 tiles (96 gate and 96 up columns) 0.84 of a round of 256x256: it
+    // wins where it needs no more rounds (2 x 12288 outputs, K = 4096: 512 rows 103 -> 96 us, 300 rows 94.5 -> 88, 700 rows
+    // 175 -> 153; 1671 rows 280 against 316 and 2048 rows 303 against 338 stay on 256x256).
+    if (dual) {
+        const int64_t big = tiles(256, 256);
+        if (big < 128) return M <= 128 ? 5 : 0;
+        return (tiles(256, 192) + 255) / 256 <= (big + 255) / 256 ? 2 : 1;
+    }
     // At most one 128x128 workgroup per CU: the contraction is bound by fetch latency, not by the
     // matrix cores; small tiles reach every CU and the deep rings keep several stages in flight.
     if (tiles(128, 128) <= 256) {
@@ -118,13 +131,15 @@ int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
         double rate;
     };
     // Residual contractions (fp32 read-modify-write epilogue), measured at 2048 x 4096 and 6144 x 3584 outputs: 256x192 beats
-    // 128x192 by 2 - 8 %; with a long K (12288: 215 against 235 us) one full round of 256x128 tiles beats two 128x128
-    // workgroups per CU, with K = 4096 it does not (the 128x128 tile in its 16x16x32 form: 73 against 77 us).  Kin = 0:
-    // unknown, taken as long.  Store epilogues: per round of workgroups the 256x128 tile is 5 - 15 % ahead of 128x128 (512 x 12288
-    // outputs: 57 against 69 us) and behind 256x192.
+    // 128x192 by 2 - 8 % and three rounds of 256x128 (K = 18944: 790 against 820 us, K = 3584: 155 against 163); one full round of
+    // 256x128 beats two 128x128 workgroups per CU (K = 4096: 66 against 75 us, in the 16x16x32 MFMA form; K = 12288, where the
+    // 32x32x16 form is level with it, 236 against 238).  Kin = 0: unknown, taken as long.  Store epilogues: the 256x128 tile is
+    // ahead of 128x128 per round of workgroups (512 x 12288 outputs: 53 against 68 us) and behind 256x192.
+    // (With the activation ring one stage deeper, 3/4 against 2/4, the 256x128 tile takes 236 us instead of 264 on 2048 x 4096
+    // outputs at K = 12288, 66 instead of 73 at K = 4096, and 53 instead of 56 on 512 x 12288.)
     const bool resid = epi == EPI_RESIDUAL;
     const Cand cand[] = {{1, 256, 1.25}, {2, 256, 1.16}, {3, 512, resid ? 1.12 : 1.15}, {0, 512, 1.00},
-                         {7, 256, !resid ? 1.03 : (Kin == 0 || Kin > 4096) ? 1.08 : 0.90}};
+                         {7, 256, !resid ? 1.06 : (Kin == 0 || Kin > 4096) ? 1.12 : 1.05}};
     int best = 0;
     double best_cost = 0;
     for (const Cand &c : cand) {
@@ -194,16 +209,39 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
     qa.k_start = kv.k_start;
     qa.k_seq = kv.k_seq;
     const int m = (int)M;
-    switch (tile) {
-        case 1:   // (the 16x16x32 MFMA form: see dispatch)
-        case 8: return launch_cfg<256, 256, 4, 2, EPI_QKV, 2, 3, S8, 16>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
-        case 4: return launch_cfg<128, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
-        case 5: return launch_cfg<128, 128, 2, 2, EPI_QKV, 4, 4, S4>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
-        case 6: return launch_cfg<64, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
-        case 7: return launch_cfg<256, 128, 4, 2, EPI_QKV, 2, 4, S8>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
-        case 9:
-        default: return launch_cfg<128, 128, 2, 2, EPI_QKV, 2, 3, S4, 16>(A, W, nullptr, m, Nout, Kin, lda, ldw, bias, qkv, nullptr, ld_qkv, none, st, 1, nullptr, qa);
+    // columns [c0, c0 + cols) on tile t
+    auto part = [&](int t, int c0, int cols) {
+        QkvArgs q = qa;
+        q.v_start -= c0;
+        q.k_start -= c0;
+        switch (t) {
+            case 1:   // (the 16x16x32 MFMA form: see dispatch)
+            case 8: return launch_cfg<256, 256, 4, 2, EPI_QKV, 2, 3, S8, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+            case 4: return launch_cfg<128, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+            case 5: return launch_cfg<128, 128, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+            case 6: return launch_cfg<64, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+            case 7: return launch_cfg<256, 128, 4, 2, EPI_QKV, 3, 4, S8, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+            case 9:
+            default: return launch_cfg<128, 128, 2, 2, EPI_QKV, 2, 3, S4, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
+        }
+    };
+    // A partial last round of 256x256 tiles costs almost a whole one.  Where the column tiles of the whole rounds come out even
+    // enough, the columns behind them run as a launch of their own in smaller tiles, one round of which is shorter (2048 x 12288
+    // outputs, K = 4096: 384 tiles in 179 us; 256 of them in 99, the other 4096 columns in 57 on 256x128 tiles).  Costs as in
+    // gemm_bf16_tile; the second launch takes some 3 us, 2000 units at that K.
+    if (tile == 1 && g_force_tile < 0) {
+        const int64_t tm = (M + 255) / 256, n = tm * ((Nout + 255) / 256), whole = n / 256 * 256 / tm;
+        const int c0 = (int)whole * 256;
+        if (n % 256 != 0 && n < 8 * 256 && whole > 0 && c0 < Nout) {
+            auto cost = [&](int64_t tiles, double area, double rate) { return (double)((tiles + 255) / 256) * area / rate; };
+            const double rest = cost(tm * ((Nout - c0 + 127) / 128), 32768, 1.06);
+            if (cost(whole * tm, 65536, 1.25) + rest + 2000.0 * 4096 / Kin < cost(n, 65536, 1.25)) {
+                part(1, 0, c0);
+                return part(7, c0, Nout - c0);
+            }
+        }
     }
+    part(tile, 0, Nout);
 }
 
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,

@@ -235,6 +235,26 @@ def test_qkv_epilogue_on_every_tile_configuration(name, N, S):
     say(f"[forward] fused QKV epilogue {name}: bit-identical on all {lib.psd_kernel_gemm_tile_count()} tile configurations")
 
 
+@pytest.mark.parametrize("heads,kv_heads", [(32, 32), (60, 12)], ids=["cut-at-v", "cut-inside-k"])
+def test_qkv_projection_in_two_launches_changes_no_bit(heads, kv_heads):
+    """2048 rows whose 256x256 tiles are one whole round and a part of one: the columns behind the whole round run as a launch
+    of their own.  The cut falls on the first V column, or on a k head with both k and V columns behind it."""
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    N, S, L = 512, 4, 16
+    shape = inp.cut_down(inp.WORKLOADS[4].shape, n_layers=1, d_model=512, n_heads=heads, n_kv_heads=kv_heads, d_ffn=640, vocab=3001,
+                         seed=23)
+    assert shape.d_head == 128 and 256 < S * N // 256 * ((heads + 2 * kv_heads) * 128 // 256) < 512
+    host, model = make_models(shape, N)
+    d = to_dev(np.stack([_state(shape, N, N - 2 * L, L, 80 + s, 5 * s) for s in range(S)]))
+    out = {}
+    for mask in (0, 8):
+        model.set_plain(mask)
+        out[mask] = psd.psd_forward_logits(model, d, N - 2 * L, L).cpu().numpy()
+    model.set_plain(0)
+    assert np.isfinite(out[0]).all() and (out[0] == out[8]).all()
+
+
 def test_batched_forward_equals_single(monkeypatch):
     """Batching S sequences must not change any sequence's (top1, conf) by more than rounding
     of the tile schedule; the decisions of the all-MFMA path must agree exactly here."""
