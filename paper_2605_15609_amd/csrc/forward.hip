@@ -68,6 +68,9 @@ struct Dispatch<float> {
     static bool append_attention(psd_handle *, const float *, int, int, int, int, int, int, float *, const KvPrefix &, int, int, hipStream_t) {
         return false;
     }
+    static bool block_attention(psd_handle *, const float *, int, int, int, int, int, int, int, float *, const KvPrefix &, hipStream_t) {
+        return false;
+    }
     static void rope_attention(psd_handle *h, float *qkv, int ld_qkv, float *, int S, int N, int pos0, int H, int Hkv, int dh,
                                float *out, const KvPrefix &pre, int block_len, hipStream_t st, bool = false) {
         launch_rope<float>(qkv, ld_qkv, (int64_t)S * N, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, st);
@@ -136,6 +139,14 @@ struct Dispatch<bf16_t> {
     // Any sequence length runs on the matrix cores: the last key tile of a sequence is cut by the descriptors (keys) and in
     // registers (values), whatever its length.  (Lengths that were no multiple of 8 used to take the plain kernel: 8546 against
     // 126 us per layer at 12 x 557 tokens, 32 heads of 128.)
+    // Block rows of a cached call (nothing reads their rotated keys afterwards): rotary and attention in one launch.  false: not on
+    // this path (a block of more than 64 rows, a debug switch)
+    static bool block_attention(psd_handle *h, const bf16_t *qkv, int ld_qkv, int S, int N, int pos0, int H, int Hkv, int dh, bf16_t *out,
+                                const KvPrefix &pre, hipStream_t st) {
+        if ((h->plain_mask & (2 | 8)) || !attention_block_fits(qkv, ld_qkv, S, N, H, dh, out, pre, h->rope_cos, h->rope_sin)) return false;
+        launch_attention_block(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, pos0, h->rope_cos, h->rope_sin, st);
+        return true;
+    }
     static void rope_attention(psd_handle *h, bf16_t *qkv, int ld_qkv, bf16_t *vT, int S, int N, int pos0, int H, int Hkv, int dh,
                                bf16_t *out, const KvPrefix &pre, int block_len, hipStream_t st, bool rotated = false) {
         if (rotated) {
@@ -308,7 +319,7 @@ int32_t forward_cached_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             all.len = kv.len + R;
             if (!Dispatch<T>::append_attention(h, qkv, ld_qkv, S, R, H, Hkv, dh, o, all, block_start, L, st))
                 launch_plain_attention<T>(qkv, ld_qkv, S, R, H, Hkv, dh, o, pre, L, st);
-        } else {
+        } else if (!Dispatch<T>::block_attention(h, qkv, ld_qkv, S, R, block_start, H, Hkv, dh, o, pre, st)) {
             Dispatch<T>::rope_attention(h, qkv, ld_qkv, vT, S, R, block_start, H, Hkv, dh, o, pre, 0, st);
         }
         pend = Dispatch<T>::gemm(h, o, H * dh, lw.wo, nullptr, H * dh, nrow, d, H * dh, EPI_RESIDUAL, nullptr, nullptr, hbuf, d, ksplit, st);

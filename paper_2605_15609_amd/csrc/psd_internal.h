@@ -330,6 +330,11 @@ void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_
 // attention_mfma.hip (bf16, d_head 64 or 128): q, k from qkv (rotary applied), values from vT (NULL: all keys are in the prefix)
 void launch_attention_bf16(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int n_heads, int n_kv_heads, int d_head,
                            bf16_t *out, const KvPrefix &pre, hipStream_t st);
+// attention_block.hip (bf16): at most 64 own rows a sequence at positions pos0 .., neither rotated nor stored yet, against a cache
+bool attention_block_fits(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int d_head, const bf16_t *out, const KvPrefix &pre,
+                          const float *cos_t, const float *sin_t);
+void launch_attention_block(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int n_kv_heads, int d_head, bf16_t *out,
+                            const KvPrefix &pre, int pos0, const float *cos_t, const float *sin_t, hipStream_t st);
 // context-causal blocks: the N queries of a sequence sit at positions pos0 .. (a multiple of block_len) and see the keys of
 // their own block and of everything before it, all of them (their own included) in the cache
 void launch_attention_causal_bf16(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int n_kv_heads, int d_head, bf16_t *out,

@@ -319,6 +319,33 @@ def test_prompt_in_one_pass_and_in_chunks_fills_the_same_cache(name, L, blocks, 
         assert torch.equal(bits, first[b][1]), "the first layer's keys and values depend on how the prompt is cut"
 
 
+@pytest.mark.parametrize("name,L,blocks,B", [("mha-dh64", 16, 0, 2), ("mha-dh64", 48, 3, 2), ("mha-dh64", 64, 1, 1), ("mha-dh64", 32, 31, 1),
+                                             ("gqa-bias-dh128", 16, 1, 3), ("gqa-bias-dh128", 16, 5, 1), ("gqa-bias-dh128", 32, 8, 2),
+                                             ("gqa-bias-dh128", 48, 1, 1), ("gqa-bias-dh128", 64, 3, 33), ("gqa-bias-dh128", 64, 5, 1),
+                                             ("gqa-bias-dh128", 32, 24, 1), ("gqa-bias-dh128", 32, 25, 1)])
+def test_block_rows_rotate_and_attend_in_one_launch(name, L, blocks, B):
+    """Prefixes that are empty, end inside a tile, fill the wavefronts evenly or not, and both sides of the rule that picks the
+    kernel, against the oracle and against the launches it replaces (bit 3 of the debug mask)."""
+    import paper_2605_15609_amd as psd
+    shape = BF16[name]
+    P, N = blocks * L, (blocks + 2) * L
+    host = inp.draw_model(shape, N)
+    model = psd.Model.from_host(host, DEV)
+    states = [_state(shape, N, P, L, 0, 110 + b, (5 * b) % L) for b in range(B)]
+    d = _dev(np.stack([t for t, _ in states]))
+    cache = psd.KvCache(model, B, N)
+    psd.psd_kv_prefill(model, d, P, L, cache)
+    top1, conf, logits = psd.psd_forward_confidence_cached(model, d, P, L, cache, want_logits=True)
+    model.set_plain(8)
+    _, _, two_pass = psd.psd_forward_confidence_cached(model, d, P, L, cache, want_logits=True)
+    model.set_plain(0)
+    # the two differ in how probabilities are grouped, then by bf16 rounding through two layers: inside the oracle's band
+    assert float((logits - two_pass).abs().max()) < 2e-2
+    b = B - 1
+    _check(shape, host, logits.cpu().numpy().reshape(B, L, -1)[b], top1[b].cpu().numpy(), conf[b].cpu().numpy(), states[b][0], P, L, 2e-2,
+           f"{name} L={L} blocks={blocks} seq {b} of {B}")
+
+
 def test_empty_prefix_full_cache_and_argument_errors():
     import paper_2605_15609_amd as psd
     shape = FP32
