@@ -8,9 +8,8 @@
 // value row are a fragment as they are: no ring, barrier or swizzle), and the partial results meet once in LDS.  The own rows pass
 // through LDS, rotated on the way, while a wavefront's first keys are under way.
 // One wavefront per SIMD: a tile's keys, values, scores and outputs are 224 registers a lane, and at 256 the compiler spills 53 of
-// them (22 us instead of 14).  With it, against rotary + transpose launch and key-split kernel: 32 heads of 128, 32 rows, 256
-// cached positions, 1 sequence 17.0 -> 14.3 us, 4 sequences 19.9 -> 14.2; 28 heads on 4 KV heads, 24 sequences, 512 positions
-// 61.8 -> 55.5.  The next tile's operands fetched ahead into a second register set: 5 - 8 % slower; eight wavefronts spill.
+// them (22 us instead of 14).  With it, against rotary + transpose launch and key-split kernel: 32 heads of 128, 32 rows, 448
+// cached positions, 1 sequence 17.0 -> 14.3 us, 4 sequences 19.9 -> 14.2.  The next tile's operands fetched ahead into a second register set: 5 - 8 % slower; eight wavefronts spill.
 #include "psd_internal.h"
 #include "device_types.h"
 #include "rope_device.h"
@@ -256,9 +255,11 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 }   // namespace
 
-// Long prefixes and many workgroups are throughput, where the tiles that attention_kernel shares in LDS win: 32 rows of 32 heads of
-// 128 against 1152 positions 37 us here and 31 there (8 sequences), so up to three tiles a wavefront and the own one; 64 rows, whose
-// keys two workgroups fetch, 30 against 36 us in 256 workgroups but 110 against 61 in 1024, so one round of workgroups.
+// Long prefixes and many workgroups are throughput, where the tiles that attention_kernel shares in LDS win.  32 rows: 448 positions
+// as above; 896 positions, 28 heads on 4 KV heads, level with 4 sequences (20.8 against 20.5 us) and ahead with 24 (55.5 against
+// 61.8); 1216 positions, 32 heads, 8 sequences, behind (37 against 31).  The line lies at three tiles a wavefront, before the two
+// meet.  33 to 64 rows, whose keys two workgroups fetch: 30 against 36 us in 256 workgroups, 110 against 61 in 1024 (1216 positions),
+// so one round of workgroups.
 bool attention_block_fits(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int d_head, const bf16_t *out, const KvPrefix &pre,
                           const float *cos_t, const float *sin_t) {
     if (N <= 32 ? pre.len > 3 * KSP * BKV : (int64_t)((N + 31) / 32) * n_heads * S > 256) return false;
