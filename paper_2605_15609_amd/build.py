@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpsd.so")
 SOURCES = ["api.hip", "forward.hip", "decide.hip", "elementwise.hip", "plain_kernels.hip", "gemm_mfma.hip", "gemm_stream.hip",
-           "attention_mfma.hip", "attention_block.hip", "lm_head.hip"]
+           "attention_mfma.hip", "attention_ordered.hip", "attention_block.hip", "lm_head.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

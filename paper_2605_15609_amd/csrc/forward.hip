@@ -136,9 +136,8 @@ struct Dispatch<bf16_t> {
     // pre: KV prefix that every own row sees; block_len > 0: context-causal blocks among the own rows (only the
     // plain kernel masks; the product path of that attention mode keeps finished blocks in the prefix instead).
     // rotated: qkv_fused produced qkv and vT, only the attention is left.
-    // Any sequence length runs on the matrix cores: the last key tile of a sequence is cut by the descriptors (keys) and in
-    // registers (values), whatever its length.  (Lengths that were no multiple of 8 used to take the plain kernel: 8546 against
-    // 126 us per layer at 12 x 557 tokens, 32 heads of 128.)
+    // Lengths that are no multiple of 8 keep fp32 probabilities and the plain kernel's order of sums; whole sequences of them run on
+    // the fp32 matrix instructions with the same bits.
     // Block rows of a cached call (nothing reads their rotated keys afterwards): rotary and attention in one launch.  false: not on
     // this path (a block of more than 64 rows, a debug switch)
     static bool block_attention(psd_handle *h, const bf16_t *qkv, int ld_qkv, int S, int N, int pos0, int H, int Hkv, int dh, bf16_t *out,
@@ -151,9 +150,11 @@ struct Dispatch<bf16_t> {
                                bf16_t *out, const KvPrefix &pre, int block_len, hipStream_t st, bool rotated = false) {
         if (rotated) {
             launch_attention_bf16(qkv, ld_qkv, vT, S, N, H, Hkv, dh, out, pre, st);
-        } else if ((h->plain_mask & 2) || (block_len > 0 && block_len < N)) {
+        } else if ((h->plain_mask & 2) || (N % 8) != 0 || (block_len > 0 && block_len < N)) {
             launch_rope<bf16_t>(qkv, ld_qkv, (int64_t)S * N, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, st);
-            launch_plain_attention<bf16_t>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
+            const bool whole = !(h->plain_mask & 2) && pre.len == 0 && !(block_len > 0 && block_len < N);
+            if (!whole || !launch_attention_ordered(qkv, ld_qkv, S, N, H, Hkv, dh, out, st))
+                launch_plain_attention<bf16_t>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
         } else {
             // the matrix-core kernel reads V transposed; rotary and that transpose share one launch
             launch_rope_transpose_v(qkv, ld_qkv, S, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, vT, st);

@@ -330,6 +330,10 @@ void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_
 // attention_mfma.hip (bf16, d_head 64 or 128): q, k from qkv (rotary applied), values from vT (NULL: all keys are in the prefix)
 void launch_attention_bf16(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int n_heads, int n_kv_heads, int d_head,
                            bf16_t *out, const KvPrefix &pre, hipStream_t st);
+// attention_ordered.hip (bf16): whole sequences, row-major q, k (rotary applied) and v from qkv, the bits of launch_plain_attention;
+// false: not for this kernel (too many keys for its LDS)
+bool launch_attention_ordered(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int n_kv_heads, int d_head, bf16_t *out,
+                              hipStream_t st);
 // attention_block.hip (bf16): at most 64 own rows a sequence at positions pos0 .., neither rotated nor stored yet, against a cache
 bool attention_block_fits(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int d_head, const bf16_t *out, const KvPrefix &pre,
                           const float *cos_t, const float *sin_t);

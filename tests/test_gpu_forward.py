@@ -173,6 +173,25 @@ def test_sequences_of_no_round_length_run_on_the_matrix_core_attention(name, N):
     _compare(model, host, states, N - L, L, 2e-2, f"{name} N={N}")
 
 
+@pytest.mark.parametrize("name", ["small-2l", "gqa-bias"])
+@pytest.mark.parametrize("N,S", [(9, 3), (31, 2), (33, 1), (63, 4), (70, 3), (127, 1), (197, 5), (1271, 1), (1273, 1), (2543, 1), (2545, 1)])
+def test_sequences_of_no_round_length_keep_the_plain_kernels_bits(name, N, S):
+    """fp32 probabilities and every sum in the plain kernel's order: logits of the product path equal those with the plain
+    attention kernel (bit 1 of the debug mask) bit for bit.  Lengths around tiles of 16 and 32 keys and queries, around the
+    64 partial sums, and on both sides of the two lengths where the scores of 32 and of 16 queries stop fitting LDS."""
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    shape, L = SHAPES[name][0], 8
+    _, model = make_models(shape, N)
+    d = to_dev(np.stack([_state(shape, N, N - L, L, 60 + s, s) for s in range(S)]))
+    out = {}
+    for mask in (0, 2):
+        model.set_plain(mask)
+        out[mask] = psd.psd_forward_logits(model, d, N - L, L).cpu().numpy()
+    model.set_plain(0)
+    assert np.isfinite(out[0]).all() and (out[0] == out[2]).all(), f"{(out[0] != out[2]).mean():.3f} of the logits differ"
+
+
 @pytest.mark.parametrize("name,N,S", [("small-2l", 192, 1), ("small-2l", 48, 11), ("small-2l", 384, 4), ("gqa-bias", 144, 1),
                                       ("gqa-bias", 272, 5), ("gqa-bias", 1280, 2)])
 def test_rotary_and_value_transpose_in_the_qkv_epilogue_change_no_bit(name, N, S):
