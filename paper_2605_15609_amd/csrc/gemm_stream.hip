@@ -59,20 +59,25 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const bf16_t *__res
     // groups of 8 rows, one fetch each, dealt to the wavefronts in turn: the swizzle key of a group is a constant of the wavefront
     const int key = (((wave & 1) << 2) + (lane >> 4)) & 7;
     const int voff_x = (lane >> 3) * ldx * 2 + (((lane & 7) ^ key) << 4), voff_y = (lane >> 3) * ldy * 2 + (((lane & 7) ^ key) << 4);
+    // A stage past the end of K is fetched from offsets that every descriptor rejects: no traffic, and the counts of fetches in
+    // flight stay what the waits assume.  (At its own offsets it would read the next part of K or the next row: with a ring of 9
+    // stages 41 stages for the 32 of a half of K = 4096.)
+    const int voff_none = 0x7ffffff0;
     auto fetch = [&](int slot, int kt) {
         unsigned char *s = lds + slot * STAGE + wave * 1024;
         const int k0 = kt * BK;
+        const int vx = kt < nk ? voff_x : voff_none, vy = kt < nk ? voff_y : voff_none;
 #pragma unroll
         for (int j = 0; j < GX; ++j)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(s + j * 4096), 16, voff_x, ((j * 4 + wave) * 8 * ldx + k0) * 2, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(s + j * 4096), 16, vx, ((j * 4 + wave) * 8 * ldx + k0) * 2, 0, 0);
 #pragma unroll
         for (int j = 0; j < GY; ++j) {
             const int g = j * 4 + wave;
             if (GYT % 4 == 0 || g < GYT) {
                 if (DUAL && g >= NC / 8)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ry2, (lds_void *)(s + (GX + j) * 4096), 16, voff_y, ((g * 8 - NC) * ldy + k0) * 2, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ry2, (lds_void *)(s + (GX + j) * 4096), 16, vy, ((g * 8 - NC) * ldy + k0) * 2, 0, 0);
                 else
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, (lds_void *)(s + (GX + j) * 4096), 16, voff_y, (g * 8 * ldy + k0) * 2, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, (lds_void *)(s + (GX + j) * 4096), 16, vy, (g * 8 * ldy + k0) * 2, 0, 0);
             }
         }
     };
@@ -128,8 +133,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const bf16_t *__res
     PSD_STREAM_SYNC(NS - 1)
     frags(0, 0);
     // Stage kt computes from registers.  Meanwhile stage kt + 1 has landed and is read, and stage kt + NS goes into the slot of
-    // stage kt, which every wavefront has read before the barrier.  Fetches past the end of K stay in the buffer range or are
-    // rejected, and are never used.
+    // stage kt, which every wavefront has read before the barrier.
     int slot = 0;
     auto step = [&](int kt, int set) {
         PSD_STREAM_SYNC(NS - 2)
