@@ -154,12 +154,14 @@ int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
     return best;
 }
 
-// A residual contraction over at most 128 rows is cut along K as the streaming kernel plans it: part 0 adds into resid, the
-// others store partial sums that the next reader of resid adds in order.
+// A residual contraction over at most 128 rows is cut along K: part 0 adds into resid, the others store partial sums that the next
+// reader of resid adds in order.  The parts are those the streaming kernel plans for 128 rows, whatever the number of rows: a
+// sequence's sums must not depend on how many rows share its call.  At most four: eight cost the norm more than they save here
+// (8B cached iteration 9.42 ms, with four 9.04, with the plan of each row count 9.06).
 int gemm_bf16_splits(int64_t M, int Nout, int Kin) {
     int splits = 1;
     if (g_force_splits > 0) splits = g_force_splits;
-    else if (g_force_tile < 0 && M <= 128) splits = stream_plan(M, Nout, Kin, EPI_RESIDUAL, 1, 8).splits;
+    else if (g_force_tile < 0 && M <= 128) splits = stream_plan(128, Nout, Kin, EPI_RESIDUAL, 1, 4).splits;
     if (splits > 8 || splits < 1 || Kin % (splits * BK) != 0) splits = 1;
     return splits;
 }

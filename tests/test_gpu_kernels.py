@@ -140,6 +140,23 @@ def test_gemm_residual_split_along_k(label, M, N, K, splits):
         assert np.array_equal(outs[0], outs[1]), f"{label} k_splits={s}: two runs differ"
 
 
+@pytest.mark.parametrize("N,K", [(4096, 4096), (4096, 12288), (3584, 3584), (3584, 18944), (512, 512), (512, 1408), (512, 640)])
+def test_sums_of_few_rows_do_not_depend_on_their_number(N, K):
+    """The residual contractions of a cached call, cut along K as the forward cuts them: a row's sum has the same bits whether 1, 16, ..
+    or 128 rows share the call (every row class of the streaming kernel, its edges and one over)."""
+    from paper_2605_15609_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + K)
+    A = torch.empty((128, K), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    W = torch.empty((N, K), dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g)
+    full = torch.zeros((128, N), dtype=torch.float32, device=DEV)
+    parts = B.kernel_gemm_residual_splitk(A, W, full)
+    for M in (1, 16, 17, 32, 33, 48, 64, 65, 127):
+        got = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+        assert B.kernel_gemm_residual_splitk(A[:M], W, got) == parts, f"{M} rows: another number of parts"
+        assert torch.equal(got, full[:M]), f"{M} rows: other bits"
+
+
 @pytest.mark.parametrize("epi", [0, 1, 2, 3], ids=["store", "bias", "residual", "swiglu"])
 def test_gemm_few_rows(epi):
     """The streaming kernel of contractions over at most 128 rows: every row class (32, 64, 128) full, one over and one short of the
