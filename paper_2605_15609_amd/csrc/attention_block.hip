@@ -255,15 +255,20 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 }   // namespace
 
-// Long prefixes and many workgroups are throughput, where the tiles that attention_kernel shares in LDS win.  32 rows: 448 positions
-// as above; 896 positions, 28 heads on 4 KV heads, level with 4 sequences (20.8 against 20.5 us) and ahead with 24 (55.5 against
-// 61.8); 1216 positions, 32 heads, 8 sequences, behind (37 against 31).  The line lies at three tiles a wavefront, before the two
-// meet.  33 to 64 rows, whose keys two workgroups fetch: 30 against 36 us in 256 workgroups, 110 against 61 in 1024 (1216 positions),
-// so one round of workgroups.
+// Long prefixes and many workgroups are throughput, where the tiles that attention_kernel shares in LDS win.  The lines must not
+// depend on the number of sequences, or a sequence's bits would (beyond the 128 rows where the contractions change too).
+// Up to 32 rows: three tiles a wavefront.  32 heads of 128, 1 to 128 sequences: 10.7 against 15.7 us (1 sequence, 128 positions), 23.9
+// against 25.2 (1, 768), 434 against 447 (128, 768), 42 against 38 (8, 1152).  28 heads on 4 KV heads: 21 against 24 (1, 768), but 4 to
+// 11 % behind at 64 sequences and more against 256, 576 or 768 positions, where a wavefront has one tile more than the others.
+// 33 to 64 rows, whose keys two workgroups fetch: while the call has at most 128 rows and such a call is one round of workgroups
+// (d_head 128, 64 rows: 22.6 against 33.6 us at 768 positions; 16 sequences 92 against 60), and for heads of 64 up to 7 tiles (8 heads: 9.5
+// against 17.7 us with 1 sequence, 23.8 against 26.9 with 64, 49 against 45 with 128).
 bool attention_block_fits(const bf16_t *qkv, int ld_qkv, int S, int N, int n_heads, int d_head, const bf16_t *out, const KvPrefix &pre,
                           const float *cos_t, const float *sin_t) {
-    if (N <= 32 ? pre.len > 3 * KSP * BKV : (int64_t)((N + 31) / 32) * n_heads * S > 256) return false;
-    return N >= 1 && N <= 64 && (d_head == 64 || d_head == 128) && ld_qkv % 8 == 0 && aligned16(qkv) && aligned16(out) && aligned16(cos_t) &&
+    if (N < 1 || N > 64) return false;
+    const bool one_round = (int64_t)S * N <= 128 && 2 * n_heads * (128 / N) <= 256;
+    if (N <= 32 ? pre.len > 3 * KSP * BKV : !one_round && (d_head != 64 || pre.len > 7 * BKV)) return false;
+    return (d_head == 64 || d_head == 128) && ld_qkv % 8 == 0 && aligned16(qkv) && aligned16(out) && aligned16(cos_t) &&
            aligned16(sin_t) &&
            (pre.len == 0 || (aligned16(pre.k) && aligned16(pre.vt) && pre.ld_k % 8 == 0 && pre.ld_vt % 64 == 0 && pre.ld_vt >= pre.len &&
                              pre.stride_k % 8 == 0 && pre.stride_vt % 8 == 0));

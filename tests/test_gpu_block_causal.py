@@ -247,6 +247,26 @@ def test_bf16_batched_cached_decode_equals_sequences_alone_and_the_masked_decode
         assert st[0].invocations == st_all[b].invocations and st[0].tokens == st_all[b].tokens == G
 
 
+@pytest.mark.parametrize("name", list(BF16))
+@pytest.mark.parametrize("L,blocks,batches", [(16, 3, (1, 2, 3, 8)), (32, 2, (1, 2, 4)), (48, 1, (1, 2)), (64, 2, (1, 2)), (32, 9, (1, 4)),
+                                              (32, 2, (5, 40)), (48, 2, (3, 40)), (64, 2, (3, 33)), (64, 8, (3, 33))])
+def test_bf16_cached_call_does_not_depend_on_the_batch(name, L, blocks, batches):
+    """Calls of at most 128 rows among themselves, and calls of more rows among themselves: a sequence's logits have the same bits
+    however many sequences share the call (the K parts of the contractions and the attention kernel are no matter of S)."""
+    import paper_2605_15609_amd as psd
+    shape = BF16[name]
+    P, N, B = blocks * L, (blocks + 1) * L, max(batches)
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    tokens = _dev(np.stack([_state(shape, N, P, L, 0, 90 + b, b % L)[0] for b in range(B)]))
+    cache = psd.KvCache(model, B, N)
+    psd.psd_kv_prefill(model, tokens, P, L, cache)
+    out = {S: psd.psd_forward_confidence_cached(model, tokens[:S].contiguous(), P, L, cache, want_logits=True)[2] for S in batches}
+    few = min(batches)
+    assert torch.isfinite(out[few]).all()
+    for S in batches:
+        assert torch.equal(out[S][: few * L], out[few]), f"{S} sequences: other bits than with {few}"
+
+
 def test_bf16_cached_call_at_128_and_256_rows_agrees_to_rounding():
     """Block-row calls over at most 128 rows cut the residual contractions along K (a weight stream needs the workgroups),
     larger ones do not: a sequence's fp32 sums, hence its logits, depend on whether 4 or 8 sequences share the call --
