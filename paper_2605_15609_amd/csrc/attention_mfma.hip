@@ -275,12 +275,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
         auto pv = [&](auto masked) {
 #pragma unroll
             for (int kg = 0; kg < 4; ++kg) {
+                // CAUSAL: blocks end at multiples of 16, so a group of 16 keys is visible to a query as a whole or hidden as a whole.
+                // A query leaves out what is hidden from it: a later block's values may be NaN or infinite.
+                if (CAUSAL && decltype(masked)::value && k0 + kg * 16 >= lim_hi) break;
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) {
                     const int r = ct * 32 + lrow;
                     const int c = kg * 2 + lhalf;
                     bf16x8 vf = *reinterpret_cast<const bf16x8 *>(sv + r * VROW + ((c ^ ((r >> 1) & 7)) << 4));
-                    if constexpr (decltype(masked)::value) {
+                    if constexpr (decltype(masked)::value && !CAUSAL) {
                         // slot order inside a group of 16 keys: this lane's elements 0-3 are keys 4*half + 0..3, elements
                         // 4-7 keys 8 + 4*half + 0..3
                         const int n_lo = limit - (k0 + kg * 16 + 4 * lhalf), n_hi = n_lo - 8;
@@ -291,11 +294,17 @@ __global__ __launch_bounds__(NW * 64, 2) void attention_kernel(const bf16_t *__r
                         w.w &= n_hi >= 4 ? 0xffffffffu : n_hi == 3 ? 0x0000ffffu : 0u;
                         vf = as_bf16x8(w);
                     }
-                    acc_o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kg], acc_o[ct], 0, 0, 0);
+                    const floatx16 sums = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[kg], acc_o[ct], 0, 0, 0);
+                    if constexpr (decltype(masked)::value && CAUSAL) {
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc_o[ct][v] = k0 + kg * 16 < lim_q ? sums[v] : acc_o[ct][v];
+                    } else {
+                        acc_o[ct] = sums;
+                    }
                 }
             }
         };
-        if (k0 + BKV > limit) pv(std::true_type());
+        if (k0 + BKV > (CAUSAL ? lim_lo : limit)) pv(std::true_type());
         else pv(std::false_type());
         PSD_ATT_SYNC()
         stage = (stage + 1 == NSTG) ? 0 : stage + 1;

@@ -160,7 +160,8 @@ __global__ __launch_bounds__(64) void plain_attention_kernel(const T *__restrict
     const int64_t cache = pre.len ? (pre.seq_rows ? pre.seq_rows[s] : s) / pre.seqs_per_cache : 0;
     const T *kc = (const T *)pre.k + cache * pre.stride_k + kvh * d_head;
     const T *vc = (const T *)pre.vt + cache * pre.stride_vt + (int64_t)kvh * d_head * pre.ld_vt;
-    const int n_keys = pre.len + N;
+    const int n_own = block_len > 0 ? min(N, (i / block_len + 1) * block_len) : N;   // (hidden rows are left out: their values may be NaN)
+    const int n_keys = pre.len + n_own;
     for (int c = lane; c < d_head; c += 64) qs[c] = to_float(q[c]);
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)d_head);
@@ -171,7 +172,6 @@ __global__ __launch_bounds__(64) void plain_attention_kernel(const T *__restrict
         float dot = 0.f;
         for (int c = 0; c < d_head; ++c) dot = fmaf(qs[c], to_float(k[c]), dot);
         dot *= scale;
-        if (own >= 0 && block_len > 0 && own / block_len > i / block_len) dot = -INFINITY;
         sc[jj] = dot;
         mx = fmaxf(mx, dot);
     }
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(64) void plain_attention_kernel(const T *__restrict
     for (int c = lane; c < d_head; c += 64) {
         float acc = 0.f;
         for (int jj = 0; jj < pre.len; ++jj) acc = fmaf(sc[jj], to_float(vc[(int64_t)c * pre.ld_vt + vt_key_slot(jj)]), acc);
-        for (int jj = 0; jj < N; ++jj) {
+        for (int jj = 0; jj < n_own; ++jj) {
             const T *v = base + (int64_t)jj * row_w + (n_heads + n_kv_heads + kvh) * d_head;
             acc = fmaf(sc[pre.len + jj], to_float(v[c]), acc);
         }

@@ -366,6 +366,36 @@ def test_block_rows_rotate_and_attend_in_one_launch(name, L, blocks, B):
            f"{name} L={L} blocks={blocks} seq {b} of {B}")
 
 
+@pytest.mark.parametrize("name", ["fp32"] + list(BF16))
+@pytest.mark.parametrize("L,blocks,bad", [(16, 5, 1), (16, 4, 3), (32, 5, 3), (48, 4, 1), (48, 4, 2), (64, 3, 1)])
+def test_later_blocks_of_a_prompt_never_reach_earlier_ones(name, L, blocks, bad):
+    """A token whose embedding is NaN sits in block `bad` of a prompt that goes into the cache in one pass.  The keys and values of
+    the blocks before it, in every layer, are those of the same prompt without it, bit for bit: hidden keys have probability
+    zero, and their values must not be multiplied with it."""
+    import paper_2605_15609_amd as psd
+    shape = dataclasses.replace(FP32 if name == "fp32" else BF16[name], n_layers=3)
+    P = blocks * L
+    model = psd.Model.from_host(inp.draw_model(shape, P), DEV)
+    nan_id = 17
+    model._tensors["tok_emb"][nan_id] = float("nan")
+    t = inp.draw_prompt(shape.vocab, P, 5)
+    t[t == nan_id] = 18
+    w, ld_vt = shape.n_kv_heads * shape.d_head, (P + 63) // 64 * 64
+    kept = []
+    for poison in (False, True):
+        tokens = t.copy()
+        if poison:
+            tokens[bad * L + L // 2] = nan_id
+        cache = psd.KvCache(model, 1, P)
+        psd.psd_kv_prefill(model, _dev(tokens[None]), P, L, cache)
+        mem = cache.mem.view(torch.int32 if name == "fp32" else torch.int16)[: shape.n_layers * w * (P + ld_vt)].view(shape.n_layers, -1)
+        keys, values = mem[:, : P * w].reshape(shape.n_layers, P, w), mem[:, P * w:].reshape(shape.n_layers, w, ld_vt)
+        kept.append((keys[:, : bad * L].cpu(), values[:, :, : bad * L].cpu()))
+        floats = keys.contiguous().view(torch.float32 if name == "fp32" else torch.bfloat16)
+        assert bool(torch.isfinite(floats[:, bad * L:].float()).all()) != poison
+    assert torch.equal(kept[0][0], kept[1][0]) and torch.equal(kept[0][1], kept[1][1])
+
+
 def test_empty_prefix_full_cache_and_argument_errors():
     import paper_2605_15609_amd as psd
     shape = FP32
