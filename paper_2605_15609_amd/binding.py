@@ -565,7 +565,7 @@ class KvCache:
 def psd_kv_prefill(model: Model, tokens: torch.Tensor, n_prompt: int, L: int, cache: KvCache) -> None:
     B, N = tokens.shape
     # workspace for the whole prompt in one pass, or for 16384 rows at a time
-    rows = max(L, min(n_prompt, 16384 // (B * L) * L)) if L > 0 else L
+    rows = max(L, min(n_prompt, 16384 // (B * L) * L)) if B > 0 and L > 0 else L      # (refused by the library)
     ws, nb = model.forward_ws(B, rows, L)
     _check(model.lib.psd_kv_prefill(model.handle, _ptr(tokens), B, N, n_prompt, L, _ptr(cache.mem), cache.capacity, _ptr(ws), nb,
                                     _stream()))

@@ -110,3 +110,21 @@ def test_the_binding_rejects_tensors_the_library_would_misread(lib):
     layers[0]["wo"] = layers[0]["wo"].float()        # a matrix in the wrong dtype
     with pytest.raises(B.PsdError, match="layer 0 wo"):
         B.Model(shape, 64, t, layers, device="cpu")
+
+
+def _no_gpu_model(psd, lib, d_model, d_ffn):
+    """A Model without a handle or device: what the binding computes before the library call."""
+    from paper_2605_15609_amd import binding as B
+    m = object.__new__(psd.Model)
+    m.lib, m.handle = lib, None
+    m.cfg = B._Config(2, d_model, 8, 8, 64, d_ffn, 5000, 4999, 1e-5, 0, 1, 1.0, 4096, 1)
+    return m
+
+
+def test_prefill_of_an_empty_batch_is_refused_by_the_library(lib):
+    import torch
+    import paper_2605_15609_amd as psd
+    m = _no_gpu_model(psd, lib, 512, 1408)
+    for shape, n_prompt, L in (((0, 64), 32, 16), ((1, 64), 32, 0), ((1, 64), 32, -16)):
+        with pytest.raises(psd.PsdError):
+            psd.psd_kv_prefill(m, torch.zeros(shape, dtype=torch.int32), n_prompt, L, None)
