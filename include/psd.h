@@ -321,8 +321,9 @@ int64_t psd_decode_scratch_bytes(int32_t B, int32_t N, int32_t L, int32_t K);
  * sequence starts.  Its length is not stored: a call's block_start says how many positions it holds,
  * and psd_kv_prefill / psd_decode_block_cached extend it block by block.  Block lengths must be
  * multiples of 16.  Workspace: psd_workspace_bytes(cfg, sequences, L, L) (+ the decode scratch).
- *   psd_kv_prefill: forwards positions [0, n_prompt) of tokens [B, N] and fills the caches, as many blocks at a time as
- *     the workspace holds: psd_workspace_bytes(cfg, B, L, L) at least, psd_workspace_bytes(cfg, B, n_prompt, L) for one pass.
+ *   psd_kv_prefill: forwards positions [0, n_prompt) of tokens [B, N] and fills the caches, in as few passes over whole blocks as
+ *     the workspace allows, cut evenly: psd_workspace_bytes(cfg, B, L, L) at least, psd_workspace_bytes(cfg, B, n_prompt, L) for
+ *     one pass.
  *   psd_forward_confidence_cached: tokens device int32 [S, N], only positions block_start .. +L are
  *     read; sequence s uses cache s / seqs_per_cache; writes top1/conf [S, L] (both or neither) and,
  *     if logits != NULL, the raw block logits [S*L, vocab] (debug).

@@ -888,8 +888,14 @@ int32_t psd_kv_prefill(psd_handle *h, const int32_t *tokens, int32_t B, int32_t 
     a.append = true;
     // as many blocks per pass as the workspace holds: a pass over one block of few rows is a stream of all weights, over
     // several hundred rows it is not much longer (8B shape, 512 positions: 77.9 ms block by block, 9.2 ms in one pass)
-    int at_once = n_prompt / L;
-    while (at_once > 1 && plan_forward(h->cfg, B, (int64_t)at_once * L, L).total > ws_bytes) at_once = (at_once + 1) / 2;
+    int at_once = 1, most = n_prompt / L;   // the largest count of blocks that fits (or one: the pass itself refuses less)
+    while (at_once < most) {
+        const int mid = at_once + (most - at_once + 1) / 2;
+        if (plan_forward(h->cfg, B, (int64_t)mid * L, L).total <= ws_bytes) at_once = mid;
+        else most = mid - 1;
+    }
+    const int passes = (n_prompt / L + at_once - 1) / at_once;
+    if (passes > 0) at_once = (n_prompt / L + passes - 1) / passes;   // even passes
     for (int start = 0; start < n_prompt; start += at_once * L) {
         a.len = start;
         const int rows = std::min(at_once * L, n_prompt - start);

@@ -128,3 +128,33 @@ def test_prefill_of_an_empty_batch_is_refused_by_the_library(lib):
     for shape, n_prompt, L in (((0, 64), 32, 16), ((1, 64), 32, 0), ((1, 64), 32, -16)):
         with pytest.raises(psd.PsdError):
             psd.psd_kv_prefill(m, torch.zeros(shape, dtype=torch.int32), n_prompt, L, None)
+
+
+def test_prefill_workspace_is_bounded_and_falls_back_to_one_block(lib, monkeypatch):
+    import types
+    import torch
+    import paper_2605_15609_amd as psd
+    from paper_2605_15609_amd import binding as B
+    for d, f in ((512, 1408), (4096, 12288)):
+        m = _no_gpu_model(psd, lib, d, f)
+        for batch, n_prompt, L in ((1, 0, 16), (1, 16, 16), (1, 4080, 48), (3, 1024, 32), (16, 4096, 64), (500, 64, 64)):
+            rows = B._prefill_rows(m, batch, n_prompt, L)
+            assert rows % L == 0 and L <= rows <= max(L, n_prompt)
+            need = lib.psd_workspace_bytes(ctypes.byref(m.cfg), batch, rows, L)
+            assert need > 0 and (rows == L or (need <= B.PREFILL_WORKSPACE and batch * rows <= B.PREFILL_ROWS))
+    # an allocation that fails: one block at a time, as small as the call ever was
+    seen, passed = [], []
+
+    def workspace(n_bytes):
+        seen.append(n_bytes)
+        if len(seen) == 1:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return torch.empty(1, dtype=torch.uint8)
+
+    m = _no_gpu_model(psd, lib, 512, 1408)
+    m.workspace = workspace
+    m.lib = types.SimpleNamespace(psd_workspace_bytes=lib.psd_workspace_bytes, psd_kv_prefill=lambda *a: passed.append(a[-2]) or 0)
+    monkeypatch.setattr(B, "_stream", lambda: None)
+    cache = types.SimpleNamespace(mem=torch.empty(1, dtype=torch.uint8), capacity=64)
+    psd.psd_kv_prefill(m, torch.zeros((1, 64), dtype=torch.int32), 64, 16, cache)
+    assert seen[1] < seen[0] and passed == [seen[1]] == [lib.psd_workspace_bytes(ctypes.byref(m.cfg), 1, 16, 16)]
