@@ -366,6 +366,44 @@ def test_block_rows_rotate_and_attend_in_one_launch(name, L, blocks, B):
            f"{name} L={L} blocks={blocks} seq {b} of {B}")
 
 
+@pytest.mark.parametrize("name", list(BF16))
+@pytest.mark.parametrize("L,blocks", [(16, 30), (48, 10)])
+def test_prompts_of_a_batch_on_the_wide_workgroups(name, L, blocks):
+    """So many queries that the context-causal kernel takes 128 per workgroup: four wavefronts that see different numbers of key tiles
+    and share the fetch of each.  The prompt goes in in two passes of 240 rows, so the last query tile is partial and the second
+    pass starts behind cached positions.  Every sequence's cache has the bits of that sequence alone (64 queries per
+    workgroup, one pass), and the block behind the prompt gives the oracle's logits."""
+    import ctypes as C
+
+    import paper_2605_15609_amd as psd
+    shape = BF16[name]
+    P, N, B = L * blocks, L * (blocks + 1), 512 // (2 * shape.n_heads)
+    rows = P // 2
+    assert (rows + 127) // 128 * shape.n_heads * B >= 512 > (P + 127) // 128 * shape.n_heads and rows % 128 != 0
+    host = inp.draw_model(shape, N)
+    model = psd.Model.from_host(host, DEV)
+    states = [_state(shape, N, P, L, 0, 200 + b, b % L) for b in range(B)]
+    d = _dev(np.stack([t for t, _ in states]))
+    per_seq = model.lib.psd_kv_cache_bytes(C.byref(model.cfg), N)
+
+    def prefill(tokens, rows):
+        cache = psd.KvCache(model, tokens.shape[0], N)
+        need = model.lib.psd_workspace_bytes(C.byref(model.cfg), tokens.shape[0], rows, L)
+        ws = model.workspace(need)
+        assert model.lib.psd_kv_prefill(model.handle, C.c_void_p(tokens.data_ptr()), tokens.shape[0], N, P, L, C.c_void_p(cache.mem.data_ptr()),
+                                        N, C.c_void_p(ws.data_ptr()), need, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        return cache
+
+    cache = prefill(d, rows)
+    for b in (0, 1, B // 2, B - 1):
+        alone = prefill(d[b: b + 1].contiguous(), P)
+        assert torch.equal(alone.mem[:per_seq], cache.mem[b * per_seq: (b + 1) * per_seq]), f"sequence {b}: other keys or values than alone"
+    top1, conf, logits = psd.psd_forward_confidence_cached(model, d, P, L, cache, want_logits=True)
+    logits = logits.cpu().numpy().reshape(B, L, -1)
+    for b in (0, B - 1):
+        _check(shape, host, logits[b], top1[b].cpu().numpy(), conf[b].cpu().numpy(), states[b][0], P, L, 2e-2, f"{name} L={L} seq {b} of {B}")
+
+
 @pytest.mark.parametrize("name", ["fp32"] + list(BF16))
 @pytest.mark.parametrize("L,blocks,bad", [(16, 5, 1), (16, 4, 3), (32, 5, 3), (48, 4, 1), (48, 4, 2), (64, 3, 1)])
 def test_later_blocks_of_a_prompt_never_reach_earlier_ones(name, L, blocks, bad):
