@@ -92,6 +92,7 @@ class Probes:
         for ms, rows, _ in swiglu:
             by_rows.setdefault(rows, []).append(ms)
         tile_name = self.lib.psd_kernel_gemm_tile_name(self.tile).decode()
+        kernel = "gemm_stream_kernel" if self.tile == self.lib.psd_kernel_gemm_tile_count() else "mfma::gemm_bf16_kernel"
         shapes = {}
         for rows, times in sorted(by_rows.items()):
             flops = 4.0 * rows * shape.d_model * shape.d_ffn
@@ -107,7 +108,7 @@ class Probes:
             by = 2.0 * shape.d_ffn * shape.d_model * 2 + rows * (shape.d_model + shape.d_ffn) * 2.0
             roof = {"bound": "mfma", "achieved": flops / (avg * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": flops / (avg * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
-                    "kernel": f"mfma::gemm_bf16_kernel, SwiGLU gate/up contraction, tile {tile_name}",
+                    "kernel": f"{kernel}, SwiGLU gate/up contraction, tile {tile_name}",
                     "launch_rows": rows, "launches": len(times), "avg_launch_us": avg * 1e3, "flops_per_launch": flops,
                     "algorithmic_bytes_per_launch": by, "all_launch_shapes": shapes,
                     "measured": "HIP events around every launch in an untimed pass of the same steps"}

@@ -230,6 +230,11 @@ int32_t psd_debug_layer(psd_handle *h, int32_t layer, float *hidden, int32_t S, 
  * and psd_kernel_gemm_tile_name for the numbering; -1 = pick per shape; a tile that cannot run the
  * epilogue asked for is ignored).  Process-wide. */
 int32_t psd_debug_force_gemm_tile(int32_t tile);
+/* Debug: what the dispatcher does with a contraction of this shape on aligned operands.  psd_debug_gemm_plan returns the kernel as
+ * psd_probe_begin numbers it, and in *parts (may be NULL) the parts along K that a cached call cuts a residual contraction into;
+ * psd_debug_qkv_cut the first column that the QKV projection of whole sequences leaves to a second launch (0: one launch). */
+int32_t psd_debug_gemm_plan(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int32_t *parts);
+int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq);
 /* Optional: the block loops (psd_decode, psd_decode_block) replay the whole-sequence model calls of a shape they have
  * seen twice as HIP graphs.  Results are bit-identical to eager launches.  Off by default: on the one workload where
  * a model call is ~75 kernels of 4-11 microseconds (8 layers, d_model 512) the queue already runs them back to back and
@@ -455,7 +460,7 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
  * launch of the layer-contraction kernel with the given epilogue (0 store, 1 bias,
  * 2 residual, 3 SwiGLU) and workgroup tile configuration (an index below
  * psd_kernel_gemm_tile_count; psd_kernel_gemm_tile_name describes it: tile extent, wavefronts,
- * depths of the two LDS rings) is bracketed by HIP events on the stream it is launched on (up to
+ * depths of the two LDS rings; psd_kernel_gemm_tile_count itself: the kernel that streams the weights past up to 128 rows) is bracketed by HIP events on the stream it is launched on (up to
  * max_launches; later ones go untimed).  Kind 4 selects the LM-head confidence pass instead
  * (all its kernels, tile ignored), kind 5 every model call (forward + confidence pass) made by
  * psd_decode_block / psd_decode; both can be timed together with one contraction kernel.
@@ -465,7 +470,8 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
  * psd_probe_read (after psd_probe_end) copies the first max_n timed launches one by one: ms[i] their duration and
  * (a[i], b[i]) = (rows, output columns) of a contraction, (rows, 0) of an LM-head pass, (sequences, drafts per
  * sequence: 1 for a stage-1 call, K for a verification call) of a model call; returns how many it wrote.
- * psd_kernel_gemm_tile tells which tile the dispatcher picks for a shape. */
+ * psd_kernel_gemm_tile tells which of them the dispatcher picks for a shape (up to 128 rows of a contraction other than SwiGLU:
+ * at a K of 4096). */
 int32_t psd_probe_begin(psd_handle *h, int32_t epilogue, int32_t tile, int32_t max_launches);
 int32_t psd_probe_end(psd_handle *h, int32_t epilogue, double *total_ms, int64_t *launches, double *work);
 int32_t psd_probe_read(psd_handle *h, int32_t epilogue, int32_t max_n, float *ms, int64_t *a, int64_t *b);

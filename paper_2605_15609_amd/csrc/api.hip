@@ -259,7 +259,7 @@ psd_handle::Probe &probe_of(psd_handle *h, int32_t kind) { return kind == 4 ? h-
 
 int32_t psd_probe_begin(psd_handle *h, int32_t epilogue, int32_t tile, int32_t max_launches) {
     if (!h) PSD_FAIL(PSD_ERR_INVALID_ARG, "handle is NULL");
-    if (epilogue < 0 || epilogue > 5 || tile < 0 || tile >= gemm_bf16_tile_count() || max_launches < 1 || max_launches > (1 << 20))
+    if (epilogue < 0 || epilogue > 5 || tile < 0 || tile > gemm_bf16_tile_count() || max_launches < 1 || max_launches > (1 << 20))
         PSD_FAIL(PSD_ERR_INVALID_ARG, "bad probe arguments");
     psd_handle::Probe &pr = probe_of(h, epilogue);
     while (pr.ev.size() < (size_t)max_launches * 2) {
@@ -1152,7 +1152,20 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
 
 int32_t psd_kernel_gemm_tile(int64_t M, int32_t Nout, int32_t epilogue) {
     if (M < 1 || Nout < 1 || epilogue < 0 || epilogue > 3) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    if (M <= 128) return gemm_bf16_kernel(M, Nout, 4096, epilogue, nullptr, nullptr, nullptr, Nout);
     return gemm_bf16_tile(M, Nout, epilogue);
+}
+
+int32_t psd_debug_gemm_plan(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int32_t *parts) {
+    if (M < 1 || Nout < 1 || Kin < 1 || epilogue < 0 || epilogue > 3) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    if (parts) *parts = epilogue == EPI_RESIDUAL ? gemm_bf16_splits(M, Nout, Kin) : 1;
+    return gemm_bf16_kernel(M, Nout, Kin, epilogue, nullptr, nullptr, nullptr, Nout);
+}
+
+int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq) {
+    if (M < 1 || Nout < 1 || Kin < 1 || rows_per_seq < 1) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    const int tile = gemm_bf16_qkv_tile(M, Nout, d_head, v_start, rows_per_seq);
+    return tile < 0 ? 0 : gemm_bf16_qkv_cut(M, Nout, Kin, tile);
 }
 
 int32_t psd_kernel_gemm_tile_count(void) { return gemm_bf16_tile_count(); }

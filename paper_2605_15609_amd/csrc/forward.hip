@@ -96,8 +96,8 @@ struct Dispatch<bf16_t> {
             pend.stride = M * Nout;
         } else {
             psd_handle::Probe &pr = h->probe;
-            const bool timed = pr.enabled && epi == pr.epi && gemm_bf16_tile(M, Nout, epi, Kin) == pr.tile &&
-                               pr.used + 2 <= pr.ev.size();
+            const bool timed = pr.enabled && epi == pr.epi && pr.used + 2 <= pr.ev.size() &&
+                               gemm_bf16_kernel(M, Nout, Kin, epi, bias, out, resid, ldo) == pr.tile;
             if (timed) (void)hipEventRecord(pr.ev[pr.used], st);
             launch_gemm_bf16(A, (const bf16_t *)W, (const bf16_t *)W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, st);
             if (timed) {

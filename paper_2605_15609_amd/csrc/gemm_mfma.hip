@@ -98,7 +98,9 @@ void gemm_bf16_force_tile(int tile) {
 }
 int gemm_tile_group_m() { return g_group_m; }
 int gemm_bf16_tile_count() { return kNumTiles; }
-const char *gemm_bf16_tile_name(int tile) { return tile >= 0 && tile < kNumTiles ? kTiles[tile].name : "?"; }
+const char *gemm_bf16_tile_name(int tile) {
+    return tile >= 0 && tile < kNumTiles ? kTiles[tile].name : tile == kNumTiles ? "all of up to 128 rows, streams the weights" : "?";
+}
 
 int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
     if (g_force_tile >= 0 && g_force_tile < kNumTiles && tile_fits(g_force_tile, epi)) return g_force_tile;
@@ -192,6 +194,20 @@ int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_pe
     return tile;
 }
 
+// A partial last round of 256x256 tiles costs almost a whole one.  Where the column tiles of the whole rounds come out even
+// enough, the columns behind them run as a launch of their own in smaller tiles, one round of which is shorter (2048 x 12288
+// outputs, K = 4096: 384 tiles in 179 us; 256 of them in 99, the other 4096 columns in 57 on 256x128 tiles).  Costs as in
+// gemm_bf16_tile; the second launch takes some 3 us, 2000 units at that K.  Returns the second launch's first column, 0: one launch.
+int gemm_bf16_qkv_cut(int64_t M, int Nout, int Kin, int tile) {
+    if (tile != 1 || g_force_tile >= 0) return 0;
+    const int64_t tm = (M + 255) / 256, n = tm * ((Nout + 255) / 256), whole = n / 256 * 256 / tm;
+    const int c0 = (int)whole * 256;
+    if (n % 256 == 0 || n >= 8 * 256 || whole == 0 || c0 >= Nout) return 0;
+    auto cost = [&](int64_t tiles, double area, double rate) { return (double)((tiles + 255) / 256) * area / rate; };
+    const double rest = cost(tm * ((Nout - c0 + 127) / 128), 32768, 1.06);
+    return cost(whole * tm, 65536, 1.25) + rest + 2000.0 * 4096 / Kin < cost(n, 65536, 1.25) ? c0 : 0;
+}
+
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
                           const KvDest &kv, int tile, hipStream_t st) {
@@ -227,32 +243,29 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
             default: return launch_cfg<128, 128, 2, 2, EPI_QKV, 2, 3, S4, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
         }
     };
-    // A partial last round of 256x256 tiles costs almost a whole one.  Where the column tiles of the whole rounds come out even
-    // enough, the columns behind them run as a launch of their own in smaller tiles, one round of which is shorter (2048 x 12288
-    // outputs, K = 4096: 384 tiles in 179 us; 256 of them in 99, the other 4096 columns in 57 on 256x128 tiles).  Costs as in
-    // gemm_bf16_tile; the second launch takes some 3 us, 2000 units at that K.
-    if (tile == 1 && g_force_tile < 0) {
-        const int64_t tm = (M + 255) / 256, n = tm * ((Nout + 255) / 256), whole = n / 256 * 256 / tm;
-        const int c0 = (int)whole * 256;
-        if (n % 256 != 0 && n < 8 * 256 && whole > 0 && c0 < Nout) {
-            auto cost = [&](int64_t tiles, double area, double rate) { return (double)((tiles + 255) / 256) * area / rate; };
-            const double rest = cost(tm * ((Nout - c0 + 127) / 128), 32768, 1.06);
-            if (cost(whole * tm, 65536, 1.25) + rest + 2000.0 * 4096 / Kin < cost(n, 65536, 1.25)) {
-                part(1, 0, c0);
-                return part(7, c0, Nout - c0);
-            }
-        }
-    }
-    part(tile, 0, Nout);
+    const int c0 = gemm_bf16_qkv_cut(M, Nout, Kin, tile);
+    if (c0 == 0) return part(tile, 0, Nout);
+    part(1, 0, c0);
+    part(7, c0, Nout - c0);
+}
+
+// the streaming kernel's plan for a contraction that it takes, tiles = 0 otherwise (16-byte accesses to out, resid and bias)
+static StreamPlan stream_choice(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo) {
+    if (M > 128 || g_force_tile >= 0 || ldo % 4 || !aligned16(epi == EPI_RESIDUAL ? (const void *)resid : (const void *)out) ||
+        (epi == EPI_BIAS && !aligned16(bias)))
+        return StreamPlan();
+    return stream_plan(M, Nout, Kin, epi, 1, 1);
+}
+
+int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo) {
+    return stream_choice(M, Nout, Kin, epi, bias, out, resid, ldo).tiles ? kNumTiles : gemm_bf16_tile(M, Nout, epi, Kin);
 }
 
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,
                       const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st) {
     const int m = (int)M;
-    if (M <= 128 && g_force_tile < 0 && ldo % 4 == 0 && (aligned16(epi == EPI_RESIDUAL ? (void *)resid : (void *)out)) && (epi != EPI_BIAS || aligned16(bias))) {
-        const StreamPlan plan = stream_plan(M, Nout, Kin, epi, 1, 1);
-        if (plan.tiles) return launch_gemm_stream(plan, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, nullptr, st);
-    }
+    const StreamPlan plan = stream_choice(M, Nout, Kin, epi, bias, out, resid, ldo);
+    if (plan.tiles) return launch_gemm_stream(plan, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, nullptr, st);
     switch (epi) {
         case EPI_STORE: dispatch<EPI_STORE>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
         case EPI_BIAS: dispatch<EPI_BIAS>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;

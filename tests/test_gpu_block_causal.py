@@ -267,6 +267,28 @@ def test_bf16_cached_call_does_not_depend_on_the_batch(name, L, blocks, batches)
         assert torch.equal(out[S][: few * L], out[few]), f"{S} sequences: other bits than with {few}"
 
 
+@pytest.mark.parametrize("S", [1, 5])
+def test_probes_file_a_launch_under_the_kernel_that_ran(S):
+    """The SwiGLU contractions of a cached call over 32 rows stream the weights, those over 160 rows run on a tile: each is timed
+    under its own number and under no other."""
+    import paper_2605_15609_amd as psd
+    shape = BF16["mha-dh64"]
+    L, P, N = 32, 32, 64
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    d = _dev(np.stack([_state(shape, N, P, L, 0, 90 + s, 3)[0] for s in range(S)]))
+    cache = psd.KvCache(model, S, N)
+    psd.psd_kv_prefill(model, d, P, L, cache)
+    count = model.lib.psd_kernel_gemm_tile_count()
+    ran = {}
+    for kernel in range(count + 1):
+        model.probe_begin(3, kernel, 64)
+        psd.psd_forward_confidence_cached(model, d, P, L, cache)
+        ran[kernel] = model.probe_end(3)[1]
+    expect = model.lib.psd_kernel_gemm_tile(S * L, shape.d_ffn, 3)
+    assert (expect == count) == (S * L <= 128) and model.lib.psd_kernel_gemm_tile_name(expect) != b"?"
+    assert ran == {k: shape.n_layers if k == expect else 0 for k in ran}
+
+
 def test_bf16_cached_call_at_128_and_256_rows_agrees_to_rounding():
     """Block-row calls over at most 128 rows cut the residual contractions along K (a weight stream needs the workgroups),
     larger ones do not: a sequence's fp32 sums, hence its logits, depend on whether 4 or 8 sequences share the call --
