@@ -265,6 +265,8 @@ def test_qkv_projection_in_two_launches_changes_no_bit(heads, kv_heads):
                          seed=23)
     assert shape.d_head == 128 and 256 < S * N // 256 * ((heads + 2 * kv_heads) * 128 // 256) < 512
     host, model = make_models(shape, N)
+    cut = model.lib.psd_debug_qkv_cut(S * N, (heads + 2 * kv_heads) * 128, 512, 128, (heads + kv_heads) * 128, N)
+    assert cut == 8192 and (cut == (heads + kv_heads) * 128 if heads == 32 else heads * 128 < cut < (heads + kv_heads) * 128)
     d = to_dev(np.stack([_state(shape, N, N - 2 * L, L, 80 + s, 5 * s) for s in range(S)]))
     out = {}
     for mask in (0, 8):

@@ -163,8 +163,10 @@ def test_gemm_few_rows(epi):
     class below, slices of every width the plan gives (from a few to thousands of outputs, ragged last ones), K of one stage (the
     ring is longer than K), of an odd number of stages, and long enough that the ring wraps several times."""
     from paper_2605_15609_amd import binding as B
-    for M, N, K in [(1, 64, 64), (31, 832, 64), (32, 4160, 192), (33, 9024, 320), (64, 12352, 128), (65, 832, 1152), (100, 16448, 448),
+    lib = B.load_library()
+    for M, N, K in [(1, 64, 64), (31, 832, 64), (32, 4160, 192), (33, 9024, 320), (64, 12352, 128), (65, 12352, 1152), (100, 16448, 448),
                     (127, 20544, 192), (128, 12288, 704)]:
+        assert lib.psd_debug_gemm_plan(M, N, K, epi, None) == lib.psd_kernel_gemm_tile_count(), "not on the streaming kernel"
         print(f"[kernels] few rows M={M} N={N} K={K} epi={epi}", flush=True)
         rng = np.random.default_rng(M + N + K)
         A = bf16_round_trip(rng.standard_normal((M, K), dtype=np.float32))
