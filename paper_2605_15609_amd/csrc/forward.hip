@@ -1,8 +1,8 @@
 // The model call of the PSD step (Sec. 3.1): bidirectional transformer forward over S
 // sequences of N tokens, then top-1 token and confidence on the L rows of the active block.
 // This file only sequences kernels on one stream; every operation runs in the kernels of
-// elementwise.hip, gemm_mfma.hip, attention_mfma.hip, lm_head.hip (plain_kernels.hip on the
-// debug path).
+// elementwise.hip, gemm_mfma.hip, gemm_stream.hip, attention_mfma.hip, attention_block.hip,
+// attention_ordered.hip, lm_head.hip (plain_kernels.hip for fp32 models and on the debug path).
 #include "psd_internal.h"
 
 // Row stride of the SwiGLU output [tokens, d_ffn]: 64 elements of padding.  With dense rows of 24 KB
@@ -132,12 +132,6 @@ struct Dispatch<bf16_t> {
         else launch_attention_causal_bf16(qkv, ld_qkv, S, R, H, Hkv, dh, out, cache, pos0, block_len, st);
         return true;
     }
-    // Rotary on q and k (row i of a sequence sits at position pos0 + i), then attention.
-    // pre: KV prefix that every own row sees; block_len > 0: context-causal blocks among the own rows (only the
-    // plain kernel masks; the product path of that attention mode keeps finished blocks in the prefix instead).
-    // rotated: qkv_fused produced qkv and vT, only the attention is left.
-    // Lengths that are no multiple of 8 keep fp32 probabilities and the plain kernel's order of sums; whole sequences of them run on
-    // the fp32 matrix instructions with the same bits.
     // Block rows of a cached call (nothing reads their rotated keys afterwards): rotary and attention in one launch.  false: not on
     // this path (a block of more than 64 rows, a debug switch)
     static bool block_attention(psd_handle *h, const bf16_t *qkv, int ld_qkv, int S, int N, int pos0, int H, int Hkv, int dh, bf16_t *out,
@@ -146,6 +140,12 @@ struct Dispatch<bf16_t> {
         launch_attention_block(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, pos0, h->rope_cos, h->rope_sin, st);
         return true;
     }
+    // Rotary on q and k (row i of a sequence sits at position pos0 + i), then attention.
+    // pre: KV prefix that every own row sees; block_len > 0: context-causal blocks among the own rows (only the
+    // plain kernel masks; the product path of that attention mode keeps finished blocks in the prefix instead).
+    // rotated: qkv_fused produced qkv and vT, only the attention is left.
+    // Lengths that are no multiple of 8 keep fp32 probabilities and the plain kernel's order of sums; whole sequences of them run on
+    // the fp32 matrix instructions with the same bits.
     static void rope_attention(psd_handle *h, bf16_t *qkv, int ld_qkv, bf16_t *vT, int S, int N, int pos0, int H, int Hkv, int dh,
                                bf16_t *out, const KvPrefix &pre, int block_len, hipStream_t st, bool rotated = false) {
         if (rotated) {

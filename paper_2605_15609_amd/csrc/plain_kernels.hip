@@ -1,6 +1,8 @@
-// Debug path: plain kernels for any shape and either storage type, fp32 arithmetic, no
-// MFMA.  The fp32 model configuration runs entirely on these; for bf16 models they are the
-// on-device cross-check of the MFMA kernels (same rounding points, different algorithm).
+// Debug path: plain kernels for any shape and either storage type, fp32 arithmetic.  The fp32
+// model configuration runs entirely on these (its contractions on the fp32 matrix instructions);
+// for bf16 models they are the on-device cross-check of the MFMA kernels: a different algorithm
+// with the same rounding points, except that the probabilities of plain_attention_kernel stay in
+// fp32 where attention_mfma.hip and attention_block.hip round them to bf16.
 #include <type_traits>
 
 #include "psd_internal.h"
@@ -72,7 +74,9 @@ __global__ __launch_bounds__(256) void plain_gemm_kernel(const T *__restrict__ A
 // fp32 contraction of the fp32 models on v_mfma_f32_32x32x2_f32 (full fp32 products and sums).  Bound by latency at the sizes of
 // these models: one workgroup per 32x32 outputs, its four wavefronts deal the 8-k chunks of K among them and fetch straight into
 // registers, eight chunks in one memory round trip, without LDS or barriers until the four partial sums are added in wavefront
-// order.  (The tiled kernel above walks 16 k per two barriers and one round trip: 54 -> 5 us at 48 x 64 outputs, K = 256.)
+// order.  (The tiled kernel above walks 16 k per two barriers and one round trip: 54 -> 5 us at 48 x 64 outputs, K = 256.  It is
+// behind at every size measured, 32 to 4096 rows and widths of 64 to 4096: 512 x 4096 outputs at K = 64 23.0 -> 18.3 us, 4096 x 2048
+// at K = 2048 2035 -> 722.)
 // A lane holds row lane % 32 and the k's 4 * (lane / 32) + 0..3 of a chunk; MFMA e of a chunk contracts k = e and 4 + e.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
