@@ -28,14 +28,14 @@ sys.path.insert(0, ROOT)
 MFMA_BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16
 HBM_PEAK_GBS = 8000.0
 
-# HBM-side bytes per launch of the SwiGLU contraction (256x256 tile, 8 wavefronts, LDS rings 2/3), from two rocprofv3 --pmc
+# HBM-side bytes per launch of the SwiGLU contraction (256x256 tile, 256x192 at 512 rows), from two rocprofv3 --pmc
 # runs (FETCH_SIZE, WRITE_SIZE) scaled by what the same counters read for a plain 256 MiB copy; commands and tables in the
 # file named.  Stored figures of an earlier profile, not measured in this run: key = rows of the launch.
 SWIGLU_TRAFFIC = {
     "source": "profiles/config5_hbm_traffic_pmc.md and profiles/config3_hbm_traffic_pmc.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, "
               "copy-calibrated; FETCH_SIZE counts what the L2s request from the fabric, Infinity-Cache hits included)",
     "d_model": 4096, "d_ffn": 12288,
-    "rows": {163840: (49.35 + 4.03) * 1e9, 20480: (6.17 + 0.50) * 1e9, 2048: (589.1 + 48.0) * 2 ** 20, 512: (230.6 + 12.0) * 2 ** 20},
+    "rows": {163840: (49.36 + 4.03) * 1e9, 20480: (6.17 + 0.50) * 1e9, 2048: (589.2 + 48.0) * 2 ** 20, 512: (233.6 + 12.0) * 2 ** 20},
 }
 
 
@@ -92,7 +92,9 @@ class Probes:
         for ms, rows, _ in swiglu:
             by_rows.setdefault(rows, []).append(ms)
         tile_name = self.lib.psd_kernel_gemm_tile_name(self.tile).decode()
-        kernel = "gemm_stream_kernel" if self.tile == self.lib.psd_kernel_gemm_tile_count() else "mfma::gemm_bf16_kernel"
+        stream = self.tile == self.lib.psd_kernel_gemm_tile_count()
+        kernel = (f"gemm_stream_kernel, SwiGLU gate/up contraction, {tile_name}" if stream else
+                  f"mfma::gemm_bf16_kernel, SwiGLU gate/up contraction, tile {tile_name}")
         shapes = {}
         for rows, times in sorted(by_rows.items()):
             flops = 4.0 * rows * shape.d_model * shape.d_ffn
@@ -108,7 +110,7 @@ class Probes:
             by = 2.0 * shape.d_ffn * shape.d_model * 2 + rows * (shape.d_model + shape.d_ffn) * 2.0
             roof = {"bound": "mfma", "achieved": flops / (avg * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": flops / (avg * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
-                    "kernel": f"{kernel}, SwiGLU gate/up contraction, tile {tile_name}",
+                    "kernel": kernel,
                     "launch_rows": rows, "launches": len(times), "avg_launch_us": avg * 1e3, "flops_per_launch": flops,
                     "algorithmic_bytes_per_launch": by, "all_launch_shapes": shapes,
                     "measured": "HIP events around every launch in an untimed pass of the same steps"}

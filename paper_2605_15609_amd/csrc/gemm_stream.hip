@@ -7,8 +7,8 @@
 // narrow slice of the weight rows, as wide as spreads the slices evenly over the 256 CUs; a residual contraction is also cut along
 // K, which shortens the activations a workgroup reads (its partial sums are added by the next norm).  stream_plan weighs the two.
 // Against the 128x64 / 128x128 tiles and the eight-fold K cut before it, inside a model call of the 8B shape: 12288 x 4096 (QKV)
-// 32 -> 22 us at 32 rows, 34.6 -> 34 at 128; the SwiGLU pair of that size 49 -> 36 .. 44 and 53 -> 48; the output and down
-// projections of a layer together 52 on average over both row counts, now 31.5 and 46.5.
+// 32 -> 22 us at 32 rows, 34.6 -> 34 at 128; the SwiGLU pair of that size 49 -> 42 and 53 -> 48; the output and down
+// projections of a layer together 52 on average over both row counts, now 29 and 46.
 //
 // Four wavefronts share one ring of NS stages of 64 k in LDS, filled by direct global -> LDS loads, 128-byte rows with the 16-byte
 // chunks swizzled as in gemm_mfma.h; one barrier per stage, the fragments of the next stage in registers while one computes.  With
@@ -224,8 +224,9 @@ void launch_stream_epi(const StreamPlan &p, const bf16_t *X, const bf16_t *Y, co
 
 }   // namespace
 
-// Slice width and K parts: the shortest of the widths 16 .. 96 and (residual contractions whose reader adds partial sums) of 1, 2, 4
-// and 8 parts, by the rates in the head of this file.  max_splits = 1: no partial sums.  tiles = 0: not for this kernel.
+// Slice width and K parts: the shortest of the widths 16 .. 96 and (residual contractions whose reader adds partial sums) of
+// min_splits, twice that, .. max_splits parts, by the rates in the head of this file.  max_splits = 1: no partial sums.  tiles = 0: not
+// for this kernel.
 StreamPlan stream_plan(int64_t M, int Nout, int Kin, int epi, int min_splits, int max_splits) {
     StreamPlan best;
     if (M > 128 || M < 1 || Nout % 4) return best;
