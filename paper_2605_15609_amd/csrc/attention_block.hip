@@ -258,8 +258,9 @@ bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 // Long prefixes and many workgroups are throughput, where the tiles that attention_kernel shares in LDS win.  The lines must not
 // depend on the number of sequences, or a sequence's bits would (beyond the 128 rows where the contractions change too).
 // Up to 32 rows: three tiles a wavefront.  32 heads of 128, 1 to 128 sequences: 10.7 against 15.7 us (1 sequence, 128 positions), 23.9
-// against 25.2 (1, 768), 434 against 447 (128, 768), 42 against 38 (8, 1152).  28 heads on 4 KV heads: 21 against 24 (1, 768), but 4 to
-// 11 % behind at 64 sequences and more against 256, 576 or 768 positions, where a wavefront has one tile more than the others.
+// against 25.2 (1, 768), 434 against 447 (128, 768), behind at 37 against 31 (8, 1216).  28 heads on 4 KV heads: 21 against 24 (1, 768),
+// but 4 to 11 % behind at 64 sequences and more against 256, 576 or 768 positions, where a wavefront has one tile more than the
+// others.
 // 33 to 64 rows, whose keys two workgroups fetch: while the call has at most 128 rows and such a call is one round of workgroups
 // (d_head 128, 64 rows: 22.6 against 33.6 us at 768 positions; 16 sequences 92 against 60), and for heads of 64 up to 7 tiles (8 heads: 9.5
 // against 17.7 us with 1 sequence, 23.8 against 26.9 with 64, 49 against 45 with 128).
