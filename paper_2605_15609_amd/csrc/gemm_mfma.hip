@@ -9,80 +9,43 @@ namespace {
 
 using namespace mfma;
 
-// Main-loop schedule of the 8- and 4-wavefront tiles (bits as in gemm_bf16_kernel)
-#ifndef PSD_SCHED_8W
-#define PSD_SCHED_8W (2 | 4 | 8)
-#endif
-#ifndef PSD_SCHED_4W
-#define PSD_SCHED_4W 8
-#endif
-constexpr int S8 = PSD_SCHED_8W, S4 = PSD_SCHED_4W;
-
 struct TileCfg {
     int bm, bn;
     const char *name;
 };
 // index = value returned by gemm_bf16_tile
 constexpr TileCfg kTiles[] = {
-    // (tiles 0 and 1 run in the 32x32x16 or the 16x16x32 MFMA form, whichever was measured faster for the epilogue; 8 and 9
-    // force the 16x16x32 form)
-    {128, 128, "128x128, 4 wavefronts, LDS rings 2/3"},   // two workgroups per CU
-    {256, 256, "256x256, 8 wavefronts, LDS rings 2/3"},   // least LDS traffic per FLOP; fills the 160 KB
-    {256, 192, "256x192, 8 wavefronts, LDS rings 2/4"},
-    {128, 192, "128x192, 4 wavefronts, LDS rings 2/2"},   // two workgroups per CU
-    {128, 64, "128x64, 4 wavefronts, LDS rings 4/4"},     // lone workgroup per CU: fetches several stages ahead
-    {128, 128, "128x128, 4 wavefronts, LDS rings 4/4"},
-    {64, 64, "64x64, 4 wavefronts, LDS rings 4/4"},
-    {256, 128, "256x128, 8 wavefronts, LDS rings 3/4"},   // one full round of 256 workgroups for 2048 x 4096 outputs
-    {256, 256, "256x256, 8 wavefronts, 16x16x32 MFMAs, LDS rings 2/3"},
-    {128, 128, "128x128, 4 wavefronts, 16x16x32 MFMAs, LDS rings 2/3"},
+    {128, 128, "128x128, LDS rings 2/3"},   // two workgroups per CU
+    {256, 256, "256x256, LDS rings 2/3"},   // least LDS traffic per FLOP; fills the 160 KB
+    {256, 192, "256x192, LDS rings 2/4"},
+    {128, 192, "128x192, LDS rings 2/2"},   // two workgroups per CU
+    {128, 64, "128x64, LDS rings 4/4"},     // lone workgroup per CU: fetches several stages ahead
+    {128, 128, "128x128, LDS rings 4/4"},
+    {64, 64, "64x64, LDS rings 4/4"},
+    {256, 128, "256x128, LDS rings 3/4"},   // one full round of 256 workgroups for 2048 x 4096 outputs
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
-template <int EPI>
-void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nout, int Kin, int lda, int ldw, const float *bias,
-              bf16_t *out, float *resid, int ldo, hipStream_t st) {
-    Top1Args none = {};
-    const int tile = gemm_bf16_tile(M, Nout, EPI, Kin);
-    // SwiGLU needs an even number of 32-column subtiles per wavefront (gate and up halves); gemm_bf16_tile
-    // never returns the others for it
-    if constexpr (EPI == EPI_SWIGLU) {
-        if (tile == 2) return launch_cfg<256, 192, 4, 2, EPI, 2, 4, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-    }
-    if constexpr (EPI != EPI_SWIGLU) {
-        switch (tile) {
-            case 2: return launch_cfg<256, 192, 4, 2, EPI, 2, 4, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            case 3: return launch_cfg<128, 192, 2, 2, EPI, 2, 2, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            case 4: return launch_cfg<128, 64, 2, 2, EPI, 4, 4, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            case 6: return launch_cfg<64, 64, 2, 2, EPI, 4, 4, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            case 7:   // (the faster MFMA form of each, as for tile 1)
-                if (EPI != EPI_RESIDUAL || Kin <= 4096)
-                    return launch_cfg<256, 128, 4, 2, EPI, 3, 4, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-                return launch_cfg<256, 128, 4, 2, EPI, 3, 4, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            default: break;
-        }
-    }
+// launches `tile`; launch_cfg's arguments
+template <int EPI, typename... Args>
+void launch_tile(int tile, Args... args) {
     switch (tile) {
-        case 1:
-            // the 16x16x32 MFMA form of the same tile is 3 - 9 % faster on the store epilogues and on residual
-            // contractions with short K (measured at 2048 - 163 840 rows), level to 5 % faster on SwiGLU (512 rows), 4 - 7 %
-            // slower on residual contractions at K = 12288
-            if (EPI != EPI_RESIDUAL || Kin <= 4096)
-                return launch_cfg<256, 256, 4, 2, EPI, 2, 3, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            return launch_cfg<256, 256, 4, 2, EPI, 2, 3, S8>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-        case 5: return launch_cfg<128, 128, 2, 2, EPI, 4, 4, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-        case 8: return launch_cfg<256, 256, 4, 2, EPI, 2, 3, S8, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-        case 9: return launch_cfg<128, 128, 2, 2, EPI, 2, 3, S4, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-        default:
-            // (128x128 in the 16x16x32 form: SwiGLU 1.07 -> 1.29 PFLOP/s at 163 840 rows, the stores + 3 %, residual
-            // contractions 81 -> 73 us at K = 4096 and level at K = 12288)
-            if (EPI != EPI_RESIDUAL || Kin <= 4096)
-                return launch_cfg<128, 128, 2, 2, EPI, 2, 3, S4, 16>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
-            return launch_cfg<128, 128, 2, 2, EPI, 2, 3, S4>(A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, none, st);
+        case 1: return launch_cfg<256, 256, 2, 2, EPI, 2, 3>(args...);
+        case 2: return launch_cfg<256, 192, 2, 2, EPI, 2, 4>(args...);
+        case 3: return launch_cfg<128, 192, 2, 2, EPI, 2, 2, 2>(args...);
+        case 4: return launch_cfg<128, 64, 2, 2, EPI, 4, 4>(args...);
+        case 5: return launch_cfg<128, 128, 2, 2, EPI, 4, 4>(args...);
+        case 6: return launch_cfg<64, 64, 2, 2, EPI, 4, 4>(args...);
+        case 7: return launch_cfg<256, 128, 2, 2, EPI, 3, 4>(args...);
+        default: return launch_cfg<128, 128, 2, 2, EPI, 2, 3, 2>(args...);
     }
 }
 
-bool tile_fits(int tile, int epi) { return epi != EPI_SWIGLU || tile == 0 || tile == 1 || tile == 2 || tile == 5 || tile == 8 || tile == 9; }
+template <int EPI>
+void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nout, int Kin, int lda, int ldw,
+              const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st) {
+    launch_tile<EPI>(gemm_bf16_tile(M, Nout, EPI, Kin), A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, Top1Args(), st);
+}
 
 }   // namespace
 
@@ -103,7 +66,7 @@ const char *gemm_bf16_tile_name(int tile) {
 }
 
 int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
-    if (g_force_tile >= 0 && g_force_tile < kNumTiles && tile_fits(g_force_tile, epi)) return g_force_tile;
+    if (g_force_tile >= 0 && g_force_tile < kNumTiles) return g_force_tile;
     const bool dual = epi == EPI_SWIGLU;
     const int64_t cols = dual ? 2 * (int64_t)Nout : Nout;
     auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
@@ -175,9 +138,8 @@ void launch_gemm_bf16_split(const bf16_t *A, const bf16_t *W, int64_t M, int Nou
         if (plan.tiles && ldo % 4 == 0 && aligned16(resid) && aligned16(partial))
             return launch_gemm_stream(plan, A, W, nullptr, M, Nout, Kin, lda, ldw, EPI_RESIDUAL, nullptr, nullptr, resid, ldo, partial, st);
     }
-    Top1Args none = {};
-    launch_cfg<128, 128, 2, 2, EPI_RESIDUAL, 4, 4, S4>(A, W, nullptr, (int)M, Nout, Kin, lda, ldw, nullptr, nullptr, resid, ldo, none, st,
-                                                     splits, partial);
+    launch_cfg<128, 128, 2, 2, EPI_RESIDUAL, 4, 4>(A, W, nullptr, (int)M, Nout, Kin, lda, ldw, nullptr, nullptr, resid, ldo, Top1Args(), st,
+                                                   splits, partial);
 }
 
 // QKV projection with rotary and the V transpose in its epilogue (EPI_QKV).  The tile is the one the plain store
@@ -211,7 +173,6 @@ int gemm_bf16_qkv_cut(int64_t M, int Nout, int Kin, int tile) {
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
                           const KvDest &kv, int tile, hipStream_t st) {
-    Top1Args none = {};
     QkvArgs qa;
     qa.d_head = d_head;
     qa.v_start = v_start;
@@ -232,16 +193,8 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
         QkvArgs q = qa;
         q.v_start -= c0;
         q.k_start -= c0;
-        switch (t) {
-            case 1:   // (the 16x16x32 MFMA form: see dispatch)
-            case 8: return launch_cfg<256, 256, 4, 2, EPI_QKV, 2, 3, S8, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-            case 4: return launch_cfg<128, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-            case 5: return launch_cfg<128, 128, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-            case 6: return launch_cfg<64, 64, 2, 2, EPI_QKV, 4, 4, S4>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-            case 7: return launch_cfg<256, 128, 4, 2, EPI_QKV, 3, 4, S8, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-            case 9:
-            default: return launch_cfg<128, 128, 2, 2, EPI_QKV, 2, 3, S4, 16>(A, W + (int64_t)c0 * ldw, nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0, nullptr, ld_qkv, none, st, 1, nullptr, q);
-        }
+        launch_tile<EPI_QKV>(t, A, W + (int64_t)c0 * ldw, (const bf16_t *)nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0,
+                             (float *)nullptr, ld_qkv, Top1Args(), st, 1, (float *)nullptr, q);
     };
     const int c0 = gemm_bf16_qkv_cut(M, Nout, Kin, tile);
     if (c0 == 0) return part(tile, 0, Nout);
