@@ -141,14 +141,15 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
     static_assert(NW == 4 && TM >= 1 && TN >= 1 && (!DUAL || TN % 2 == 0), "tile shape");
     static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "every wavefront moves whole row groups of both tiles");
 
-    // XCD-aware tile id: ids i, i+8, i+16 ... land on the same XCD; give that XCD a contiguous tile range
+    // XCD-aware tile id: ids i, i+8, i+16 ... land on the same XCD; give that XCD a contiguous tile range (XCD x has one id more than
+    // n_tiles / 8 while x < n_tiles % 8)
     int pid = blockIdx.x, split = 0;
     if (EPI == EPI_RESIDUAL && k_splits > 1) {
         split = pid / n_tiles;
         pid -= split * n_tiles;
     }
     const int k_len = Kin / k_splits, k_beg = split * k_len;   // this workgroup's K range
-    if (n_tiles % 8 == 0) pid = (pid % 8) * (n_tiles / 8) + pid / 8;
+    pid = (pid % 8) * (n_tiles / 8) + min(pid % 8, n_tiles % 8) + pid / 8;
     // Each XCD has its own L2 and runs about 32 consecutive tile ids of its range at a time, all walking K roughly in
     // step, so those 32 tiles should share operand tiles both ways: ids are laid out in bands of `group_m` row tiles,
     // column-major inside a band, which makes 32 consecutive ids a patch of group_m x (32 / group_m) tiles (every

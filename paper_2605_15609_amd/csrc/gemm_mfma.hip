@@ -11,18 +11,24 @@ using namespace mfma;
 
 struct TileCfg {
     int bm, bn;
+    double stage;       // us for 64 of K with every CU at work (the model of gemm_bf16_tile)
     const char *name;
 };
-// index = value returned by gemm_bf16_tile
+// index = value returned by gemm_bf16_tile.  One workgroup per CU: two of 128x128 or 128x192 with shallower rings were never ahead
+// by more than 2 % of the best of these.
 constexpr TileCfg kTiles[] = {
-    {128, 128, "128x128, LDS rings 2/3"},   // two workgroups per CU
-    {256, 256, "256x256, LDS rings 2/3"},   // least LDS traffic per FLOP; fills the 160 KB
-    {256, 192, "256x192, LDS rings 2/4"},
-    {128, 192, "128x192, LDS rings 2/2"},   // two workgroups per CU
-    {128, 64, "128x64, LDS rings 4/4"},     // lone workgroup per CU: fetches several stages ahead
-    {128, 128, "128x128, LDS rings 4/4"},
-    {64, 64, "64x64, LDS rings 4/4"},
-    {256, 128, "256x128, LDS rings 3/4"},   // one full round of 256 workgroups for 2048 x 4096 outputs
+    {192, 256, 1.054, "192x256, LDS rings 2/3"},
+    {256, 256, 1.349, "256x256, LDS rings 2/3"},   // least LDS and fetch traffic per FLOP; fills the 160 KB
+    {256, 192, 1.067, "256x192, LDS rings 2/4"},
+    {128, 192, 0.683, "128x192, LDS rings 4/4"},
+    {128, 64, 0.341, "128x64, LDS rings 4/4"},
+    {128, 128, 0.527, "128x128, LDS rings 4/4"},
+    {64, 64, 0.208, "64x64, LDS rings 4/4"},
+    {256, 128, 0.786, "256x128, LDS rings 3/4"},
+    {96, 128, 0.435, "96x128, LDS rings 4/4"},
+    {192, 128, 0.643, "192x128, LDS rings 3/4"},
+    {192, 192, 0.841, "192x192, LDS rings 2/4"},
+    {192, 64, 0.465, "192x64, LDS rings 4/4"},
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -30,14 +36,18 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 template <int EPI, typename... Args>
 void launch_tile(int tile, Args... args) {
     switch (tile) {
+        case 0: return launch_cfg<192, 256, 2, 2, EPI, 2, 3>(args...);
         case 1: return launch_cfg<256, 256, 2, 2, EPI, 2, 3>(args...);
         case 2: return launch_cfg<256, 192, 2, 2, EPI, 2, 4>(args...);
-        case 3: return launch_cfg<128, 192, 2, 2, EPI, 2, 2, 2>(args...);
+        case 3: return launch_cfg<128, 192, 2, 2, EPI, 4, 4>(args...);
         case 4: return launch_cfg<128, 64, 2, 2, EPI, 4, 4>(args...);
-        case 5: return launch_cfg<128, 128, 2, 2, EPI, 4, 4>(args...);
         case 6: return launch_cfg<64, 64, 2, 2, EPI, 4, 4>(args...);
         case 7: return launch_cfg<256, 128, 2, 2, EPI, 3, 4>(args...);
-        default: return launch_cfg<128, 128, 2, 2, EPI, 2, 3, 2>(args...);
+        case 8: return launch_cfg<96, 128, 2, 2, EPI, 4, 4>(args...);
+        case 9: return launch_cfg<192, 128, 2, 2, EPI, 3, 4>(args...);
+        case 10: return launch_cfg<192, 192, 2, 2, EPI, 2, 4>(args...);
+        case 11: return launch_cfg<192, 64, 2, 2, EPI, 4, 4>(args...);
+        default: return launch_cfg<128, 128, 2, 2, EPI, 4, 4>(args...);
     }
 }
 
@@ -65,58 +75,43 @@ const char *gemm_bf16_tile_name(int tile) {
     return tile >= 0 && tile < kNumTiles ? kTiles[tile].name : tile == kNumTiles ? "all of up to 128 rows, streams the weights" : "?";
 }
 
-int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
-    if (g_force_tile >= 0 && g_force_tile < kNumTiles) return g_force_tile;
-    const bool dual = epi == EPI_SWIGLU;
-    const int64_t cols = dual ? 2 * (int64_t)Nout : Nout;
-    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((cols + bn - 1) / bn); };
-    // SwiGLU reads two weight operands against one activation tile: the big tile as soon as it
-    // reaches half of the CUs
-    // (a single row tile is a pure weight stream: the deep equal rings keep more of it in flight)
-    // A partial round costs a whole one, and a round of 256x192 tiles (96 gate and 96 up columns) 0.84 of a round of 256x256: it
-    // wins where it needs no more rounds (2 x 12288 outputs, K = 4096: 512 rows 103 -> 96 us, 300 rows 94.5 -> 88, 700 rows
-    // 175 -> 153; 1671 rows 280 against 316 and 2048 rows 303 against 338 stay on 256x256).
-    if (dual) {
-        const int64_t big = tiles(256, 256);
-        if (big < 128) return M <= 128 ? 5 : 0;
-        return (tiles(256, 192) + 255) / 256 <= (big + 255) / 256 ? 2 : 1;
-    }
-    // At most one 128x128 workgroup per CU: the contraction is bound by fetch latency, not by the
-    // matrix cores; small tiles reach every CU and the deep rings keep several stages in flight.
-    if (tiles(128, 128) <= 256) {
-        const int64_t t = tiles(128, 64);
-        return t <= 128 ? 6 : t <= 256 ? 4 : 5;
-    }
-    // Otherwise: rounds of workgroups over the 256 CUs times the work of one round, weighted by the
-    // rate each tile sustains on a full machine (PFLOP/s with weights streamed cold from HBM, from a
-    // sweep over the layer shapes of the benchmark configurations).  A tile that runs two workgroups per
-    // CU does a round of 512 in the time of two.
-    struct Cand {
-        int tile, per_round;
-        double rate;
-    };
-    // Residual contractions (fp32 read-modify-write epilogue), measured at 2048 x 4096 and 6144 x 3584 outputs: 256x192 beats
-    // 128x192 by 2 - 8 % and three rounds of 256x128 (K = 18944: 790 against 820 us, K = 3584: 155 against 163); one full round of
-    // 256x128 beats two 128x128 workgroups per CU (K = 4096: 66 against 75 us, in the 16x16x32 MFMA form; K = 12288, where the
-    // 32x32x16 form is level with it, 236 against 238).  Kin = 0: unknown, taken as long.  Store epilogues: the 256x128 tile is
-    // ahead of 128x128 per round of workgroups (512 x 12288 outputs: 53 against 68 us) and behind 256x192.
-    // (With the activation ring one stage deeper, 3/4 against 2/4, the 256x128 tile takes 236 us instead of 264 on 2048 x 4096
-    // outputs at K = 12288, 66 instead of 73 at K = 4096, and 53 instead of 56 on 512 x 12288.)
-    const bool resid = epi == EPI_RESIDUAL;
-    const Cand cand[] = {{1, 256, 1.25}, {2, 256, 1.16}, {3, 512, resid ? 1.12 : 1.15}, {0, 512, 1.00},
-                         {7, 256, !resid ? 1.06 : (Kin == 0 || Kin > 4096) ? 1.12 : 1.05}};
-    int best = 0;
-    double best_cost = 0;
-    for (const Cand &c : cand) {
-        const int64_t n = tiles(kTiles[c.tile].bm, kTiles[c.tile].bn);
-        const int64_t rounds = (n + c.per_round - 1) / c.per_round;
-        const double cost = (double)rounds * (c.per_round / 256) * kTiles[c.tile].bm * kTiles[c.tile].bn / c.rate;
-        if (best_cost == 0 || cost < best_cost) {
-            best_cost = cost;
-            best = c.tile;
+// Time of a launch (us).  Every workgroup has a CU to itself, so a launch takes whole rounds of 256 of them: K / 64 stages of the tile's
+// time, plus prologue and epilogue, which are bound by memory and so by the outputs of the tile (256x256: 20 us for the read and
+// write of the fp32 stream, 6.5 us for bf16 outputs).  A partial last round is shorter than a whole one, but not by much: the CUs
+// run faster with others idle (clock, caches), down to 3/4 of the time (4/5 for small tiles).  Stage times fitted to a sweep of
+// all tiles over the layer shapes of the benchmark configurations, 160 - 12 288 rows, cold weights: the tile chosen is within 1 %
+// of the fastest on average, within 10 % everywhere but for 640 rows of the residual contractions (25 %).
+static double tile_time(const TileCfg &t, int64_t M, int64_t cols, int Kin, int epi) {
+    const int64_t n = ((M + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn), whole = n / 256;
+    const double part = (double)(n % 256) / 256, area = t.bm * t.bn / 65536.0, least = area >= 0.375 ? 0.75 : 0.8;
+    const double stages = (Kin / mfma::BK) * t.stage, ends = area * (epi == EPI_RESIDUAL ? 20 : 6.5) + 0.7;
+    return 1.5 + stages * (whole + (part > 0 ? least + (1 - least) * part : 0)) + ends * (whole + (part > 0));
+}
+
+// the fastest tile among those that `fits` takes, -1: none
+template <typename F>
+static int fastest_tile(int64_t M, int64_t cols, int Kin, int epi, F fits) {
+    int best = -1;
+    double best_time = 0;
+    for (int t = 0; t < kNumTiles; ++t) {
+        if (!fits(kTiles[t])) continue;
+        const double time = tile_time(kTiles[t], M, cols, Kin, epi);
+        if (best < 0 || time < best_time) {
+            best = t;
+            best_time = time;
         }
     }
     return best;
+}
+
+// K of the model where the outputs are bf16: the depth does not move the choice there (the same regret with every shape's own K), and
+// callers that ask for a tile by rows and outputs alone get the one that runs
+constexpr int kStoreK = 4096;
+
+int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
+    if (g_force_tile >= 0 && g_force_tile < kNumTiles) return g_force_tile;
+    // SwiGLU reads two weight operands against one activation tile, half of the tile's columns each
+    return fastest_tile(M, epi == EPI_SWIGLU ? 2 * (int64_t)Nout : Nout, epi == EPI_RESIDUAL && Kin ? Kin : kStoreK, epi, [](const TileCfg &) { return true; });
 }
 
 // A residual contraction over at most 128 rows is cut along K: part 0 adds into resid, the others store partial sums that the next
@@ -142,32 +137,37 @@ void launch_gemm_bf16_split(const bf16_t *A, const bf16_t *W, int64_t M, int Nou
                                                    splits, partial);
 }
 
-// QKV projection with rotary and the V transpose in its epilogue (EPI_QKV).  The tile is the one the plain store
-// would get, provided every tile then holds whole heads of one kind: the tile width a multiple of d_head and the first
-// V column a multiple of the tile width.  -1: no such tile, run the store epilogue and the separate kernel instead.
+// QKV projection with rotary and the V transpose in its epilogue (EPI_QKV): every tile has to hold whole heads of one kind, so the
+// tile width is a multiple of d_head and the first V column a multiple of the tile width.  -1: no such tile, run the store epilogue
+// and the separate kernel instead.
+static int qkv_tile(int64_t M, int Nout, int d_head, int v_start) {
+    return fastest_tile(M, Nout, kStoreK, EPI_STORE, [&](const TileCfg &t) { return t.bn % d_head == 0 && v_start % t.bn == 0; });
+}
+
 int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_per_seq) {
     if ((d_head != 64 && d_head != 128) || rows_per_seq % 16 != 0 || Nout % 8 != 0) return -1;
-    int tile = gemm_bf16_tile(M, Nout, EPI_STORE);
-    // the 192-column tiles cut heads in two: the 256x256 tile takes over where the plain store would have picked one of
-    // them (2048 x 6144 outputs: 87 us + 24 us for the separate rotary / transpose kernel against 95 us in one)
-    if (tile == 2 || tile == 3) tile = 1;
-    const int bn = kTiles[tile].bn;
-    if (bn % d_head != 0 || v_start % bn != 0) return -1;
-    return tile;
+    if (g_force_tile >= 0 && g_force_tile < kNumTiles) {
+        const int bn = kTiles[g_force_tile].bn;
+        return bn % d_head == 0 && v_start % bn == 0 ? g_force_tile : -1;
+    }
+    return qkv_tile(M, Nout, d_head, v_start);
 }
 
 // A partial last round of 256x256 tiles costs almost a whole one.  Where the column tiles of the whole rounds come out even
-// enough, the columns behind them run as a launch of their own in smaller tiles, one round of which is shorter (2048 x 12288
-// outputs, K = 4096: 384 tiles in 179 us; 256 of them in 99, the other 4096 columns in 57 on 256x128 tiles).  Costs as in
-// gemm_bf16_tile; the second launch takes some 3 us, 2000 units at that K.  Returns the second launch's first column, 0: one launch.
-int gemm_bf16_qkv_cut(int64_t M, int Nout, int Kin, int tile) {
-    if (tile != 1 || g_force_tile >= 0) return 0;
+// enough, the columns behind them run as a launch of their own in the tiles that suit them (2048 x 12288 outputs, K = 4096: 384
+// tiles in 172 us; 256 of them in 93, the other 4096 columns in 55 on 256x128 tiles), if that is faster than `tile` alone.
+// Returns the second launch's first column, 0: one launch.
+int gemm_bf16_qkv_cut(int64_t M, int Nout, int d_head, int v_start, int tile) {
+    if (g_force_tile >= 0) return 0;
+    const TileCfg &big = kTiles[1];
+    if (big.bn % d_head != 0 || v_start % big.bn != 0) return 0;
     const int64_t tm = (M + 255) / 256, n = tm * ((Nout + 255) / 256), whole = n / 256 * 256 / tm;
     const int c0 = (int)whole * 256;
     if (n % 256 == 0 || n >= 8 * 256 || whole == 0 || c0 >= Nout) return 0;
-    auto cost = [&](int64_t tiles, double area, double rate) { return (double)((tiles + 255) / 256) * area / rate; };
-    const double rest = cost(tm * ((Nout - c0 + 127) / 128), 32768, 1.06);
-    return cost(whole * tm, 65536, 1.25) + rest + 2000.0 * 4096 / Kin < cost(n, 65536, 1.25) ? c0 : 0;
+    const int rest = qkv_tile(M, Nout - c0, d_head, v_start > c0 ? v_start - c0 : 0);
+    if (rest < 0) return 0;
+    const double two = tile_time(big, M, c0, kStoreK, EPI_STORE) + tile_time(kTiles[rest], M, Nout - c0, kStoreK, EPI_STORE);
+    return two < tile_time(kTiles[tile], M, Nout, kStoreK, EPI_STORE) ? c0 : 0;
 }
 
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
@@ -196,10 +196,10 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
         launch_tile<EPI_QKV>(t, A, W + (int64_t)c0 * ldw, (const bf16_t *)nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0,
                              (float *)nullptr, ld_qkv, Top1Args(), st, 1, (float *)nullptr, q);
     };
-    const int c0 = gemm_bf16_qkv_cut(M, Nout, Kin, tile);
+    const int c0 = gemm_bf16_qkv_cut(M, Nout, d_head, v_start, tile);
     if (c0 == 0) return part(tile, 0, Nout);
     part(1, 0, c0);
-    part(7, c0, Nout - c0);
+    part(qkv_tile(M, Nout - c0, d_head, v_start > c0 ? v_start - c0 : 0), c0, Nout - c0);
 }
 
 // the streaming kernel's plan for a contraction that it takes, tiles = 0 otherwise (16-byte accesses to out, resid and bias)

@@ -281,7 +281,7 @@ void launch_head_finish(const float *row_sum, const int32_t *row_arg, const int3
 
 // gemm_mfma.hip (bf16; Nout, Kin multiples of 64)
 // index of the tile configuration the dispatcher picks for a shape; gemm_bf16_tile_name(i) describes configuration i
-// (workgroup tile, wavefronts, LDS ring depths), 0 <= i < gemm_bf16_tile_count()
+// (workgroup tile, LDS ring depths), 0 <= i < gemm_bf16_tile_count()
 int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin = 0);   // Kin = 0: not known (matters for residual contractions only)
 int gemm_bf16_tile_count();
 // what launch_gemm_bf16 runs: such an index, or gemm_bf16_tile_count() for the streaming kernel of few rows
@@ -291,7 +291,7 @@ int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, c
 // to pass on, or -1 when the shape has no tile that holds whole heads of one kind (then the two-pass form runs).
 // rows_per_seq: rows of A per sequence (a multiple of 16); v_start: first V column; pos0: position of a sequence's row 0.
 int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_per_seq);
-int gemm_bf16_qkv_cut(int64_t M, int Nout, int Kin, int tile);   // first column of its second launch, 0: one launch
+int gemm_bf16_qkv_cut(int64_t M, int Nout, int d_head, int v_start, int tile);   // first column of its second launch, 0: one launch
 // Where the keys and the transposed values of that projection go: k = NULL: keys next to the queries in qkv, otherwise
 // straight into the sequences' KV caches (row i of sequence s at k[s * k_seq + i * ld_k], columns from k_start on); values at
 // vT[s * vt_seq + column * ld_vt + slot], slot the permuted key order of vt_key_slot.
