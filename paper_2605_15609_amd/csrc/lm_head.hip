@@ -297,8 +297,12 @@ void launch_head_confidence_bf16(const bf16_t *y, const bf16_t *W, int rows, int
         launch_cfg<SLAB_SMALL, 32, 4, 1, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else if (rows <= 64)
         launch_cfg<SLAB_BIG, 64, 4, 1, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+    else if (rows > 128 && d >= 2048)
+        // (256 hidden rows against 128 a tile, V = 126 464 - 152 064, K = 3584 - 4096: 200 rows 270 -> 226 us, 768 rows 746 -> 617, 8192 rows 6649 -> 5848
+        // = 1.45 PFLOP/s; 320 rows, a partial second tile, 365 against 389; with K = 512 it is ahead only where the tiles come out even)
+        launch_cfg<SLAB_BIG, 256, 2, 2, EPI_TOP1, 2, 3>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else
-        launch_cfg<SLAB_BIG, 128, 2, 2, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        launch_cfg<SLAB_BIG, 128, 2, 2, EPI_TOP1, 3, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     hipLaunchKernelGGL(head_merge_kernel, dim3(rows), dim3(64), 0, st, t1.pmax, t1.psum, t1.parg, slabs, rows, row_sum,
                        row_arg);
 }
