@@ -230,6 +230,56 @@ void launch_kv_store(const T *qkv, int ld_qkv, int S, int rows_per_seq, int row_
     hipLaunchKernelGGL(kv_store_kernel<T>, dim3((unsigned)(S * count)), dim3(256), 0, st, qkv, ld_qkv, rows_per_seq, row_first,
                        count, n_heads, n_kv_heads, d_head, k_cache, vt_cache, at);
 }
+namespace {
+// The refreshed entries of the approximate cache: the rotated keys and the values of every position outside the block, prefix first,
+// in one launch with 16-byte accesses.  Values come from the key-contiguous copy that the attention has just read, so a cache row is
+// a row of it with the block cut out: 8 slots (keys 0-3 and 8-11, or 4-7 and 12-15, of a group of 16) move at once where the
+// group stays a group, i.e. everywhere but for the group that the prefix ends in (cached block lengths are multiples of 16).
+// Workgroups [0, S * (N - L)): one row of keys each; the rest: one value row (channel) per wavefront.
+__global__ __launch_bounds__(256) void kv_store_outside_kernel(const bf16_t *__restrict__ qkv, int ld_qkv, const bf16_t *__restrict__ vT, int ld_vt_src,
+                                                               int S, int N, int b0, int L, int n_heads, int w, bf16_t *__restrict__ k_cache,
+                                                               bf16_t *__restrict__ vt_cache, int d_head, KvPrefix at) {
+    const int kept = N - L, n_keys = S * kept;
+    const auto cache_of = [&](int s) { return (int64_t)((at.seq_rows ? at.seq_rows[s] : s) / at.seqs_per_cache); };
+    if ((int)blockIdx.x < n_keys) {
+        const int s = blockIdx.x / kept, j = blockIdx.x % kept, i = j < b0 ? j : j + L;
+        const uint4 *src = reinterpret_cast<const uint4 *>(qkv + ((int64_t)s * N + i) * ld_qkv + n_heads * d_head);
+        uint4 *dst = reinterpret_cast<uint4 *>(k_cache + cache_of(s) * at.stride_k + (int64_t)j * at.ld_k);
+        for (int c = threadIdx.x; c < w / 8; c += 256) dst[c] = src[c];
+        return;
+    }
+    const int64_t row = (int64_t)(blockIdx.x - n_keys) * 4 + (threadIdx.x >> 6);   // (w is a multiple of 4: rows of one sequence)
+    const int s = (int)(row / w), c = (int)(row % w);
+    const bf16_t *src = vT + row * ld_vt_src;
+    bf16_t *dst = vt_cache + cache_of(s) * at.stride_vt + (int64_t)c * at.ld_vt;
+    for (int u = threadIdx.x & 63; u * 8 < (kept + 15) / 16 * 16; u += 64) {
+        const int g = u >> 1, first = g * 16 + 4 * (u & 1), last = first + 11;      // keys first .. first + 3 and last - 3 .. last
+        const int shift = first < b0 ? 0 : L;
+        if (last < kept && (last < b0 || first >= b0)) {
+            *reinterpret_cast<uint4 *>(dst + u * 8) = *reinterpret_cast<const uint4 *>(src + u * 8 + shift);
+        } else {
+            for (int e = 0; e < 8; ++e) {
+                const int j = first + (e & 3) + (e >> 2) * 8;
+                if (j < kept) dst[u * 8 + e] = src[vt_key_slot(j < b0 ? j : j + L)];
+            }
+        }
+    }
+}
+}   // namespace
+
+bool launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
+                             bf16_t *k_cache, bf16_t *vt_cache, const KvPrefix &at, hipStream_t st) {
+    const int w = n_kv_heads * d_head;
+    const auto aligned = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+    if (d_head % 8 || ld_qkv % 8 || at.ld_k % 8 || at.ld_vt % 8 || at.stride_k % 8 || at.stride_vt % 8 || !aligned(qkv) || !aligned(vT) || !aligned(k_cache) ||
+        !aligned(vt_cache))
+        return false;
+    if (N <= L || S <= 0) return true;
+    hipLaunchKernelGGL(kv_store_outside_kernel, dim3((unsigned)(S * (N - L) + S * (int64_t)w / 4)), dim3(256), 0, st, qkv, ld_qkv, vT, (int)vt_row_stride(N), S,
+                       N, b0, L, n_heads, w, k_cache, vt_cache, d_head, at);
+    return true;
+}
+
 template void launch_kv_store<float>(const float *, int, int, int, int, int, int, int, int, float *, float *, const KvPrefix &,
                                      hipStream_t);
 template void launch_kv_store<bf16_t>(const bf16_t *, int, int, int, int, int, int, int, int, bf16_t *, bf16_t *, const KvPrefix &,

@@ -71,11 +71,13 @@ struct Dispatch<float> {
     static bool block_attention(psd_handle *, const float *, int, int, int, int, int, int, int, float *, const KvPrefix &, hipStream_t) {
         return false;
     }
-    static void rope_attention(psd_handle *h, float *qkv, int ld_qkv, float *, int S, int N, int pos0, int H, int Hkv, int dh,
+    static bool rope_attention(psd_handle *h, float *qkv, int ld_qkv, float *, int S, int N, int pos0, int H, int Hkv, int dh,
                                float *out, const KvPrefix &pre, int block_len, hipStream_t st, bool = false) {
         launch_rope<float>(qkv, ld_qkv, (int64_t)S * N, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, st);
         launch_plain_attention<float>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
+        return false;
     }
+    static bool store_outside(const float *, int, const float *, int, int, int, int, int, int, int, float *, float *, const KvPrefix &, hipStream_t) { return false; }
 };
 
 template <>
@@ -146,7 +148,8 @@ struct Dispatch<bf16_t> {
     // rotated: qkv_fused produced qkv and vT, only the attention is left.
     // Lengths that are no multiple of 8 keep fp32 probabilities and the plain kernel's order of sums; whole sequences of them run on
     // the fp32 matrix instructions with the same bits.
-    static void rope_attention(psd_handle *h, bf16_t *qkv, int ld_qkv, bf16_t *vT, int S, int N, int pos0, int H, int Hkv, int dh,
+    // Returns whether vT holds the values.
+    static bool rope_attention(psd_handle *h, bf16_t *qkv, int ld_qkv, bf16_t *vT, int S, int N, int pos0, int H, int Hkv, int dh,
                                bf16_t *out, const KvPrefix &pre, int block_len, hipStream_t st, bool rotated = false) {
         if (rotated) {
             launch_attention_bf16(qkv, ld_qkv, vT, S, N, H, Hkv, dh, out, pre, st);
@@ -155,11 +158,17 @@ struct Dispatch<bf16_t> {
             const bool whole = !(h->plain_mask & 2) && pre.len == 0 && !(block_len > 0 && block_len < N);
             if (!whole || !launch_attention_ordered(qkv, ld_qkv, S, N, H, Hkv, dh, out, st))
                 launch_plain_attention<bf16_t>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
+            return false;
         } else {
             // the matrix-core kernel reads V transposed; rotary and that transpose share one launch
             launch_rope_transpose_v(qkv, ld_qkv, S, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, vT, st);
             launch_attention_bf16(qkv, ld_qkv, vT, S, N, H, Hkv, dh, out, pre, st);
         }
+        return true;
+    }
+    static bool store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int H, int Hkv, int dh, bf16_t *k_cache,
+                              bf16_t *vt_cache, const KvPrefix &at, hipStream_t st) {
+        return launch_kv_store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st);
     }
 };
 
@@ -194,12 +203,11 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         const int block_len = c.attention == PSD_ATTN_BLOCK_CAUSAL ? L : 0;
         bool rotated = false;
         if (fused) {
-            // (the approximate-cache refresh reads V row-major out of qkv afterwards: two-pass form there)
             KvDest own;
             own.vT = (bf16_t *)vT;
             own.ld_vt = (int)vt_row_stride(N);
             own.vt_seq = (int64_t)Hkv * dh * own.ld_vt;
-            rotated = !store && ld_qkv == qkv_w &&
+            rotated = ld_qkv == qkv_w &&
                       Dispatch<T>::qkv_fused(h, a, wq, ntok, N, 0, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, own, block_len, st);
             if (!rotated) Dispatch<T>::gemm(h, a, d, wq, nullptr, d, ntok, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st);
         } else {
@@ -207,7 +215,7 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             Dispatch<T>::gemm(h, a, d, wk, nullptr, d, ntok, Hkv * dh, d, epi_qkv, lw.bk, qkv + H * dh, nullptr, ld_qkv, nullptr, st);
             Dispatch<T>::gemm(h, a, d, wv, nullptr, d, ntok, Hkv * dh, d, epi_qkv, lw.bv, qkv + (H + Hkv) * dh, nullptr, ld_qkv, nullptr, st);
         }
-        Dispatch<T>::rope_attention(h, qkv, ld_qkv, vT, S, N, 0, H, Hkv, dh, o, KvPrefix(), block_len, st, rotated);
+        const bool transposed = Dispatch<T>::rope_attention(h, qkv, ld_qkv, vT, S, N, 0, H, Hkv, dh, o, KvPrefix(), block_len, st, rotated);
         if (store) {
             // approximate cache: freeze this layer's keys / values of every position outside the block, prefix first
             const KvLayout lay = kv_layout(c, store->capacity);
@@ -219,9 +227,14 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             at.seq_rows = seq_rows;
             at.len = 0;
             const int b0 = block_start.common;     // (a common block start: checked by run_forward_hidden)
-            launch_kv_store<T>(qkv, ld_qkv, S, N, 0, b0, H, Hkv, dh, k_cache, vt_cache, at, st);
-            at.len = b0;
-            launch_kv_store<T>(qkv, ld_qkv, S, N, b0 + L, N - b0 - L, H, Hkv, dh, k_cache, vt_cache, at, st);
+            // one launch of 16-byte copies where the attention read the values key-contiguous (8B shape, 512 tokens: rotary, attention and
+            // copies 53 us a layer, 26 with it and the projection's own rotary); else (lengths that are no multiple of 8, the debug paths) V
+            // is row-major in qkv
+            if (!transposed || !Dispatch<T>::store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st)) {
+                launch_kv_store<T>(qkv, ld_qkv, S, N, 0, b0, H, Hkv, dh, k_cache, vt_cache, at, st);
+                at.len = b0;
+                launch_kv_store<T>(qkv, ld_qkv, S, N, b0 + L, N - b0 - L, H, Hkv, dh, k_cache, vt_cache, at, st);
+            }
         }
         // After the last attention only the block rows feed the LM-head: the rest of that layer (output
         // projection, FFN) and the final norm run on those S*L rows alone, gathered into a packed stream.

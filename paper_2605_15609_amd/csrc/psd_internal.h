@@ -229,6 +229,10 @@ void launch_embed_block(const int32_t *tokens, const int32_t *seq_rows, int S, i
 template <typename T>
 void launch_kv_store(const T *qkv, int ld_qkv, int S, int rows_per_seq, int row_first, int count, int n_heads, int n_kv_heads,
                      int d_head, T *k_cache, T *vt_cache, const KvPrefix &at, hipStream_t st);
+// the entries of all positions outside rows [b0, b0 + L) of every sequence (N rows each, rotated) at cache positions 0 .. N - L - 1, values
+// taken from vT (as the MFMA attention reads them); false, nothing launched: not 16-byte accessible
+bool launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
+                             bf16_t *k_cache, bf16_t *vt_cache, const KvPrefix &at, hipStream_t st);
 // K-split partial sums that still have to be added to the residual stream h [rows, d]: partial[s] has the
 // same shape, s = 0 .. n-1, `stride` floats apart.  The norm that reads h next adds them (and stores h).
 struct PendingSums {

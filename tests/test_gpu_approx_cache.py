@@ -173,3 +173,29 @@ def test_argument_errors():
         psd.psd_decode_block_approx(bc, d, 16, L, psd.Policy(), psd.chain_graph(2), psd.KvCache(bc, 1, N))   # exact cache exists
     with pytest.raises(psd.PsdError):
         psd.psd_kv_prefill(model, d, 16, L, cache)                                           # the exact cache calls need block-causal
+
+
+@pytest.mark.parametrize("name", list(BF16))
+@pytest.mark.parametrize("N,start,L", [(96, 40, 16), (104, 24, 16), (120, 33, 48), (128, 0, 32), (136, 104, 32), (72, 8, 64), (160, 61, 48), (1040, 515, 64)])
+def test_refreshed_entries_are_copies_of_the_keys_and_values(name, N, start, L):
+    """A refresh stores the entries from the key-contiguous values that the attention reads, or (plain attention, debug bit 1) from
+    the row-major ones.  In a one-layer model both see the same keys and values, so the caches must be equal bit for bit, and
+    neither may touch what lies behind the N - L positions.  Prefixes that end inside a group of 16 keys or are empty, an empty
+    suffix."""
+    import paper_2605_15609_amd as psd
+    shape = inp.cut_down(BF16[name], n_layers=1)
+    B = 3
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    tokens = np.stack([inp.draw_prompt(shape.vocab, N, 70 + b) for b in range(B)]).astype(np.int32)
+    tokens[:, start:start + L] = shape.mask_id
+    mem = {}
+    for mask in (0, 2):
+        model.set_plain(mask)
+        cache = psd.KvCache(model, B, N - L + 8)
+        cache.mem.fill_(0x7f)
+        psd.psd_forward_confidence_approx(model, _dev(tokens), start, L, cache, refresh=True)
+        mem[mask] = cache.mem.clone()
+    model.set_plain(0)
+    assert torch.equal(mem[0], mem[2])
+    values = mem[0].view(torch.int16)
+    assert int((values != 0x7f7f).sum()) >= values.numel() * (N - L) // (2 * ((N - L + 8 + 63) // 64 * 64)) * 0.9
