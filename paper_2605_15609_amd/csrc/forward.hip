@@ -56,13 +56,13 @@ template <>
 struct Dispatch<float> {
     // A [M, Kin] with row stride lda; weights [Nout, Kin] with row stride ldw
     static PendingSums gemm(psd_handle *, const float *A, int lda, const void *W, const void *W2, int ldw, int64_t M, int Nout,
-                            int Kin, int epi, const float *bias, float *out, float *resid, int ldo, float *, hipStream_t st) {
+                            int Kin, int epi, const float *bias, float *out, float *resid, int ldo, float *, hipStream_t st, const Warm & = Warm()) {
         launch_plain_gemm<float, float>(A, (const float *)W, (const float *)W2, M, Nout, Kin, lda, ldw, epi, bias, 1.0f, out,
                                         resid, ldo, st);
         return PendingSums();
     }
     static bool qkv_fused(psd_handle *, const float *, const void *, int64_t, int, int, int, int, int, const float *, float *, int,
-                          const KvDest &, int, hipStream_t) {
+                          const KvDest &, int, hipStream_t, const Warm & = Warm()) {
         return false;
     }
     static bool append_attention(psd_handle *, const float *, int, int, int, int, int, int, float *, const KvPrefix &, int, int, hipStream_t) {
@@ -85,7 +85,7 @@ struct Dispatch<bf16_t> {
     // returns the K-split partial sums (left in `ksplit`) that the next reader of resid has to add
     static PendingSums gemm(psd_handle *h, const bf16_t *A, int lda, const void *W, const void *W2, int ldw, int64_t M, int Nout,
                             int Kin, int epi, const float *bias, bf16_t *out, float *resid, int ldo, float *ksplit,
-                            hipStream_t st) {
+                            hipStream_t st, const Warm &next = Warm()) {
         PendingSums pend;
         if (h->plain_mask & 1)
             launch_plain_gemm<bf16_t, bf16_t>(A, (const bf16_t *)W, (const bf16_t *)W2, M, Nout, Kin, lda, ldw, epi, bias, 1.0f, out,
@@ -101,7 +101,7 @@ struct Dispatch<bf16_t> {
             const bool timed = pr.enabled && epi == pr.epi && pr.used + 2 <= pr.ev.size() &&
                                gemm_bf16_kernel(M, Nout, Kin, epi, bias, out, resid, ldo) == pr.tile;
             if (timed) (void)hipEventRecord(pr.ev[pr.used], st);
-            launch_gemm_bf16(A, (const bf16_t *)W, (const bf16_t *)W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, st);
+            launch_gemm_bf16(A, (const bf16_t *)W, (const bf16_t *)W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, st, next);
             if (timed) {
                 (void)hipEventRecord(pr.ev[pr.used + 1], st);
                 pr.used += 2;
@@ -115,14 +115,14 @@ struct Dispatch<bf16_t> {
     // epilogue; false (nothing launched) when the matrix-core attention will not run on its output, the shape has no
     // tile that holds whole heads, or a debug switch (plain_mask bit 3) asks for the two-pass form.
     static bool qkv_fused(psd_handle *h, const bf16_t *A, const void *W, int64_t M, int N, int pos0, int H, int Hkv, int dh,
-                          const float *bias, bf16_t *qkv, int ld_qkv, const KvDest &kv, int block_len, hipStream_t st) {
+                          const float *bias, bf16_t *qkv, int ld_qkv, const KvDest &kv, int block_len, hipStream_t st, const Warm &next = Warm()) {
         if ((h->plain_mask & (1 | 2 | 8)) || (block_len > 0 && block_len < N)) return false;
         if (h->probe.enabled && (h->probe.epi == EPI_STORE || h->probe.epi == EPI_BIAS)) return false;   // that probe times the plain store
         const int d = h->cfg.d_model, qkv_w = (H + 2 * Hkv) * dh;
         const int tile = gemm_bf16_qkv_tile(M, qkv_w, dh, (H + Hkv) * dh, N);
         if (tile < 0) return false;
         launch_gemm_bf16_qkv(A, (const bf16_t *)W, M, qkv_w, d, d, d, bias, qkv, ld_qkv, dh, (H + Hkv) * dh, N, pos0, h->rope_cos,
-                             h->rope_sin, kv, tile, st);
+                             h->rope_sin, kv, tile, st, next);
         return true;
     }
     // attention of R rows per sequence, one block or several, whose own keys and values are in the cache already; false: not
@@ -194,6 +194,16 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
     launch_embed<T>(tokens, seq_rows, S, N, (const T *)h->tok_emb, c.vocab, d, hbuf, st);
     for (size_t li = 0; li < h->layers.size(); ++li) {
         const psd_handle::Layer &lw = h->layers[li];
+        Warm next_o, next_down, next_qkv;   // weights that the contractions in front of them may read ahead
+        if (c.dtype == PSD_DTYPE_BF16) {
+            next_o.add(lw.wo, d, H * dh, H * dh);
+            next_down.add(lw.w_down, d, F, h->w_down_stride);
+            if (li + 1 < h->layers.size()) {
+                next_qkv.add(h->layers[li + 1].wq, (int64_t)H * dh, d, d);
+                next_qkv.add(h->layers[li + 1].wk, (int64_t)Hkv * dh, d, d);
+                next_qkv.add(h->layers[li + 1].wv, (int64_t)Hkv * dh, d, d);
+            }
+        }
         launch_rmsnorm<T>(hbuf, ntok, d, lw.attn_norm, c.rms_eps, a, pend, st);
         const int epi_qkv = c.qkv_bias ? EPI_BIAS : EPI_STORE;
         // one launch when wq | wk | wv (and the biases) sit back to back in memory, as one [qkv_w, d] matrix
@@ -208,8 +218,8 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             own.ld_vt = (int)vt_row_stride(N);
             own.vt_seq = (int64_t)Hkv * dh * own.ld_vt;
             rotated = ld_qkv == qkv_w &&
-                      Dispatch<T>::qkv_fused(h, a, wq, ntok, N, 0, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, own, block_len, st);
-            if (!rotated) Dispatch<T>::gemm(h, a, d, wq, nullptr, d, ntok, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st);
+                      Dispatch<T>::qkv_fused(h, a, wq, ntok, N, 0, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, own, block_len, st, next_o);
+            if (!rotated) Dispatch<T>::gemm(h, a, d, wq, nullptr, d, ntok, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st, next_o);
         } else {
             Dispatch<T>::gemm(h, a, d, wq, nullptr, d, ntok, H * dh, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st);
             Dispatch<T>::gemm(h, a, d, wk, nullptr, d, ntok, Hkv * dh, d, epi_qkv, lw.bk, qkv + H * dh, nullptr, ld_qkv, nullptr, st);
@@ -251,8 +261,8 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         }
         pend = Dispatch<T>::gemm(h, os, H * dh, lw.wo, nullptr, H * dh, nrow, d, H * dh, EPI_RESIDUAL, nullptr, nullptr, hs, d, ksplit, st);
         launch_rmsnorm<T>(hs, nrow, d, lw.ffn_norm, c.rms_eps, a, pend, st);
-        Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st);
-        pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hs, d, ksplit, st);
+        Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st, next_down);
+        pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hs, d, ksplit, st, next_qkv);
     }
     T *ypack = (c.dtype == PSD_DTYPE_BF16 && h->lm_head_packed && head_stream_supported(S * L, d)) ? (T *)(ws + p.off_ypack) : nullptr;
     if (final_in != hbuf)   // already the packed block rows
@@ -293,6 +303,16 @@ int32_t forward_cached_impl(psd_handle *h, const int32_t *tokens, const int32_t 
     launch_embed_block<T>(tokens, seq_rows, S, N, block_start, R, (const T *)h->tok_emb, c.vocab, d, hbuf, st);
     for (size_t li = 0; li < h->layers.size(); ++li) {
         const psd_handle::Layer &lw = h->layers[li];
+        Warm next_o, next_down, next_qkv;   // weights that the contractions in front of them may read ahead
+        if (c.dtype == PSD_DTYPE_BF16) {
+            next_o.add(lw.wo, d, H * dh, H * dh);
+            next_down.add(lw.w_down, d, F, h->w_down_stride);
+            if (li + 1 < h->layers.size()) {
+                next_qkv.add(h->layers[li + 1].wq, (int64_t)H * dh, d, d);
+                next_qkv.add(h->layers[li + 1].wk, (int64_t)Hkv * dh, d, d);
+                next_qkv.add(h->layers[li + 1].wv, (int64_t)Hkv * dh, d, d);
+            }
+        }
         T *k_cache = (T *)kv.base + (int64_t)li * (lay.k_elems + lay.vt_elems), *vt_cache = k_cache + lay.k_elems;
         pre.k = k_cache;
         pre.vt = vt_cache;
@@ -312,11 +332,11 @@ int32_t forward_cached_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             to.k = (bf16_t *)k_cache + (int64_t)kv.len * lay.ld_k;
             to.ld_k = pre.ld_k;
             to.k_start = H * dh;
-            stored = Dispatch<T>::qkv_fused(h, a, wq, nrow, R, block_start, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, to, 0, st);
+            stored = Dispatch<T>::qkv_fused(h, a, wq, nrow, R, block_start, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, to, 0, st, next_o);
         }
         if (!stored) {
             if (fused && !kv_only) {
-                Dispatch<T>::gemm(h, a, d, wq, nullptr, d, nrow, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st);
+                Dispatch<T>::gemm(h, a, d, wq, nullptr, d, nrow, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st, next_o);
             } else {
                 if (!kv_only) Dispatch<T>::gemm(h, a, d, wq, nullptr, d, nrow, H * dh, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st);
                 Dispatch<T>::gemm(h, a, d, wk, nullptr, d, nrow, (kv_joined ? 2 : 1) * Hkv * dh, d, epi_qkv, lw.bk, qkv + H * dh, nullptr, ld_qkv, nullptr, st);
@@ -338,8 +358,8 @@ int32_t forward_cached_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         }
         pend = Dispatch<T>::gemm(h, o, H * dh, lw.wo, nullptr, H * dh, nrow, d, H * dh, EPI_RESIDUAL, nullptr, nullptr, hbuf, d, ksplit, st);
         launch_rmsnorm<T>(hbuf, nrow, d, lw.ffn_norm, c.rms_eps, a, pend, st);
-        Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st);
-        pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hbuf, d, ksplit, st);
+        Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st, next_down);
+        pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hbuf, d, ksplit, st, next_qkv);
     }
     T *ypack = (c.dtype == PSD_DTYPE_BF16 && h->lm_head_packed && head_stream_supported(S * L, d)) ? (T *)(ws + p.off_ypack) : nullptr;
     launch_rmsnorm_block<T>(hbuf, nullptr, S, L, 0, L, d, h->final_norm, c.rms_eps, y, ypack, pend, st);

@@ -47,6 +47,7 @@
 #include "psd_internal.h"
 #include "device_types.h"
 #include "rope_device.h"
+#include "warm_device.h"
 
 // row tiles per band of the tile order (see the kernel); 4 unless a tuning run changes it (measured over the layer
 // contractions of the 8B shapes at 2048 - 163 840 rows: bands of 4 and 8 within 1 %, 1 and 16 about 5 % slower)
@@ -127,7 +128,10 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
                                                         const float *__restrict__ bias, bf16_t *__restrict__ out,
                                                         float *__restrict__ resid, int ldo, int tiles_n, int n_tiles,
                                                         Top1Args t1, int k_splits, float *__restrict__ partial, int group_m,
-                                                        QkvArgs qa) {
+                                                        QkvArgs qa, Warm next) {
+    if constexpr (EPI != EPI_TOP1) {
+        if ((int)blockIdx.x >= (int)gridDim.x - next.wgs) return warm_part(next, blockIdx.x - (gridDim.x - next.wgs));   // spare workgroups
+    }
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int ROW_BYTES = BK * 2;                     // an LDS row: one tile row of one stage
     constexpr int LPR = ROW_BYTES / 16, RPI = 64 / LPR;   // lanes per LDS row (8) and rows per DMA instruction (8: 1 KB)
@@ -557,7 +561,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
 template <int BM, int BN, int WGM, int WGN, int EPI, int NSA, int NSB, int WPS = 1>
 void launch_cfg(const bf16_t *X, const bf16_t *Y, const bf16_t *Y2, int M, int Nout, int Kin, int ldx, int ldy, const float *bias,
                 bf16_t *out, float *resid, int ldo, Top1Args t1, hipStream_t st, int k_splits = 1, float *partial = nullptr,
-                QkvArgs qa = QkvArgs()) {
+                QkvArgs qa = QkvArgs(), const Warm &next = Warm()) {
     constexpr int BN_OUT = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (Nout + BN_OUT - 1) / BN_OUT;
     const int n_tiles = tiles_m * tiles_n;
@@ -567,8 +571,8 @@ void launch_cfg(const bf16_t *X, const bf16_t *Y, const bf16_t *Y2, int M, int N
     static std::atomic<uint64_t> lds_raised{0};   // one per instantiation
     ensure_dynamic_lds(reinterpret_cast<const void *>(kern), smem, lds_raised);
     if (EPI != EPI_RESIDUAL) k_splits = 1;
-    hipLaunchKernelGGL(kern, dim3(n_tiles * k_splits), dim3(WGM * WGN * 64), smem, st, X, Y, Y2, M, Nout, Kin, ldx, ldy, bias, out, resid,
-                       ldo, tiles_n, n_tiles, t1, k_splits, partial, gemm_tile_group_m(), qa);
+    hipLaunchKernelGGL(kern, dim3(n_tiles * k_splits + next.wgs), dim3(WGM * WGN * 64), smem, st, X, Y, Y2, M, Nout, Kin, ldx, ldy, bias, out, resid,
+                       ldo, tiles_n, n_tiles, t1, k_splits, partial, gemm_tile_group_m(), qa, next);
 }
 
 }   // namespace mfma

@@ -51,10 +51,32 @@ void launch_tile(int tile, Args... args) {
     }
 }
 
+// What the CUs that the last round of tiles leaves idle read ahead of `next`: items are cut to the bytes that they fetch in half of the
+// round (45 GB/s a CU, 2 TB/s together), so that the tiles end last and keep most of the HBM rate (3 TB/s over 60 % of it gave
+// the 7B cached batch 17.6 - 17.9 ms, 4 TB/s over 90 % 17.8, this 17.5, nothing 18.1; 8B prefill 8.47, nothing 8.59).  Above 2048 rows
+// the contractions are bound by the matrix cores, whatever their weights come from.
+Warm spare_reads(Warm next, int tile, int64_t M, int64_t cols, int Kin) {
+    const TileCfg &t = kTiles[tile];
+    const int64_t n = ((M + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn);
+    const int idle = (int)((256 - n % 256) % 256);
+    const double rate = idle * 45e3 < 2e6 ? idle * 45e3 : 2e6;     // bytes per us
+    int64_t left = idle < 16 || M > 2048 ? 0 : (int64_t)(rate * (Kin / mfma::BK) * t.stage * 0.5) / 1024;    // KB
+    for (int i = 0; i < next.n; ++i) {
+        const int64_t fit = left / next.rows[i];
+        if (next.kb[i] > fit) next.kb[i] = (int)fit;
+        left -= (int64_t)next.rows[i] * next.kb[i];
+        if (next.kb[i]) next.wgs = idle;
+        else next.rows[i] = 0;
+    }
+    return next;
+}
+
 template <int EPI>
 void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nout, int Kin, int lda, int ldw,
-              const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st) {
-    launch_tile<EPI>(gemm_bf16_tile(M, Nout, EPI, Kin), A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, Top1Args(), st);
+              const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st, const Warm &next) {
+    const int tile = gemm_bf16_tile(M, Nout, EPI, Kin);
+    launch_tile<EPI>(tile, A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, Top1Args(), st, 1, (float *)nullptr, QkvArgs(),
+                     spare_reads(next, tile, M, EPI == EPI_SWIGLU ? 2 * (int64_t)Nout : Nout, Kin));
 }
 
 }   // namespace
@@ -172,7 +194,7 @@ int gemm_bf16_qkv_cut(int64_t M, int Nout, int d_head, int v_start, int tile) {
 
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
-                          const KvDest &kv, int tile, hipStream_t st) {
+                          const KvDest &kv, int tile, hipStream_t st, const Warm &next) {
     QkvArgs qa;
     qa.d_head = d_head;
     qa.v_start = v_start;
@@ -194,7 +216,7 @@ void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout,
         q.v_start -= c0;
         q.k_start -= c0;
         launch_tile<EPI_QKV>(t, A, W + (int64_t)c0 * ldw, (const bf16_t *)nullptr, m, cols, Kin, lda, ldw, bias ? bias + c0 : nullptr, qkv + c0,
-                             (float *)nullptr, ld_qkv, Top1Args(), st, 1, (float *)nullptr, q);
+                             (float *)nullptr, ld_qkv, Top1Args(), st, 1, (float *)nullptr, q, c0 + cols == Nout ? spare_reads(next, t, M, cols, Kin) : Warm());
     };
     const int c0 = gemm_bf16_qkv_cut(M, Nout, d_head, v_start, tile);
     if (c0 == 0) return part(tile, 0, Nout);
@@ -215,15 +237,15 @@ int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, c
 }
 
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,
-                      const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st) {
+                      const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st, const Warm &next) {
     const int m = (int)M;
     const StreamPlan plan = stream_choice(M, Nout, Kin, epi, bias, out, resid, ldo);
     if (plan.tiles) return launch_gemm_stream(plan, A, W, W2, M, Nout, Kin, lda, ldw, epi, bias, out, resid, ldo, nullptr, st);
     switch (epi) {
-        case EPI_STORE: dispatch<EPI_STORE>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
-        case EPI_BIAS: dispatch<EPI_BIAS>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
-        case EPI_RESIDUAL: dispatch<EPI_RESIDUAL>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
-        default: dispatch<EPI_SWIGLU>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st); break;
+        case EPI_STORE: dispatch<EPI_STORE>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st, next); break;
+        case EPI_BIAS: dispatch<EPI_BIAS>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st, next); break;
+        case EPI_RESIDUAL: dispatch<EPI_RESIDUAL>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st, next); break;
+        default: dispatch<EPI_SWIGLU>(A, W, W2, m, Nout, Kin, lda, ldw, bias, out, resid, ldo, st, next); break;
     }
 }
 

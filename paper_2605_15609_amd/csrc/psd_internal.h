@@ -283,6 +283,24 @@ void launch_head_finish(const float *row_sum, const int32_t *row_arg, const int3
                         const int32_t *out_rows, int S, int N, BlockStart block_start, int L, int mask_id, int vocab, int32_t *top1,
                         float *conf, hipStream_t st);
 
+// Weights that spare workgroups of a launch read ahead (warm_device.h): the first kb KB of `rows` rows, `stride` bytes apart, of each
+// item, in order; wgs workgroups behind the launch's own
+struct Warm {
+    static constexpr int ITEMS = 3;
+    const char *p[ITEMS] = {};
+    int64_t stride[ITEMS] = {};
+    int rows[ITEMS] = {}, kb[ITEMS] = {};
+    int n = 0, wgs = 0;
+    // a bf16 matrix [n_rows, cols] with row stride ld, whole KB of its rows (16-byte accesses)
+    void add(const void *w, int64_t n_rows, int64_t cols, int64_t ld) {
+        const int64_t use = cols * 2 / 1024;
+        if (n == ITEMS || use < 1 || (reinterpret_cast<uintptr_t>(w) & 15) || ld % 8 || n_rows * use > (1 << 24)) return;
+        p[n] = (const char *)w;
+        stride[n] = ld * 2;
+        rows[n] = (int)n_rows;
+        kb[n++] = (int)use;
+    }
+};
 // gemm_mfma.hip (bf16; Nout, Kin multiples of 64)
 // index of the tile configuration the dispatcher picks for a shape; gemm_bf16_tile_name(i) describes configuration i
 // (workgroup tile, LDS ring depths), 0 <= i < gemm_bf16_tile_count()
@@ -309,7 +327,7 @@ struct KvDest {
 };
 void launch_gemm_bf16_qkv(const bf16_t *A, const bf16_t *W, int64_t M, int Nout, int Kin, int lda, int ldw, const float *bias, bf16_t *qkv,
                           int ld_qkv, int d_head, int v_start, int rows_per_seq, int pos0, const float *cos_t, const float *sin_t,
-                          const KvDest &kv, int tile, hipStream_t st);
+                          const KvDest &kv, int tile, hipStream_t st, const Warm &next = Warm());
 // K-split of a residual contraction (1 = none).  With s > 1 parts, launch_gemm_bf16_split adds part 0 into
 // resid and stores parts 1..s-1 to partial [s-1][M][Nout] fp32; the next reader of resid adds them in order.
 int gemm_bf16_splits(int64_t M, int Nout, int Kin);
@@ -332,8 +350,9 @@ void gemm_bf16_force_tile(int tile);
 // 256 workgroups x 4 wavefronts x iters x 16 MFMAs (32x32x16 bf16) on the given operand data; sink >= 4 MiB
 void launch_mfma_rate(const void *operands, int n_vec16, int iters, void *sink, hipStream_t st);
 // A [M, Kin] with row stride lda, W / W2 [Nout, Kin] with row stride ldw (elements)
+// next: what the launch behind this one will read, for workgroups that the last round of tiles has to spare
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,
-                      const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st);
+                      const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st, const Warm &next = Warm());
 // attention_mfma.hip (bf16, d_head 64 or 128): q, k from qkv (rotary applied), values from vT (NULL: all keys are in the prefix)
 void launch_attention_bf16(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int n_heads, int n_kv_heads, int d_head,
                            bf16_t *out, const KvPrefix &pre, hipStream_t st);
