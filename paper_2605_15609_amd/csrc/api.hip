@@ -36,6 +36,25 @@ __global__ void count_masks_kernel(const int32_t *__restrict__ tokens, int N, Bl
     }
 }
 
+// The same for the sequences of `who` without anything copied to the device before it or back after it: the block starts come as an
+// argument and are stored for the kernels that follow (starts == NULL: one common start), the counts also go to pinned host memory.
+// clear: the counters start from zero.
+__global__ void enter_kernel(const int32_t *__restrict__ tokens, int N, SeqStarts at, SeqSet who, int L, int32_t mask_id, int32_t *__restrict__ n_left,
+                             int32_t *__restrict__ devstats, int32_t *__restrict__ starts, int32_t *__restrict__ n_left_host, int clear) {
+    const int b = blockIdx.x, j = threadIdx.x;
+    int32_t *ds = devstats + (int64_t)b * PSD_DEVSTAT_WORDS;
+    if (starts && j == 0) starts[b] = at.at[b];
+    const bool counted = who.has(b);
+    const bool live = counted && j < L && tokens[(int64_t)b * N + at.at[b] + j] == mask_id;
+    const uint64_t set = __ballot(live);
+    for (int i = j; i < PSD_DEVSTAT_WORDS; i += 64) {
+        const bool entry = counted && (i == PSD_DEVSTAT_ENTRY || i == PSD_DEVSTAT_ENTRY + 1 || i == PSD_DEVSTAT_EOS);
+        if (entry) ds[i] = i == PSD_DEVSTAT_ENTRY ? (int32_t)(uint32_t)set : i == PSD_DEVSTAT_EOS ? 0 : (int32_t)(uint32_t)(set >> 32);
+        else if (clear) ds[i] = 0;
+    }
+    if (counted && j == 0) n_left[b] = n_left_host[b] = __popcll(set);
+}
+
 __global__ void fill_i32_kernel(int32_t *p, int64_t n, int32_t v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -617,15 +636,22 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
         return rc;
     };
 
-    {
+    // Small batches without EOS stopping: control words travel as kernel arguments and counts come back through pinned memory.  The
+    // copies between the launches of an iteration, ten of 4 bytes a sequence, cost a launch each, 60 of 315 us at two layers of 64.
+    const bool direct = !eos_stop && B <= SeqSet::MAX;
+    bool cleared = false;
+    auto clear_counters = [&]() {
         const int64_t n = (int64_t)B * PSD_DEVSTAT_WORDS;
         hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, devstats, n, 0);
-    }
+        cleared = true;
+    };
+    if (!direct) clear_counters();
     enum { ENTER, RUN, DONE };
     std::vector<int> state(B, ENTER);
     std::vector<int64_t> invocations(B, 0);
     std::vector<int32_t> eos_pos(B, -1);
     std::vector<char> stopped(B, 0);
+    std::vector<char> counted(B, 0);       // the token count of the block is closed already (last iteration of a direct call)
     std::vector<char> have_tables(B, 0);   // single-forward loop: (top1, conf)[b] hold the accepted draft's verifier output
     for (int b = 0; b < B; ++b)
         if (advance && starts[b] >= N) state[b] = DONE;
@@ -642,13 +668,24 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
     // the sequences that leave their block: close its token count, then move on (or finish)
     auto leave_blocks = [&](const std::vector<int> &who, std::vector<char> &stopped) -> int32_t {
         if (who.empty()) return PSD_OK;
-        std::vector<char> mark(B, 0);
-        for (int b : who) mark[b] = 1;
-        CHECK(upload_flags([&](int b) { return mark[b] != 0; }));
-        launch_finish_counts(tokens, B, N, bs_seq, L, mask_id, policy->eos_stop, policy->eos_id, devstats, d_flags, st);
+        SeqSet set;
+        if (direct) {
+            bool any = false;
+            for (int b : who)
+                if (!counted[b]) {
+                    set.add(b);
+                    any = true;
+                }
+            if (any) launch_finish_export(tokens, B, N, bs_seq, L, mask_id, devstats, set, hstats, st);
+        } else {
+            std::vector<char> mark(B, 0);
+            for (int b : who) mark[b] = 1;
+            CHECK(upload_flags([&](int b) { return mark[b] != 0; }));
+            launch_finish_counts(tokens, B, N, bs_seq, L, mask_id, policy->eos_stop, policy->eos_id, devstats, d_flags, st);
+        }
         if (eos_stop) PSD_HIP(hipMemcpyAsync(hstats, devstats, sizeof(int32_t) * B * PSD_DEVSTAT_WORDS, hipMemcpyDeviceToHost, st));
         // (the staging buffer may be rewritten by the next upload: the copy of the flags must have been consumed)
-        PSD_HIP(hipStreamSynchronize(st));
+        if (!direct) PSD_HIP(hipStreamSynchronize(st));
         for (int b : who) {
             // an EOS token in the block it leaves ends the sequence (App. B.1), whatever is still masked in it
             const int32_t eos = eos_stop ? hstats[(int64_t)b * PSD_DEVSTAT_WORDS + PSD_DEVSTAT_EOS] : 0;
@@ -667,17 +704,34 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
         return PSD_OK;
     };
 
-    CHECK(upload_starts());
+    if (!direct) CHECK(upload_starts());
+    bool exported = false;   // hstats holds every sequence's final counters
     int iterations = 0, stalled = 0;
     while (true) {
         // sequences entering a block: count its masks; a block without masks is left at once
         bool entering = false;
         for (int b = 0; b < B; ++b) entering = entering || state[b] == ENTER;
         while (entering) {
-            CHECK(upload_starts());
-            CHECK(upload_flags([&](int b) { return state[b] == ENTER; }));
-            hipLaunchKernelGGL(count_masks_kernel, dim3(B), dim3(64), 0, st, tokens, N, bs_seq, L, mask_id, n_left, devstats, d_flags);
-            PSD_HIP(hipMemcpyAsync(hc, n_left, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+            if (direct) {
+                SeqSet who;
+                SeqStarts at;
+                for (int b = 0; b < B; ++b) {
+                    at.at[b] = std::min(starts[b], N - L);    // a finished sequence keeps its last block
+                    if (state[b] == ENTER) {
+                        who.add(b);
+                        counted[b] = 0;
+                    }
+                }
+                hipLaunchKernelGGL(enter_kernel, dim3(B), dim3(64), 0, st, tokens, N, at, who, L, mask_id, n_left, devstats, kv ? nullptr : d_starts, hc,
+                                   cleared ? 0 : 1);
+                cleared = true;
+                exported = false;
+            } else {
+                CHECK(upload_starts());
+                CHECK(upload_flags([&](int b) { return state[b] == ENTER; }));
+                hipLaunchKernelGGL(count_masks_kernel, dim3(B), dim3(64), 0, st, tokens, N, bs_seq, L, mask_id, n_left, devstats, d_flags);
+                PSD_HIP(hipMemcpyAsync(hc, n_left, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+            }
             PSD_HIP(hipStreamSynchronize(st));
             std::vector<int> empty;
             for (int b = 0; b < B; ++b) {
@@ -708,9 +762,12 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
             if (!have_tables[b]) fresh.push_back(b);
         const int S1 = (int)fresh.size();
         if (S1 > 0) {
-            for (int s = 0; s < S1; ++s) hrows[s] = fresh[s];
-            PSD_HIP(hipMemcpyAsync(rows, hrows, sizeof(int32_t) * S1, hipMemcpyHostToDevice, st));
-            CHECK(model_call(tokens, rows, S1, 1, bs_seq, top1, conf, st));
+            // (every sequence in order needs no list)
+            if (S1 < B) {
+                for (int s = 0; s < S1; ++s) hrows[s] = fresh[s];
+                PSD_HIP(hipMemcpyAsync(rows, hrows, sizeof(int32_t) * S1, hipMemcpyHostToDevice, st));
+            }
+            CHECK(model_call(tokens, S1 < B ? rows : nullptr, S1, 1, bs_seq, top1, conf, st));
             for (int b : fresh) invocations[b] += 1;
             const int32_t *only = nullptr;
             if (single_forward) {   // the others committed already, by the policy on their accepted draft's output
@@ -721,9 +778,9 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
             }
             launch_select_unmask(tokens, B, N, bs_seq, L, top1, conf, *policy, mask_id, nullptr, nullptr, n_left, devstats, only, st);
         }
-        launch_build_drafts(tokens, B, N, bs_seq, L, top1, conf, g, mask_id, sigma, m, drafts, st);
+        launch_build_drafts(tokens, B, N, bs_seq, L, top1, conf, g, mask_id, sigma, m, drafts, st, direct ? hc : nullptr);
         if (eos_stop) launch_eos_stop(tokens, B, N, bs_seq, L, policy->eos_id, n_left, m, devstats, st);
-        PSD_HIP(hipMemcpyAsync(hc, m, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+        if (!direct) PSD_HIP(hipMemcpyAsync(hc, m, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
         PSD_HIP(hipStreamSynchronize(st));
         std::vector<int> vset;
         for (int b : active)
@@ -731,19 +788,31 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
         if (!vset.empty()) {
             // stage 3: one batched forward over the K drafts of every sequence that still has masks
             const int S3 = (int)vset.size() * K;
-            for (size_t i = 0; i < vset.size(); ++i)
-                for (int k = 0; k < K; ++k) hrows[i * K + k] = vset[i] * K + k;
-            PSD_HIP(hipMemcpyAsync(rows, hrows, sizeof(int32_t) * S3, hipMemcpyHostToDevice, st));
-            CHECK(model_call(drafts, rows, S3, K, bs_draft, v_top1, v_conf, st));
+            if (S3 < B * K) {
+                for (size_t i = 0; i < vset.size(); ++i)
+                    for (int k = 0; k < K; ++k) hrows[i * K + k] = vset[i] * K + k;
+                PSD_HIP(hipMemcpyAsync(rows, hrows, sizeof(int32_t) * S3, hipMemcpyHostToDevice, st));
+            }
+            CHECK(model_call(drafts, S3 < B * K ? rows : nullptr, S3, K, bs_draft, v_top1, v_conf, st));
             for (int b : vset) invocations[b] += 1;
             launch_accept(tokens, drafts, B, N, bs_seq, L, sigma, m, g, *policy, mask_id, v_top1, v_conf, k_star, accepted,
-                          n_left, devstats, single_forward ? top1 : nullptr, single_forward ? conf : nullptr, st);
+                          n_left, devstats, single_forward ? top1 : nullptr, single_forward ? conf : nullptr, st, direct ? hc : nullptr);
             if (single_forward)
                 for (int b : vset) have_tables[b] = 1;
             if (eos_stop) launch_eos_stop(tokens, B, N, bs_seq, L, policy->eos_id, n_left, nullptr, devstats, st);
         }
         // who is done with the block: no masks left, or stopped on an EOS token (its mask counts were zeroed)
-        PSD_HIP(hipMemcpyAsync(hc, n_left, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+        if (!direct || vset.empty()) PSD_HIP(hipMemcpyAsync(hc, n_left, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+        // In the last iteration of the call every running sequence's count is closed, whether it leaves the block or the call does
+        if (direct && max_iterations > 0 && iterations >= max_iterations) {
+            SeqSet set;
+            for (int b : active) {
+                set.add(b);
+                counted[b] = 1;
+            }
+            launch_finish_export(tokens, B, N, bs_seq, L, mask_id, devstats, set, hstats, st);
+            exported = true;
+        }
         PSD_HIP(hipStreamSynchronize(st));
         std::vector<int> leaving;
         for (int b : active)
@@ -755,16 +824,26 @@ int32_t decode_impl(psd_handle *h, int32_t *tokens, int32_t B, int32_t N, int32_
     {
         std::vector<int> open;
         for (int b = 0; b < B; ++b)
-            if (state[b] == RUN) open.push_back(b);
-        if (!open.empty()) {
+            if (state[b] == RUN && !counted[b]) open.push_back(b);
+        if (direct) {
+            if (!cleared) clear_counters();
+            if (!exported || !open.empty()) {
+                SeqSet set;
+                for (int b : open) set.add(b);
+                launch_finish_export(tokens, B, N, bs_seq, L, mask_id, devstats, set, hstats, st);
+                PSD_HIP(hipStreamSynchronize(st));
+            }
+        } else if (!open.empty()) {
             std::vector<char> mark(B, 0);
             for (int b : open) mark[b] = 1;
             CHECK(upload_flags([&](int b) { return mark[b] != 0; }));
             launch_finish_counts(tokens, B, N, bs_seq, L, mask_id, policy->eos_stop, policy->eos_id, devstats, d_flags, st);
         }
     }
-    PSD_HIP(hipMemcpyAsync(hstats, devstats, sizeof(int32_t) * B * PSD_DEVSTAT_WORDS, hipMemcpyDeviceToHost, st));
-    PSD_HIP(hipStreamSynchronize(st));
+    if (!direct) {
+        PSD_HIP(hipMemcpyAsync(hstats, devstats, sizeof(int32_t) * B * PSD_DEVSTAT_WORDS, hipMemcpyDeviceToHost, st));
+        PSD_HIP(hipStreamSynchronize(st));
+    }
     for (int b = 0; b < B; ++b) {
         const int32_t *ds = hstats + (int64_t)b * PSD_DEVSTAT_WORDS;
         stats[b].invocations += invocations[b];

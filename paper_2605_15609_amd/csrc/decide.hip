@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WAVE *DRAFT_WAVES) void build_drafts_kernel(const i
                                                             int L, const int32_t *__restrict__ top1,
                                                             const float *__restrict__ conf, GraphArg g, int32_t mask_id,
                                                             int32_t *__restrict__ sigma, int32_t *__restrict__ m_out,
-                                                            int32_t *__restrict__ drafts) {
+                                                            int32_t *__restrict__ drafts, int32_t *__restrict__ m_host) {
     const int k = blockIdx.x;
     const int b = blockIdx.y;
     const int j = threadIdx.x;
@@ -111,7 +111,10 @@ __global__ __launch_bounds__(WAVE *DRAFT_WAVES) void build_drafts_kernel(const i
         if (live) s_pos[rank] = j;
         __builtin_amdgcn_wave_barrier();
         if (in) sigma[(int64_t)b * L + j] = (j < m) ? s_pos[j] : -1;
-        if (j == 0) m_out[b] = m;
+        if (j == 0) {
+            m_out[b] = m;
+            if (m_host) m_host[b] = m;
+        }
     }
 }
 
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(WAVE *ACCEPT_WAVES) void accept_kernel(
     int32_t *__restrict__ tokens, const int32_t *__restrict__ drafts, int N, BlockStart bs, int L, const int32_t *__restrict__ sigma,
     const int32_t *__restrict__ m_in, GraphArg g, psd_policy policy, int32_t mask_id, const int32_t *__restrict__ v_top1,
     const float *__restrict__ v_conf, int32_t *__restrict__ k_star_out, uint8_t *__restrict__ accepted_out, int32_t *__restrict__ n_left,
-    int32_t *__restrict__ devstats, int32_t *__restrict__ adopt_top1, float *__restrict__ adopt_conf) {
+    int32_t *__restrict__ devstats, int32_t *__restrict__ adopt_top1, float *__restrict__ adopt_conf, int32_t *__restrict__ n_left_host) {
     __shared__ int s_rank[WAVE];                               // block position -> rank in sigma, or -1
     __shared__ int32_t s_tok[PSD_MAX_NODES][WAVE];             // the drafts' blocks
     __shared__ int32_t s_top[PSD_MAX_NODES][WAVE];             // the verifier's predictions on them
@@ -143,6 +146,7 @@ __global__ __launch_bounds__(WAVE *ACCEPT_WAVES) void accept_kernel(
         if (wave > 0) return;
         if (j == 0) {
             if (k_star_out) k_star_out[b] = 0;
+            if (n_left_host) n_left_host[b] = n_left[b];
         }
         if (accepted_out && j < K) accepted_out[(int64_t)b * K + j] = (j == 0) ? 1 : 0;
         return;
@@ -223,6 +227,7 @@ __global__ __launch_bounds__(WAVE *ACCEPT_WAVES) void accept_kernel(
         const int depth = __popcll(s_S[k_star]);
         if (k_star_out) k_star_out[b] = k_star;
         if (n_left) n_left[b] = n_live - n_take;
+        if (n_left_host) n_left_host[b] = n_live - n_take;
         if (devstats) {
             int32_t *ds = devstats + (int64_t)b * PSD_DEVSTAT_WORDS;
             ds[PSD_DEVSTAT_DRAFT] += depth;
@@ -254,11 +259,9 @@ __global__ __launch_bounds__(WAVE) void eos_stop_kernel(const int32_t *__restric
 // block (when stopping on EOS is on) and the number of positions resolved since the block was entered at or before
 // it -- all resolved positions without an EOS -- are added to the sequence's counters.  The positions masked on
 // entry are in the counters as a 64-bit set.  only != NULL: just the sequences b with only[b] != 0.
-__global__ __launch_bounds__(WAVE) void finish_counts_kernel(const int32_t *__restrict__ tokens, int N, BlockStart bs, int L,
-                                                             int32_t mask_id, int32_t eos_stop, int32_t eos_id,
-                                                             int32_t *__restrict__ devstats, const int32_t *__restrict__ only) {
+__device__ __forceinline__ void finish_counts(const int32_t *__restrict__ tokens, int N, const BlockStart &bs, int L, int32_t mask_id, int32_t eos_stop,
+                                              int32_t eos_id, int32_t *__restrict__ devstats) {
     const int b = blockIdx.x, j = threadIdx.x;
-    if (only && only[b] == 0) return;
     const int block_start = bs.of_row(b);
     const int32_t tok = j < L ? tokens[(int64_t)b * N + block_start + j] : mask_id;
     const uint64_t hits = __ballot(eos_stop && j < L && tok == eos_id);
@@ -274,6 +277,21 @@ __global__ __launch_bounds__(WAVE) void finish_counts_kernel(const int32_t *__re
     }
 }
 
+__global__ __launch_bounds__(WAVE) void finish_counts_kernel(const int32_t *__restrict__ tokens, int N, BlockStart bs, int L,
+                                                             int32_t mask_id, int32_t eos_stop, int32_t eos_id,
+                                                             int32_t *__restrict__ devstats, const int32_t *__restrict__ only) {
+    if (only && only[blockIdx.x] == 0) return;
+    finish_counts(tokens, N, bs, L, mask_id, eos_stop, eos_id, devstats);
+}
+
+__global__ __launch_bounds__(WAVE) void finish_export_kernel(const int32_t *__restrict__ tokens, int N, BlockStart bs, int L, int32_t mask_id,
+                                                             int32_t *devstats, SeqSet who, int32_t *__restrict__ host_stats) {
+    if (who.has(blockIdx.x)) finish_counts(tokens, N, bs, L, mask_id, 0, 0, devstats);
+    __syncthreads();
+    const int64_t at = (int64_t)blockIdx.x * PSD_DEVSTAT_WORDS;
+    for (int i = threadIdx.x; i < PSD_DEVSTAT_WORDS; i += WAVE) host_stats[at + i] = devstats[at + i];
+}
+
 }   // namespace
 
 void launch_eos_stop(const int32_t *tokens, int B, int N, BlockStart block_start, int L, int32_t eos_id, int32_t *n_left, int32_t *m,
@@ -287,6 +305,11 @@ void launch_finish_counts(const int32_t *tokens, int B, int N, BlockStart block_
                        devstats, only);
 }
 
+void launch_finish_export(const int32_t *tokens, int B, int N, BlockStart block_start, int L, int32_t mask_id, int32_t *devstats, const SeqSet &who,
+                          int32_t *host_stats, hipStream_t st) {
+    hipLaunchKernelGGL(finish_export_kernel, dim3(B), dim3(WAVE), 0, st, tokens, N, block_start, L, mask_id, devstats, who, host_stats);
+}
+
 void launch_select_unmask(int32_t *tokens, int B, int N, BlockStart block_start, int L, const int32_t *top1, const float *conf,
                           psd_policy policy, int32_t mask_id, uint8_t *transfer_mask, int32_t *n_selected,
                           int32_t *n_left, int32_t *devstats, const int32_t *only, hipStream_t st) {
@@ -296,15 +319,15 @@ void launch_select_unmask(int32_t *tokens, int B, int N, BlockStart block_start,
 
 void launch_build_drafts(const int32_t *tokens, int B, int N, BlockStart block_start, int L, const int32_t *top1,
                          const float *conf, const GraphArg &g, int32_t mask_id, int32_t *sigma, int32_t *m,
-                         int32_t *drafts, hipStream_t st) {
+                         int32_t *drafts, hipStream_t st, int32_t *m_host) {
     hipLaunchKernelGGL(build_drafts_kernel, dim3(g.K, B), dim3(WAVE * DRAFT_WAVES), 0, st, tokens, N, block_start, L, top1, conf, g,
-                       mask_id, sigma, m, drafts);
+                       mask_id, sigma, m, drafts, m_host);
 }
 
 void launch_accept(int32_t *tokens, const int32_t *drafts, int B, int N, BlockStart block_start, int L, const int32_t *sigma,
                    const int32_t *m, const GraphArg &g, psd_policy policy, int32_t mask_id, const int32_t *v_top1,
                    const float *v_conf, int32_t *k_star, uint8_t *accepted, int32_t *n_left, int32_t *devstats,
-                   int32_t *adopt_top1, float *adopt_conf, hipStream_t st) {
+                   int32_t *adopt_top1, float *adopt_conf, hipStream_t st, int32_t *n_left_host) {
     hipLaunchKernelGGL(accept_kernel, dim3(B), dim3(WAVE * (g.K < ACCEPT_WAVES ? g.K : ACCEPT_WAVES)), 0, st, tokens, drafts, N, block_start, L, sigma, m, g, policy,
-                       mask_id, v_top1, v_conf, k_star, accepted, n_left, devstats, adopt_top1, adopt_conf);
+                       mask_id, v_top1, v_conf, k_star, accepted, n_left, devstats, adopt_top1, adopt_conf, n_left_host);
 }

@@ -109,6 +109,18 @@ struct BlockStart {
     __host__ __device__ int of_row(int64_t row) const { return per_seq ? per_seq[row / rows_per_seq] : common; }
 };
 
+// Which sequences of a small batch a kernel is for, and their block starts: kernel arguments, so that no copy to the device has to
+// come before the kernel
+struct SeqSet {
+    static constexpr int MAX = 128;
+    uint32_t bits[MAX / 32] = {};
+    void add(int b) { bits[b >> 5] |= 1u << (b & 31); }
+    __host__ __device__ bool has(int b) const { return (bits[b >> 5] >> (b & 31)) & 1u; }
+};
+struct SeqStarts {
+    int32_t at[SeqSet::MAX];
+};
+
 struct GraphArg {
     int32_t K;
     uint64_t rank_set[PSD_MAX_NODES];
@@ -128,6 +140,10 @@ inline void ensure_dynamic_lds(const void *kernel, int bytes, std::atomic<uint64
 void launch_eos_stop(const int32_t *tokens, int B, int N, BlockStart block_start, int L, int32_t eos_id, int32_t *n_left, int32_t *m,
                      int32_t *devstats, hipStream_t st);
 // only[b] != 0 selects the sequences to finish (NULL: all); their counters of resolved positions are ADDED to
+// (m_host, n_left_host, host_stats: pinned host memory that also receives the counts; a copy back costs a launch of its own)
+// the same as launch_finish_counts for the sequences of `who`, then every sequence's counters into host_stats
+void launch_finish_export(const int32_t *tokens, int B, int N, BlockStart block_start, int L, int32_t mask_id, int32_t *devstats, const SeqSet &who,
+                          int32_t *host_stats, hipStream_t st);
 void launch_finish_counts(const int32_t *tokens, int B, int N, BlockStart block_start, int L, int32_t mask_id, int32_t eos_stop,
                           int32_t eos_id, int32_t *devstats, const int32_t *only, hipStream_t st);
 // only[b] != 0 selects the sequences the policy is applied to (NULL: all); the others keep tokens and n_left
@@ -136,11 +152,11 @@ void launch_select_unmask(int32_t *tokens, int B, int N, BlockStart block_start,
                           int32_t *n_selected, int32_t *n_left, int32_t *devstats, const int32_t *only, hipStream_t st);
 void launch_build_drafts(const int32_t *tokens, int B, int N, BlockStart block_start, int L, const int32_t *top1,
                          const float *conf, const GraphArg &g, int32_t mask_id, int32_t *sigma, int32_t *m,
-                         int32_t *drafts, hipStream_t st);
+                         int32_t *drafts, hipStream_t st, int32_t *m_host = nullptr);
 void launch_accept(int32_t *tokens, const int32_t *drafts, int B, int N, BlockStart block_start, int L,
                    const int32_t *sigma, const int32_t *m, const GraphArg &g, psd_policy policy, int32_t mask_id,
                    const int32_t *v_top1, const float *v_conf, int32_t *k_star, uint8_t *accepted,
-                   int32_t *n_left, int32_t *devstats, int32_t *adopt_top1, float *adopt_conf, hipStream_t st);
+                   int32_t *n_left, int32_t *devstats, int32_t *adopt_top1, float *adopt_conf, hipStream_t st, int32_t *n_left_host = nullptr);
 // (adopt_top1 / adopt_conf [B, L], or NULL: receive the verifier output of the accepted draft k* of every sequence with m > 0)
 
 // ---------------------------------------------------------------- forward (forward.hip)

@@ -626,3 +626,42 @@ def test_psd_decode_block_with_one_block_start_per_sequence():
         assert (s[0].invocations, s[0].tokens) == (stats[b].invocations, stats[b].tokens) and s[0].tokens == L
         row = together[b].cpu().numpy()
         assert (row[starts[b]: starts[b] + L] != shape.mask_id).all() and (row[starts[b] + L:] == shape.mask_id).all()
+
+
+@pytest.mark.parametrize("max_iterations", [1, 2, 3, 0])
+def test_counters_do_not_depend_on_how_they_travel(max_iterations):
+    """Up to 128 sequences the loop's control words are kernel arguments and its counts come back through pinned memory, above that
+    both are copied.  A batch of 131 against the same sequences in two calls of 65 and 66: tokens, block starts and every
+    counter, call by call; some blocks arrive resolved, some sequences at their end, and a call ends in mid-block or as sequences
+    move on to the next one."""
+    import paper_2605_15609_amd as psd
+    shape = inp.cut_down(inp.WORKLOADS[4].shape, name="fp32-131", dtype="fp32", n_layers=1, d_model=32, n_heads=2, n_kv_heads=2, d_head=16,
+                         d_ffn=32, vocab=61, seed=77, logit_scale=12.0)
+    N, P, L, K, B = 24, 8, 8, 2, 131
+    host = inp.draw_model(shape, N)
+    model = psd.Model.from_host(host, DEV)
+    policy, graph = psd.Policy(0.5, 1, 0), psd.chain_graph(K)
+    rng = np.random.default_rng(5)
+    tokens = np.full((B, N), shape.mask_id, dtype=np.int32)
+    starts = [P + L * int(b) for b in rng.integers(0, 3, B)]          # the third one: at the end
+    for b in range(B):
+        tokens[b, :min(starts[b], N)] = rng.integers(0, shape.vocab - 1, min(starts[b], N))
+        if b % 7 == 0 and starts[b] < N:
+            tokens[b, starts[b]:starts[b] + L] = 5                    # resolved already
+        elif b % 3 == 0 and starts[b] < N:
+            tokens[b, starts[b]:starts[b] + L - 1 - b % 2] = 6        # one or two masks left
+    whole, parts = _dev(tokens), [_dev(tokens[:65]), _dev(tokens[65:])]
+    ws, ps = list(starts), [list(starts[:65]), list(starts[65:])]
+
+    def fields(s):
+        return (s.invocations, s.tokens_policy, s.tokens_draft, s.tokens_postverify, s.tokens_counted, tuple(s.depth_hist))
+
+    for _ in range(4 if max_iterations else 1):
+        stats, ws, done = psd.psd_decode(model, whole, ws, L, policy, graph, max_iterations=max_iterations)
+        got = []
+        for i in range(2):
+            st, ps[i], _ = psd.psd_decode(model, parts[i], ps[i], L, policy, graph, max_iterations=max_iterations)
+            got += st
+        assert ws == ps[0] + ps[1]
+        assert (whole.cpu() == torch.cat([p.cpu() for p in parts])).all()
+        assert [fields(s) for s in stats] == [fields(s) for s in got]
