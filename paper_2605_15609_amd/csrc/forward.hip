@@ -111,7 +111,7 @@ struct Dispatch<bf16_t> {
         }
         return pend;
     }
-    // The QKV projection of [M = S * N, d] rows with wq | wk | wv as one matrix, rotary and the V transpose in its
+    // The QKV projection of [M = S * N, d] rows with wq | wk | wv as one matrix, rotary and (kv.vT) the V transpose in its
     // epilogue; false (nothing launched) when the matrix-core attention will not run on its output, the shape has no
     // tile that holds whole heads, or a debug switch (plain_mask bit 3) asks for the two-pass form.
     static bool qkv_fused(psd_handle *h, const bf16_t *A, const void *W, int64_t M, int N, int pos0, int H, int Hkv, int dh,
@@ -119,7 +119,7 @@ struct Dispatch<bf16_t> {
         if ((h->plain_mask & (1 | 2 | 8)) || (block_len > 0 && block_len < N)) return false;
         if (h->probe.enabled && (h->probe.epi == EPI_STORE || h->probe.epi == EPI_BIAS)) return false;   // that probe times the plain store
         const int d = h->cfg.d_model, qkv_w = (H + 2 * Hkv) * dh;
-        const int tile = gemm_bf16_qkv_tile(M, qkv_w, dh, (H + Hkv) * dh, N);
+        const int tile = gemm_bf16_qkv_tile(M, qkv_w, dh, (H + Hkv) * dh, kv.vT ? N : 16);
         if (tile < 0) return false;
         launch_gemm_bf16_qkv(A, (const bf16_t *)W, M, qkv_w, d, d, d, bias, qkv, ld_qkv, dh, (H + Hkv) * dh, N, pos0, h->rope_cos,
                              h->rope_sin, kv, tile, st, next);
@@ -145,16 +145,16 @@ struct Dispatch<bf16_t> {
     // Rotary on q and k (row i of a sequence sits at position pos0 + i), then attention.
     // pre: KV prefix that every own row sees; block_len > 0: context-causal blocks among the own rows (only the
     // plain kernel masks; the product path of that attention mode keeps finished blocks in the prefix instead).
-    // rotated: qkv_fused produced qkv and vT, only the attention is left.
+    // rotated: qkv_fused produced qkv (and vT), only the attention is left.
     // Lengths that are no multiple of 8 keep fp32 probabilities and the plain kernel's order of sums; whole sequences of them run on
     // the fp32 matrix instructions with the same bits.
     // Returns whether vT holds the values.
     static bool rope_attention(psd_handle *h, bf16_t *qkv, int ld_qkv, bf16_t *vT, int S, int N, int pos0, int H, int Hkv, int dh,
                                bf16_t *out, const KvPrefix &pre, int block_len, hipStream_t st, bool rotated = false) {
-        if (rotated) {
+        if (rotated && N % 8 == 0) {
             launch_attention_bf16(qkv, ld_qkv, vT, S, N, H, Hkv, dh, out, pre, st);
         } else if ((h->plain_mask & 2) || (N % 8) != 0 || (block_len > 0 && block_len < N)) {
-            launch_rope<bf16_t>(qkv, ld_qkv, (int64_t)S * N, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, st);
+            if (!rotated) launch_rope<bf16_t>(qkv, ld_qkv, (int64_t)S * N, N, pos0, H, Hkv, dh, h->rope_cos, h->rope_sin, st);
             const bool whole = !(h->plain_mask & 2) && pre.len == 0 && !(block_len > 0 && block_len < N);
             if (!whole || !launch_attention_ordered(qkv, ld_qkv, S, N, H, Hkv, dh, out, st))
                 launch_plain_attention<bf16_t>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
@@ -214,7 +214,7 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         bool rotated = false;
         if (fused) {
             KvDest own;
-            own.vT = (bf16_t *)vT;
+            own.vT = N % 8 == 0 ? (bf16_t *)vT : nullptr;   // (the attention of the other lengths reads V row-major)
             own.ld_vt = (int)vt_row_stride(N);
             own.vt_seq = (int64_t)Hkv * dh * own.ld_vt;
             rotated = ld_qkv == qkv_w &&

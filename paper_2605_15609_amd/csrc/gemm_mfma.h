@@ -75,9 +75,9 @@ struct Top1Args {
 struct QkvArgs {
     int d_head;           // 64 or 128; every tile holds whole heads (BN % d_head == 0)
     int v_start;          // columns [0, v_start) are q and k heads, [v_start, Nout) V heads; a multiple of BN
-    int N, pos0;          // rows per sequence (a multiple of 16) and the rotary position of a sequence's first row
+    int N, pos0;          // rows per sequence (a multiple of 16 if vT) and the rotary position of a sequence's first row
     const float *cos_t, *sin_t;   // [positions, d_head / 2]
-    bf16_t *vT;           // value column c, key i of sequence s at vT[s * vt_seq + c * ld_vt + slot(i)]
+    bf16_t *vT;           // value column c, key i of sequence s at vT[s * vt_seq + c * ld_vt + slot(i)]; NULL: values row-major in `out`
     int ld_vt;
     int64_t vt_seq;
     // k heads (columns [k_start, v_start)): k_dst = NULL: into `out` next to q; otherwise into a KV cache, row i of sequence s
@@ -408,8 +408,9 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
         constexpr int LDT = BM * 2 + 8;    // bytes per column of the column-major one
         static_assert(BM * LDC <= (NSA * BM + NSB * BN) * ROW_BYTES && BN * LDT <= (NSA * BM + NSB * BN) * ROW_BYTES, "staging tile fits the rings");
         __syncthreads();                   // every wavefront is done with the operand rings
-        if (n0 < qa.v_start) {
+        if (n0 < qa.v_start || !qa.vT) {
             // ---- q / k heads: stage row-major, rotate pairs (j, j + d_head / 2), store 16 bytes per access
+            // (V heads whose reader wants them row-major: the same without the rotation)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
                 const int col = wn * WTN + j * MI + 4 * lq;
@@ -424,6 +425,15 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
                 }
             }
             __syncthreads();
+            if (n0 >= qa.v_start) {
+                for (int u = tid; u < BM * (BN / 8); u += NT) {
+                    const int c8 = u % (BN / 8), row = u / (BN / 8);
+                    const int m = m0 + row, n = n0 + c8 * 8;
+                    if (m < M && n < Nout)
+                        *reinterpret_cast<uint4 *>(out + (int64_t)m * ldo + n) = *reinterpret_cast<const uint4 *>(lds + row * LDC + c8 * 16);
+                }
+                return;
+            }
             const int half = qa.d_head >> 1, groups = half >> 3, heads = BN / qa.d_head;
             const int units = BM * heads * groups;   // 8 pair indices of one head of one row each
             for (int u = tid; u < units; u += NT) {

@@ -221,6 +221,44 @@ def test_rotary_and_value_transpose_in_the_qkv_epilogue_change_no_bit(name, N, S
     assert err < 2e-2
 
 
+@pytest.mark.parametrize("name,N,S", [("small-2l", 197, 5), ("small-2l", 77, 11), ("small-2l", 1285, 1), ("gqa-bias", 331, 3), ("gqa-bias", 133, 16)])
+def test_rotary_in_the_qkv_epilogue_of_odd_lengths_changes_no_bit(name, N, S):
+    """Lengths that are no multiple of 8: the projection rotates q and k in its epilogue and leaves V row-major, for the attention that
+    reads it so; bit 3 asks for the plain store and the separate rotary launch.  Sequences begin anywhere inside a tile."""
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    shape = SHAPES[name][0]
+    L = 16
+    bs = N - 2 * L
+    host, model = make_models(shape, N)
+    d = to_dev(np.stack([_state(shape, N, bs, L, 140 + s, (3 * s) % L) for s in range(S)]))
+    out = {}
+    for mask in (0, 8):
+        model.set_plain(mask)
+        out[mask] = psd.psd_forward_logits(model, d, bs, L).cpu().numpy()
+    model.set_plain(0)
+    assert np.isfinite(out[0]).all() and (out[0] == out[8]).all()
+
+
+@pytest.mark.parametrize("d_model", [128, 320, 512, 576])
+@pytest.mark.parametrize("N,S", [(40, 1), (72, 3)])
+def test_norms_of_narrow_models(d_model, N, S):
+    """Rows of up to 512 values are normed by a wavefront each, four to a workgroup (40 and 216 rows, a batch of 3 and the last layer's
+    48 block rows), wider ones by a workgroup: logits against the oracle, and a sequence does not depend on its neighbours."""
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    shape = inp.cut_down(inp.WORKLOADS[2].shape, n_layers=2, d_model=d_model, n_heads=d_model // 64, n_kv_heads=d_model // 64, d_ffn=192, vocab=997,
+                         seed=91)
+    L = 16
+    bs = N - 2 * L
+    host, model = make_models(shape, N)
+    states = np.stack([_state(shape, N, bs, L, 160 + s, s) for s in range(S)])
+    z = psd.psd_forward_logits(model, to_dev(states), bs, L).cpu().numpy().reshape(S, L, -1)
+    for s in range(S):
+        assert float(np.abs(z[s] - orc.block_logits(host, states[s], bs, L)).max()) < 2e-2
+        assert (psd.psd_forward_logits(model, to_dev(states[s: s + 1]), bs, L).cpu().numpy().reshape(L, -1) == z[s]).all()
+
+
 @pytest.mark.parametrize("name,N,S", [("small-2l", 96, 5), ("gqa-bias", 272, 3)])
 def test_qkv_epilogue_on_every_tile_configuration(name, N, S):
     """The same comparison with every workgroup tile forced in turn (the forced tile serves all contractions of both runs):
