@@ -486,7 +486,10 @@ int32_t run_head_confidence(psd_handle *h, const int32_t *tokens, const int32_t 
     if (c.dtype == PSD_DTYPE_BF16 && !(h->plain_mask & 4) && h->lm_head_packed && head_stream_supported(rows, c.d_model)) {
         // y was already written in fragment order by the final norm; the merge writes (top1, conf) directly
         HeadFinish fin = {tokens, seq_rows, out_rows, S, N, block_start, L, top1, conf};
-        launch_head_stream_finish_bf16((const bf16_t *)(ws + p.off_ypack), (const bf16_t *)h->lm_head_packed, rows, c.vocab,
+        if (head_few_workgroups(c.vocab))
+            launch_head_tiled_finish_bf16((const bf16_t *)(ws + p.off_y), (const bf16_t *)h->lm_head, rows, c.vocab, c.d_model, c.logit_scale, c.mask_id,
+                                          ws + p.off_part, fin, st);
+        else launch_head_stream_finish_bf16((const bf16_t *)(ws + p.off_ypack), (const bf16_t *)h->lm_head_packed, rows, c.vocab,
                                        c.d_model, c.logit_scale, c.mask_id, ws + p.off_part, fin, st);
         PSD_HIP(hipGetLastError());
         return PSD_OK;

@@ -280,6 +280,30 @@ void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_pack
                        mask_id, V);
 }
 
+// The streaming kernel deals 512 vocabulary ids a workgroup; a vocabulary that gives it less than one workgroup for every other CU is spread
+// over tiles of 128 ids instead (V = 32 000, K = 512: 128 rows 25.2 -> 13.4 us, 32 rows 13.0 -> 9.8)
+bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
+
+void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
+                                   const HeadFinish &fin, hipStream_t st) {
+    const int slabs = (V + SLAB_SMALL - 1) / SLAB_SMALL;
+    const int64_t stride = align_up((int64_t)((V + 31) / 32) * rows * 4, 256);
+    Top1Args t1;
+    t1.scale = scale;
+    t1.mask_id = mask_id;
+    t1.pmax = (float *)partials;
+    t1.psum = (float *)((char *)partials + stride);
+    t1.parg = (int32_t *)((char *)partials + 2 * stride);
+    t1.cols_total = rows;
+    if (rows <= 32)
+        launch_cfg<SLAB_SMALL, 32, 4, 1, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+    else if (rows <= 64)
+        launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+    else
+        launch_cfg<SLAB_SMALL, 128, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+    hipLaunchKernelGGL(head_merge_finish_kernel, dim3(rows), dim3(256), 0, st, t1.pmax, t1.psum, t1.parg, slabs, rows, fin, mask_id, V);
+}
+
 void launch_head_confidence_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id,
                                  void *partials, float *row_sum, int32_t *row_arg, hipStream_t st) {
     const int slab = slab_rows(rows);

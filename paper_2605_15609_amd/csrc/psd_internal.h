@@ -307,10 +307,11 @@ struct Warm {
     int64_t stride[ITEMS] = {};
     int rows[ITEMS] = {}, kb[ITEMS] = {};
     int n = 0, wgs = 0;
-    // a bf16 matrix [n_rows, cols] with row stride ld, whole KB of its rows (16-byte accesses)
+    // a bf16 matrix [n_rows, cols] with row stride ld, whole KB of its rows (16-byte accesses); not the matrices of models whose layers
+    // stay in the cache by themselves (below 8 MB)
     void add(const void *w, int64_t n_rows, int64_t cols, int64_t ld) {
         const int64_t use = cols * 2 / 1024;
-        if (n == ITEMS || use < 1 || (reinterpret_cast<uintptr_t>(w) & 15) || ld % 8 || n_rows * use > (1 << 24)) return;
+        if (n == ITEMS || n_rows * use < 8192 || (reinterpret_cast<uintptr_t>(w) & 15) || ld % 8 || n_rows * use > (1 << 24)) return;
         p[n] = (const char *)w;
         stride[n] = ld * 2;
         rows[n] = (int)n_rows;
@@ -402,6 +403,9 @@ struct HeadFinish {
     int32_t *top1;
     float *conf;
 };
+bool head_few_workgroups(int V);
+void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
+                                   const HeadFinish &fin, hipStream_t st);
 void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_packed, int rows, int V, int d, float scale,
                                     int mask_id, void *partials, const HeadFinish &fin, hipStream_t st);
 void launch_head_confidence_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id,
