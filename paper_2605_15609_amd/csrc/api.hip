@@ -1241,6 +1241,14 @@ int32_t psd_debug_gemm_plan(int64_t M, int32_t Nout, int32_t Kin, int32_t epilog
     return gemm_bf16_kernel(M, Nout, Kin, epilogue, nullptr, nullptr, nullptr, Nout);
 }
 
+int32_t psd_debug_gemm_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int64_t *rows, int64_t *cols) {
+    if (M < 1 || Nout < 1 || Kin < 1 || epilogue < 0 || epilogue > 3 || !rows || !cols) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    const SplitPlan p = gemm_bf16_plan(M, Nout, epilogue, Kin);
+    *rows = p.rows;
+    *cols = p.cols;
+    return PSD_OK;
+}
+
 int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq) {
     if (M < 1 || Nout < 1 || Kin < 1 || rows_per_seq < 1) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
     const int tile = gemm_bf16_qkv_tile(M, Nout, d_head, v_start, rows_per_seq);

@@ -71,14 +71,6 @@ Warm spare_reads(Warm next, int tile, int64_t M, int64_t cols, int Kin) {
     return next;
 }
 
-template <int EPI>
-void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nout, int Kin, int lda, int ldw,
-              const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st, const Warm &next) {
-    const int tile = gemm_bf16_tile(M, Nout, EPI, Kin);
-    launch_tile<EPI>(tile, A, W, W2, M, Nout, Kin, lda, ldw, bias, out, resid, ldo, Top1Args(), st, 1, (float *)nullptr, QkvArgs(),
-                     spare_reads(next, tile, M, EPI == EPI_SWIGLU ? 2 * (int64_t)Nout : Nout, Kin));
-}
-
 }   // namespace
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -104,7 +96,7 @@ const char *gemm_bf16_tile_name(int tile) {
 // all tiles over the layer shapes of the benchmark configurations, 160 - 12 288 rows, cold weights: the tile chosen is within 1 %
 // of the fastest on average, within 10 % everywhere but for 640 rows of the residual contractions (25 %).
 static double tile_time(const TileCfg &t, int64_t M, int64_t cols, int Kin, int epi) {
-    const int64_t n = ((M + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn), whole = n / 256;
+    const unsigned n = (((unsigned)M + t.bm - 1) / t.bm) * (((unsigned)cols + t.bn - 1) / t.bn), whole = n / 256;   // (32 bits, as the grid)
     const double part = (double)(n % 256) / 256, area = t.bm * t.bn / 65536.0, least = area >= 0.375 ? 0.75 : 0.8;
     const double stages = (Kin / mfma::BK) * t.stage, ends = area * (epi == EPI_RESIDUAL ? 20 : 6.5) + 0.7;
     return 1.5 + stages * (whole + (part > 0 ? least + (1 - least) * part : 0)) + ends * (whole + (part > 0));
@@ -135,6 +127,78 @@ int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin) {
     // SwiGLU reads two weight operands against one activation tile, half of the tile's columns each
     return fastest_tile(M, epi == EPI_SWIGLU ? 2 * (int64_t)Nout : Nout, epi == EPI_RESIDUAL && Kin ? Kin : kStoreK, epi, [](const TileCfg &) { return true; });
 }
+
+// A partial last round costs most of a whole one.  A contraction of some rounds may run as two launches instead: rows (or columns) that
+// come out as whole rounds of one of the two largest tiles, and the others in the tiles that suit them.  Looked for from 1000 rows on
+// (below, idle CUs read weights ahead: the 7B cached batch, 768 rows, is level), where a launch takes 50 us or more (the search
+// takes some 5 us of the host's time) and up to 16 rounds; taken where the model, which adds 1.5 us for the gap, says 2.5 %.  8B
+// ragged steps (6684 and 1671 rows) 125.7 -> 122.1 ms, 7B iteration (6144 and 1024) 78.3 -> 77.4.
+SplitPlan gemm_bf16_plan(int64_t M, int Nout, int epi, int Kin) {
+    SplitPlan best;
+    best.tile = gemm_bf16_tile(M, Nout, epi, Kin);
+    if (g_force_tile >= 0 || M < 1000 || (double)M * Nout * Kin < 3e10) return best;
+    const int dual = epi == EPI_SWIGLU ? 2 : 1, K = epi == EPI_RESIDUAL && Kin ? Kin : kStoreK;
+    const int64_t cols = (int64_t)Nout * dual;
+    const auto any = [](const TileCfg &) { return true; };
+    double least = tile_time(kTiles[best.tile], M, cols, K, epi) * 0.975 - 1.5;
+    for (int t : {0, 1}) {
+        const TileCfg &c = kTiles[t];
+        const int64_t tm = (M + c.bm - 1) / c.bm, tn = (cols + c.bn - 1) / c.bn;
+        if (tm * tn > 16 * 256) continue;
+        for (int64_t r = 1; r * 256 < tm * tn; ++r) {
+            const int64_t m0 = r * 256 / tn * c.bm, c0 = r * 256 / tm * c.bn;
+            if (m0 > 0 && m0 < M) {
+                const int rest = fastest_tile(M - m0, cols, K, epi, any);
+                const double time = tile_time(c, m0, cols, K, epi) + tile_time(kTiles[rest], M - m0, cols, K, epi);
+                if (time < least) {
+                    least = time;
+                    best.tile = t;
+                    best.rows = m0;
+                    best.cols = 0;
+                    best.rest = rest;
+                }
+            }
+            if (c0 > 0 && c0 < cols) {
+                const int rest = fastest_tile(M, cols - c0, K, epi, any);
+                const double time = tile_time(c, M, c0, K, epi) + tile_time(kTiles[rest], M, cols - c0, K, epi);
+                if (time < least) {
+                    least = time;
+                    best.tile = t;
+                    best.rows = 0;
+                    best.cols = c0 / dual;
+                    best.rest = rest;
+                }
+            }
+        }
+    }
+    return best;
+}
+
+namespace {
+
+template <int EPI>
+void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nout, int Kin, int lda, int ldw,
+              const float *bias, bf16_t *out, float *resid, int ldo, hipStream_t st, const Warm &next) {
+    const SplitPlan p = gemm_bf16_plan(M, Nout, EPI, Kin);
+    // rows [m0, m0 + rows) and output columns [c0, c0 + cols) on `tile`
+    auto part = [&](int tile, int64_t m0, int rows, int c0, int cols, const Warm &ahead) {
+        const int64_t o = m0 * ldo + c0, w = (int64_t)c0 * ldw;
+        launch_tile<EPI>(tile, A + m0 * lda, W + w, W2 ? W2 + w : W2, rows, cols, Kin, lda, ldw, bias ? bias + c0 : bias, out ? out + o : out,
+                         resid ? resid + o : resid, ldo, Top1Args(), st, 1, (float *)nullptr, QkvArgs(),
+                         spare_reads(ahead, tile, rows, EPI == EPI_SWIGLU ? 2 * (int64_t)cols : cols, Kin));
+    };
+    if (p.rows) {
+        part(p.tile, 0, (int)p.rows, 0, Nout, Warm());
+        part(p.rest, p.rows, M - (int)p.rows, 0, Nout, next);
+    } else if (p.cols) {
+        part(p.tile, 0, M, 0, (int)p.cols, Warm());
+        part(p.rest, 0, M, (int)p.cols, Nout - (int)p.cols, next);
+    } else {
+        part(p.tile, 0, M, 0, Nout, next);
+    }
+}
+
+}   // namespace
 
 // A residual contraction over at most 128 rows is cut along K: part 0 adds into resid, the others store partial sums that the next
 // reader of resid adds in order.  The parts are those the streaming kernel plans for 128 rows, whatever the number of rows: a

@@ -323,6 +323,12 @@ struct Warm {
 // (workgroup tile, LDS ring depths), 0 <= i < gemm_bf16_tile_count()
 int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin = 0);   // Kin = 0: not known (matters for residual contractions only)
 int gemm_bf16_tile_count();
+// a contraction as one launch (rows = cols = 0) or as two: its first rows, or its first output columns, on `tile`, the others on `rest`
+struct SplitPlan {
+    int tile = 0, rest = 0;
+    int64_t rows = 0, cols = 0;
+};
+SplitPlan gemm_bf16_plan(int64_t M, int Nout, int epi, int Kin);
 // what launch_gemm_bf16 runs: such an index, or gemm_bf16_tile_count() for the streaming kernel of few rows
 int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo);
 // QKV projection that also applies the rotary embedding to the q / k heads and stores V transposed into vT (what

@@ -109,6 +109,37 @@ def test_gemm_every_tile_configuration(epi):
         lib.psd_debug_force_gemm_tile(-1)
 
 
+@pytest.mark.parametrize("epi,M,N,K", [(2, 5000, 4032, 3072), (2, 6143, 3584, 6144), (3, 1037, 18944, 2048), (3, 1021, 19008, 2048), (3, 6684, 12288, 1024), (1, 5001, 12288, 2048)])
+def test_contraction_in_two_launches_changes_no_bit(epi, M, N, K):
+    """Contractions whose last round of tiles is partial run as two launches, cut along the rows or the output columns.  Against one
+    launch on one tile (forced), bit for bit, with rows and columns that no tile divides."""
+    import ctypes as C
+    from paper_2605_15609_amd import binding as B
+    lib = B.load_library()
+    rows, cols = C.c_int64(), C.c_int64()
+    assert lib.psd_debug_gemm_cut(M, N, K, epi, C.byref(rows), C.byref(cols)) == 0
+    assert 0 < rows.value < M or 0 < cols.value < N, "one launch"
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + N)
+    def draw(*s, std=1.0):
+        return torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0.0, std, generator=g)
+    A, W, W2 = draw(M, K), draw(N, K, std=0.05), draw(N, K, std=0.05) if epi == 3 else None
+    bias = torch.empty(N, device=DEV).normal_(generator=g) if epi == 1 else None
+    resid = torch.empty(M, N, device=DEV).normal_(generator=g) if epi == 2 else None
+    got = []
+    try:
+        for tile in (-1, 5):
+            lib.psd_debug_force_gemm_tile(tile)
+            if epi == 2:
+                got.append(resid.clone())
+                B.kernel_gemm_bf16(A, W, epi, resid=got[-1])
+            else:
+                got.append(B.kernel_gemm_bf16(A, W, epi, W2=W2, bias=bias))
+    finally:
+        lib.psd_debug_force_gemm_tile(-1)
+    assert torch.equal(got[0], got[1])
+
+
 SPLITK_CASES = [("c3-block-down", 128, 4096, 12288, (0, 8)), ("c3-block-o", 128, 4096, 4096, (0, 8)),
                 ("c3-stage1-block-down", 32, 4096, 12288, (0, 4)), ("c4-block-down", 192, 3584, 18944, (0, 2, 4)),
                 ("c4-block-o", 96, 3584, 3584, (0,)), ("ragged", 77, 832, 1536, (1, 2, 3, 4, 6, 8))]
