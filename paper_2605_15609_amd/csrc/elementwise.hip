@@ -209,26 +209,28 @@ __global__ __launch_bounds__(256) void rope_bf16_vec_kernel(bf16_t *__restrict__
 }   // namespace
 
 namespace {
-// dst[r, :] = src[(r / L) * N + block_start + r % L, :]: the block rows of every sequence, packed
-template <typename T>
-__global__ __launch_bounds__(256) void gather_block_rows_kernel(const T *__restrict__ src, T *__restrict__ dst, int width, int N,
-                                                                BlockStart block_start, int L,
-                                                                const int32_t *__restrict__ seq_rows) {
+// dst[r, :] = src[(r / L) * N + block_start + r % L, :] for two matrices at once: the block rows of every sequence, packed
+template <typename T1, typename T2>
+__global__ __launch_bounds__(256) void gather_block_rows_kernel(const T1 *__restrict__ src1, T1 *__restrict__ dst1, int width1,
+                                                                const T2 *__restrict__ src2, T2 *__restrict__ dst2, int width2, int N,
+                                                                BlockStart block_start, int L, const int32_t *__restrict__ seq_rows) {
     const int64_t r = blockIdx.x;
-    const T *s = src + ((r / L) * N + block_start.of_row(seq_rows ? seq_rows[r / L] : r / L) + (r % L)) * width;
-    T *d = dst + r * width;
-    for (int c = threadIdx.x; c < width; c += blockDim.x) d[c] = s[c];
+    const int64_t from = (r / L) * N + block_start.of_row(seq_rows ? seq_rows[r / L] : r / L) + (r % L);
+    for (int c = threadIdx.x; c < width1; c += blockDim.x) dst1[r * width1 + c] = src1[from * width1 + c];
+    for (int c = threadIdx.x; c < width2; c += blockDim.x) dst2[r * width2 + c] = src2[from * width2 + c];
 }
 }   // namespace
 
 template <typename T>
-void launch_gather_block_rows(const T *src, T *dst, int width, const int32_t *seq_rows, int S, int N, BlockStart block_start, int L,
-                              hipStream_t st) {
-    hipLaunchKernelGGL(gather_block_rows_kernel<T>, dim3((unsigned)(S * L)), dim3(256), 0, st, src, dst, width, N, block_start, L,
-                       seq_rows);
+void launch_gather_block_rows(const float *src1, float *dst1, int width1, const T *src2, T *dst2, int width2, const int32_t *seq_rows, int S, int N,
+                              BlockStart block_start, int L, hipStream_t st) {
+    hipLaunchKernelGGL((gather_block_rows_kernel<float, T>), dim3((unsigned)(S * L)), dim3(256), 0, st, src1, dst1, width1, src2, dst2, width2, N,
+                       block_start, L, seq_rows);
 }
-template void launch_gather_block_rows<float>(const float *, float *, int, const int32_t *, int, int, BlockStart, int, hipStream_t);
-template void launch_gather_block_rows<bf16_t>(const bf16_t *, bf16_t *, int, const int32_t *, int, int, BlockStart, int, hipStream_t);
+template void launch_gather_block_rows<float>(const float *, float *, int, const float *, float *, int, const int32_t *, int, int, BlockStart, int,
+                                              hipStream_t);
+template void launch_gather_block_rows<bf16_t>(const float *, float *, int, const bf16_t *, bf16_t *, int, const int32_t *, int, int, BlockStart, int,
+                                               hipStream_t);
 
 template <typename T>
 void launch_embed(const int32_t *tokens, const int32_t *seq_rows, int S, int N, const T *emb, int vocab, int d, float *h,

@@ -255,8 +255,7 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
             hs = (float *)(ws + p.off_hc);
             os = (T *)(ws + p.off_oc);
             nrow = (int64_t)S * L;
-            launch_gather_block_rows<float>(hbuf, hs, d, seq_rows, S, N, block_start, L, st);
-            launch_gather_block_rows<T>(o, os, H * dh, seq_rows, S, N, block_start, L, st);
+            launch_gather_block_rows<T>(hbuf, hs, d, o, os, H * dh, seq_rows, S, N, block_start, L, st);
             final_in = hs;
         }
         pend = Dispatch<T>::gemm(h, os, H * dh, lw.wo, nullptr, H * dh, nrow, d, H * dh, EPI_RESIDUAL, nullptr, nullptr, hs, d, ksplit, st);

@@ -262,10 +262,10 @@ template <typename T>
 void launch_rmsnorm_block(float *h, const int32_t *seq_rows, int S, int N, BlockStart block_start, int L, int d, const float *gain,
                           float eps, T *out, T *packed /* fragment-order copy, may be NULL */, PendingSums pend,
                           hipStream_t st);
-// dst [S*L, width] <- the L block rows of each of the S sequences of src [S*N, width]
+// dst [S*L, width] <- the L block rows of each of the S sequences of src [S*N, width], two matrices in one launch
 template <typename T>
-void launch_gather_block_rows(const T *src, T *dst, int width, const int32_t *seq_rows, int S, int N, BlockStart block_start, int L,
-                              hipStream_t st);
+void launch_gather_block_rows(const float *src1, float *dst1, int width1, const T *src2, T *dst2, int width2, const int32_t *seq_rows, int S, int N,
+                              BlockStart block_start, int L, hipStream_t st);
 template <typename T>
 void launch_rope(T *qkv, int ld /* row stride */, int64_t tokens, int N, int pos0 /* position of row 0 of each sequence */, int n_heads, int n_kv_heads, int d_head, const float *cos_t,
                  const float *sin_t, hipStream_t st);
