@@ -338,7 +338,8 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
             sb = nb;
         }
     }
-    // no DMA may outlive the loop, and the last MFMA results may be read
+    // No DMA may outlive the loop, and an MFMA's result may be read 8 wait states after its issue only, which the compiler does not know of
+    // the asm lines.  (Copies that it places in front of this wait are checked in a listing by a test.)
     asm volatile("s_waitcnt vmcnt(0)\n\ts_nop 15\n\ts_nop 15" ::: "memory");
 #pragma unroll
     for (int i = 0; i < TM; ++i)

@@ -2,7 +2,7 @@
 //
 // The vocabulary is streamed once: W_lm [V, d] is the ROW operand of the MFMA kernel, the
 // hidden rows y [rows, d] the column operand, so a lane holds 16 vocabulary entries of one
-// hidden row per 32x32 tile and reduces them in registers.  Every workgroup owns a slab of
+// hidden row per 32x32 tile (4 per 16x16 tile) and reduces them in registers.  Every workgroup owns a slab of
 // 256 (or 128) vocabulary ids for a tile of hidden rows and emits one (max, argmax, sum-exp)
 // triple per row; a second tiny kernel merges the slabs in ascending id order, so ties keep
 // the lowest token id and the result does not depend on scheduling.  Full logits never
@@ -281,7 +281,8 @@ void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_pack
 }
 
 // The streaming kernel deals 512 vocabulary ids a workgroup; a vocabulary that gives it less than one workgroup for every other CU is spread
-// over tiles of 128 ids instead (V = 32 000, K = 512: 128 rows 25.2 -> 13.4 us, 32 rows 13.0 -> 9.8)
+// over tiles of 128 ids instead (V = 32 000, K = 512: 128 rows 25.2 -> 13.4 us, 32 rows 13.0 -> 9.8).  Two wavefronts share the ids of a
+// tile whatever its width, so the exponentials of a row are added in one order for every number of rows.
 bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
 
 void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
@@ -296,7 +297,7 @@ void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, i
     t1.parg = (int32_t *)((char *)partials + 2 * stride);
     t1.cols_total = rows;
     if (rows <= 32)
-        launch_cfg<SLAB_SMALL, 32, 4, 1, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        launch_cfg<SLAB_SMALL, 32, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else if (rows <= 64)
         launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else

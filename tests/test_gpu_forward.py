@@ -259,6 +259,34 @@ def test_norms_of_narrow_models(d_model, N, S):
         assert (psd.psd_forward_logits(model, to_dev(states[s: s + 1]), bs, L).cpu().numpy().reshape(L, -1) == z[s]).all()
 
 
+@pytest.mark.parametrize("vocab", [128, 997, 5000])
+def test_head_of_small_vocabularies(vocab):
+    """Vocabularies of few ids are dealt in tiles of 128: one tile and ragged last ones, 32 to 192 hidden rows (each width of a tile, whole
+    and partial).  Against the softmax of the call's own logits, which another kernel computes from the same hidden rows: two fp32 sums
+    of 512 products differ by at most 2 * 512 * 2^-24 * sum |y w| < 1e-3 (the sum is about 15), and a logit error of e changes a
+    probability by a factor exp(2 e) at most.  And a sequence's bits do not depend on how many stand in the call."""
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    shape = inp.cut_down(SMALL, n_layers=2, vocab=vocab, seed=93)
+    N, bs, L = 64, 32, 32
+    host, model = make_models(shape, N)
+    states = np.stack([_state(shape, N, bs, L, 170 + s, (3 * s) % 8) for s in range(6)])
+    first = None
+    for S in (1, 2, 3, 4, 5, 6):
+        d = to_dev(states[:S])
+        top1, conf = (x.cpu().numpy().reshape(S, L) for x in psd.psd_forward_confidence(model, d, bs, L))
+        z = psd.psd_forward_logits(model, d, bs, L).cpu().numpy().reshape(S, L, -1).astype(np.float64)
+        z[..., shape.mask_id] = -np.inf
+        p = np.exp(z - z.max(-1, keepdims=True))
+        p = p.max(-1) / p.sum(-1)
+        masked = states[:S, bs: bs + L] == shape.mask_id
+        assert (np.abs(conf - p) <= np.expm1(2e-3) * p)[masked].all() and (conf == -1)[~masked].all()
+        assert (np.take_along_axis(z, top1[..., None], -1)[..., 0] >= z.max(-1) - 2e-3)[masked].all()
+        if first is None:
+            first = top1[0], conf[0]
+        assert (top1[0] == first[0]).all() and (conf[0] == first[1]).all()
+
+
 @pytest.mark.parametrize("name,N,S", [("small-2l", 96, 5), ("gqa-bias", 272, 3)])
 def test_qkv_epilogue_on_every_tile_configuration(name, N, S):
     """The same comparison with every workgroup tile forced in turn (the forced tile serves all contractions of both runs):
