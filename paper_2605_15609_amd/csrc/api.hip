@@ -212,7 +212,7 @@ int32_t psd_create(const psd_model_config *cfg, const psd_weights *w, psd_handle
         }
     }
     h->lm_head_packed = nullptr;
-    if (cfg->dtype == PSD_DTYPE_BF16) {
+    if (cfg->dtype == PSD_DTYPE_BF16 && head_streamed(1, cfg->vocab, cfg->d_model)) {
         // second copy of the LM-head in MFMA-fragment order for the streaming confidence pass
         hipError_t pe = hipMalloc(&h->lm_head_packed, packed_rows_bytes(cfg->vocab, cfg->d_model));
         if (pe != hipSuccess) {

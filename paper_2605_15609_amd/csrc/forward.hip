@@ -263,7 +263,7 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st, next_down);
         pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hs, d, ksplit, st, next_qkv);
     }
-    T *ypack = (c.dtype == PSD_DTYPE_BF16 && h->lm_head_packed && head_stream_supported(S * L, d)) ? (T *)(ws + p.off_ypack) : nullptr;
+    T *ypack = (h->lm_head_packed && head_streamed(S * L, c.vocab, d)) ? (T *)(ws + p.off_ypack) : nullptr;
     if (final_in != hbuf)   // already the packed block rows
         launch_rmsnorm_block<T>(final_in, nullptr, S, L, 0, L, d, h->final_norm, c.rms_eps, y, ypack, pend, st);
     else
@@ -360,7 +360,7 @@ int32_t forward_cached_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         Dispatch<T>::gemm(h, a, d, lw.w_gate, lw.w_up, d, nrow, F, d, EPI_SWIGLU, nullptr, act, nullptr, ld_act, nullptr, st, next_down);
         pend = Dispatch<T>::gemm(h, act, ld_act, lw.w_down, nullptr, h->w_down_stride, nrow, d, F, EPI_RESIDUAL, nullptr, nullptr, hbuf, d, ksplit, st, next_qkv);
     }
-    T *ypack = (c.dtype == PSD_DTYPE_BF16 && h->lm_head_packed && head_stream_supported(S * L, d)) ? (T *)(ws + p.off_ypack) : nullptr;
+    T *ypack = (h->lm_head_packed && head_streamed(S * L, c.vocab, d)) ? (T *)(ws + p.off_ypack) : nullptr;
     launch_rmsnorm_block<T>(hbuf, nullptr, S, L, 0, L, d, h->final_norm, c.rms_eps, y, ypack, pend, st);
     return PSD_OK;
 }
@@ -482,14 +482,15 @@ int32_t run_head_confidence(psd_handle *h, const int32_t *tokens, const int32_t 
     } stop{pr, timed, st, (double)c.vocab * c.d_model * (c.dtype == PSD_DTYPE_BF16 ? 2.0 : 4.0) +
                               (double)rows * c.d_model * (c.dtype == PSD_DTYPE_BF16 ? 2.0 : 4.0) + rows * 8.0, rows};
     if (timed) (void)hipEventRecord(pr.ev[pr.used], st);
-    if (c.dtype == PSD_DTYPE_BF16 && !(h->plain_mask & 4) && h->lm_head_packed && head_stream_supported(rows, c.d_model)) {
-        // y was already written in fragment order by the final norm; the merge writes (top1, conf) directly
+    if (c.dtype == PSD_DTYPE_BF16 && !(h->plain_mask & 4) && head_stream_supported(rows, c.d_model)) {
+        // the merge writes (top1, conf) directly
         HeadFinish fin = {tokens, seq_rows, out_rows, S, N, block_start, L, top1, conf};
-        if (head_few_workgroups(c.vocab))
+        if (h->lm_head_packed && head_streamed(rows, c.vocab, c.d_model))   // y was written in fragment order by the final norm
+            launch_head_stream_finish_bf16((const bf16_t *)(ws + p.off_ypack), (const bf16_t *)h->lm_head_packed, rows, c.vocab, c.d_model,
+                                           c.logit_scale, c.mask_id, ws + p.off_part, fin, st);
+        else
             launch_head_tiled_finish_bf16((const bf16_t *)(ws + p.off_y), (const bf16_t *)h->lm_head, rows, c.vocab, c.d_model, c.logit_scale, c.mask_id,
                                           ws + p.off_part, fin, st);
-        else launch_head_stream_finish_bf16((const bf16_t *)(ws + p.off_ypack), (const bf16_t *)h->lm_head_packed, rows, c.vocab,
-                                       c.d_model, c.logit_scale, c.mask_id, ws + p.off_part, fin, st);
         PSD_HIP(hipGetLastError());
         return PSD_OK;
     } else if (c.dtype == PSD_DTYPE_BF16 && !(h->plain_mask & 4)) {

@@ -17,8 +17,6 @@ using namespace mfma;
 
 constexpr int SLAB_BIG = 256, SLAB_SMALL = 128;
 
-int slab_rows(int rows) { return rows <= 32 ? SLAB_SMALL : SLAB_BIG; }
-
 // one wavefront per hidden row: merge the per-slab triples; row_sum = sum_v exp(z_v - z_max)
 __global__ __launch_bounds__(64) void head_merge_kernel(const float *__restrict__ pmax, const float *__restrict__ psum,
                                                         const int32_t *__restrict__ parg, int slabs, int rows,
@@ -44,7 +42,7 @@ __global__ __launch_bounds__(64) void head_merge_kernel(const float *__restrict_
 
 
 // ---------------------------------------------------------------------------------------------
-// Streaming head for few hidden rows (<= 192): the pass is HBM-bound, so it is built as a pure
+// Streaming head for few hidden rows (<= 192; where it runs: head_streamed): the pass is HBM-bound, so it is built as a pure
 // stream.  W_lm is kept in a second copy laid out in MFMA-fragment order -- for every block of 32
 // vocabulary rows and 16 k, the 64 lanes' 16-byte operands back to back (1 KB) -- so that a
 // wavefront that owns TMV*32 vocabulary ids reads its share of the matrix as one linear run of
@@ -280,54 +278,64 @@ void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_pack
                        mask_id, V);
 }
 
-// The streaming kernel deals 512 vocabulary ids a workgroup; a vocabulary that gives it less than one workgroup for every other CU is spread
-// over tiles of 128 ids instead (V = 32 000, K = 512: 128 rows 25.2 -> 13.4 us, 32 rows 13.0 -> 9.8).  Two wavefronts share the ids of a
-// tile whatever its width, so the exponentials of a row are added in one order for every number of rows.
-bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
-
-void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
-                                   const HeadFinish &fin, hipStream_t st) {
-    const int slabs = (V + SLAB_SMALL - 1) / SLAB_SMALL;
-    const int64_t stride = align_up((int64_t)((V + 31) / 32) * rows * 4, 256);
-    Top1Args t1;
-    t1.scale = scale;
-    t1.mask_id = mask_id;
-    t1.pmax = (float *)partials;
-    t1.psum = (float *)((char *)partials + stride);
-    t1.parg = (int32_t *)((char *)partials + 2 * stride);
-    t1.cols_total = rows;
-    if (rows <= 32)
-        launch_cfg<SLAB_SMALL, 32, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    else if (rows <= 64)
-        launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    else
-        launch_cfg<SLAB_SMALL, 128, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    hipLaunchKernelGGL(head_merge_finish_kernel, dim3(rows), dim3(256), 0, st, t1.pmax, t1.psum, t1.parg, slabs, rows, fin, mask_id, V);
+// Which way the pass goes up to 192 rows.  The streaming kernel reads its packed copy of the matrix as one linear run, but its wavefronts fetch the
+// hidden rows again and again and wait for every fetch in order.  The tiles, two workgroups of 256 ids a CU, share them through LDS and are
+// ahead or level at every number of rows (us, streamed -> tiled, with V ids and rows of d): V 126 464, d 4096: 32 rows 190 -> 177,
+// 128 rows 215 -> 191, 160 rows 290 -> 226; V 152 064, d 3584: 246 -> 230, 301 -> 236, 347 -> 278; V 131 072, d 1024: 58 -> 48, 68 -> 60, 98 -> 86;
+// d 3072, 2560 and 1536 level up to 128 rows.  Only where a row of the matrix is 4 KB long does reading it row by row lose (d 2048: 32 rows
+// 106 -> 130, 128 rows 119 -> 138, but 160 rows 166 -> 153); rows of more than 8 KB are not measured and stay with the packed copy.
+bool head_streamed(int rows, int V, int d) {
+    return !head_few_workgroups(V) && rows <= 128 && head_stream_supported(rows, d) && (d == 2048 || d > 4096);
 }
 
-void launch_head_confidence_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id,
-                                 void *partials, float *row_sum, int32_t *row_arg, hipStream_t st) {
-    const int slab = slab_rows(rows);
-    const int slabs = (V + slab - 1) / slab;
+// A vocabulary that gives the streaming kernel, 512 ids a workgroup, less than one workgroup for every other CU is spread over tiles of 128 ids
+// (V = 32 000, K = 512: 128 rows 25.2 streamed -> 13.4 us, 32 rows 13.0 -> 9.8)
+bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
+
+// row operand = W_lm (M := V), column operand = y (Nout := rows).  Two wavefronts share the ids of a tile whatever its width, so a row's
+// exponentials are added in one order for every number of rows.
+static int tiled_partials(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials, Top1Args &t1,
+                          hipStream_t st) {
     const int64_t stride = align_up((int64_t)((V + 31) / 32) * rows * 4, 256);
-    Top1Args t1;
     t1.scale = scale;
     t1.mask_id = mask_id;
     t1.pmax = (float *)partials;
     t1.psum = (float *)((char *)partials + stride);
     t1.parg = (int32_t *)((char *)partials + 2 * stride);
     t1.cols_total = rows;
-    // row operand = W_lm (M := V), column operand = y (Nout := rows)
+    if (rows <= 192 && head_few_workgroups(V)) {
+        if (rows <= 32)
+            launch_cfg<SLAB_SMALL, 32, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        else if (rows <= 64)
+            launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        else
+            launch_cfg<SLAB_SMALL, 128, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        return (V + SLAB_SMALL - 1) / SLAB_SMALL;
+    }
     if (rows <= 32)
-        launch_cfg<SLAB_SMALL, 32, 4, 1, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        launch_cfg<SLAB_BIG, 32, 2, 2, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else if (rows <= 64)
-        launch_cfg<SLAB_BIG, 64, 4, 1, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+        launch_cfg<SLAB_BIG, 64, 2, 2, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else if (rows > 128 && d >= 2048)
         // (256 hidden rows against 128 a tile, V = 126 464 - 152 064, K = 3584 - 4096: 200 rows 270 -> 226 us, 768 rows 746 -> 617, 8192 rows 6649 -> 5848
         // = 1.45 PFLOP/s; 320 rows, a partial second tile, 365 against 389; with K = 512 it is ahead only where the tiles come out even)
         launch_cfg<SLAB_BIG, 256, 2, 2, EPI_TOP1, 2, 3>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
     else
         launch_cfg<SLAB_BIG, 128, 2, 2, EPI_TOP1, 3, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
+    return (V + SLAB_BIG - 1) / SLAB_BIG;
+}
+
+void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
+                                   const HeadFinish &fin, hipStream_t st) {
+    Top1Args t1;
+    const int slabs = tiled_partials(y, W, rows, V, d, scale, mask_id, partials, t1, st);
+    hipLaunchKernelGGL(head_merge_finish_kernel, dim3(rows), dim3(256), 0, st, t1.pmax, t1.psum, t1.parg, slabs, rows, fin, mask_id, V);
+}
+
+void launch_head_confidence_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id,
+                                 void *partials, float *row_sum, int32_t *row_arg, hipStream_t st) {
+    Top1Args t1;
+    const int slabs = tiled_partials(y, W, rows, V, d, scale, mask_id, partials, t1, st);
     hipLaunchKernelGGL(head_merge_kernel, dim3(rows), dim3(64), 0, st, t1.pmax, t1.psum, t1.parg, slabs, rows, row_sum,
                        row_arg);
 }

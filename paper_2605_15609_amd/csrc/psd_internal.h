@@ -25,7 +25,7 @@ struct psd_handle {
     int w_down_stride;       // row stride of every w_down (elements)
     int device;
     int plain_mask;          // debug: bit 0 plain GEMM, bit 1 plain attention, bit 2 plain LM-head, bit 3 rotary / V transpose as a separate kernel
-    void *lm_head_packed;    // bf16 models: fragment-order copy of lm_head owned by the handle (streaming LM-head)
+    void *lm_head_packed;    // bf16 models whose head runs streamed: fragment-order copy of lm_head owned by the handle
     int32_t *host_counts;    // pinned host staging for psd_decode_block
     int host_counts_cap;
     // optional HIP-event timing of one contraction kernel (epilogue kind + tile config)
@@ -410,6 +410,7 @@ struct HeadFinish {
     float *conf;
 };
 bool head_few_workgroups(int V);
+bool head_streamed(int rows, int V, int d);   // up to 192 rows: the streaming kernel on the packed copy, else tiles
 void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
                                    const HeadFinish &fin, hipStream_t st);
 void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_packed, int rows, int V, int d, float scale,

@@ -259,10 +259,10 @@ def test_norms_of_narrow_models(d_model, N, S):
         assert (psd.psd_forward_logits(model, to_dev(states[s: s + 1]), bs, L).cpu().numpy().reshape(L, -1) == z[s]).all()
 
 
-@pytest.mark.parametrize("vocab", [128, 997, 5000])
-def test_head_of_small_vocabularies(vocab):
-    """Vocabularies of few ids are dealt in tiles of 128: one tile and ragged last ones, 32 to 192 hidden rows (each width of a tile, whole
-    and partial).  Against the softmax of the call's own logits, which another kernel computes from the same hidden rows: two fp32 sums
+@pytest.mark.parametrize("vocab", [128, 997, 5000, 66001])
+def test_head_in_tiles(vocab):
+    """The head over 32 to 192 hidden rows (each width of a tile, whole and partial): few ids in tiles of 128, one tile and ragged last ones,
+    many in tiles of 256.  Against the softmax of the call's own logits, which another kernel computes from the same hidden rows: two fp32 sums
     of 512 products differ by at most 2 * 512 * 2^-24 * sum |y w| < 1e-3 (the sum is about 15), and a logit error of e changes a
     probability by a factor exp(2 e) at most.  And a sequence's bits do not depend on how many stand in the call."""
     import paper_2605_15609_amd as psd
