@@ -429,10 +429,10 @@ int64_t psd_kernel_attention_scratch_bytes(int32_t S, int32_t N, int32_t n_kv_he
 int32_t psd_kernel_attention_bf16(const void *qkv, int32_t ld_qkv, int32_t S, int32_t N, int32_t n_heads,
                                   int32_t n_kv_heads, int32_t d_head, void *vT, void *out, void *stream);
 int64_t psd_kernel_head_scratch_bytes(int32_t rows, int32_t vocab);
-/*   streaming head (what the forward runs for <= 192 rows): both operands in MFMA-fragment order,
+/*   streaming head (at most 192 rows; the forward runs it up to 128, where a row of the matrix is 4 KB or over 8 KB): both operands in MFMA-fragment order,
  *          [ceil(R/32)][K/16][64 lanes][8 bf16]; psd_kernel_pack_rows builds that copy of a row-major
  *          [R, K] matrix into dst of psd_kernel_packed_bytes(R, K) bytes.  Same outputs and scratch as
- *          psd_kernel_head_confidence_bf16 (the tiled kernel, which the forward keeps for more rows). */
+ *          psd_kernel_head_confidence_bf16 (the tiled kernel, which the forward runs otherwise). */
 int64_t psd_kernel_packed_bytes(int64_t R, int32_t K);
 int32_t psd_kernel_pack_rows(const void *src, int64_t R, int32_t K, void *dst, void *stream);
 int32_t psd_kernel_head_stream_bf16(const void *y_packed, const void *W_packed, int32_t rows, int32_t vocab, int32_t d,
