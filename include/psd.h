@@ -204,7 +204,9 @@ int32_t psd_forward_logits(psd_handle *h, const int32_t *tokens, int32_t S, int3
 
 /* Debug switch for numeric cross-checks: bit 0 runs the layer contractions, bit 1 the
  * attention, bit 2 the LM-head on the plain (non-MFMA) kernels; bit 3 keeps the rotary embedding and the
- * transpose of V in a kernel of their own instead of the QKV projection's epilogue (same bits either way).
+ * transpose of V in a kernel of their own instead of the QKV projection's epilogue (same bits either way); bit 4
+ * takes the entries that a refresh stores in the approximate cache from the row-major values instead of the
+ * transposed ones (same bits too).
  * 0 (default) = MFMA path. */
 int32_t psd_debug_set_plain(psd_handle *h, int32_t mask);
 

@@ -310,17 +310,18 @@ __global__ __launch_bounds__(256) void kv_store_outside_kernel(const bf16_t *__r
 }
 }   // namespace
 
-bool launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
+bool kv_store_outside_fits(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int d_head, const bf16_t *k_cache, const bf16_t *vt_cache, const KvPrefix &at) {
+    const auto aligned = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+    return d_head % 8 == 0 && ld_qkv % 8 == 0 && at.ld_k % 8 == 0 && at.ld_vt % 8 == 0 && at.stride_k % 8 == 0 && at.stride_vt % 8 == 0 && aligned(qkv) &&
+           aligned(vT) && aligned(k_cache) && aligned(vt_cache);
+}
+
+void launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
                              bf16_t *k_cache, bf16_t *vt_cache, const KvPrefix &at, hipStream_t st) {
     const int w = n_kv_heads * d_head;
-    const auto aligned = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    if (d_head % 8 || ld_qkv % 8 || at.ld_k % 8 || at.ld_vt % 8 || at.stride_k % 8 || at.stride_vt % 8 || !aligned(qkv) || !aligned(vT) || !aligned(k_cache) ||
-        !aligned(vt_cache))
-        return false;
-    if (N <= L || S <= 0) return true;
+    if (N <= L || S <= 0) return;
     hipLaunchKernelGGL(kv_store_outside_kernel, dim3((unsigned)(S * (N - L) + S * (int64_t)w / 4)), dim3(256), 0, st, qkv, ld_qkv, vT, (int)vt_row_stride(N), S,
                        N, b0, L, n_heads, w, k_cache, vt_cache, d_head, at);
-    return true;
 }
 
 template void launch_kv_store<float>(const float *, int, int, int, int, int, int, int, int, float *, float *, const KvPrefix &,

@@ -77,7 +77,8 @@ struct Dispatch<float> {
         launch_plain_attention<float>(qkv, ld_qkv, S, N, H, Hkv, dh, out, pre, block_len, st);
         return false;
     }
-    static bool store_outside(const float *, int, const float *, int, int, int, int, int, int, int, float *, float *, const KvPrefix &, hipStream_t) { return false; }
+    static bool store_outside_fits(psd_handle *, const float *, int, const float *, int, int, const float *, const float *, const KvPrefix &) { return false; }
+    static void store_outside(const float *, int, const float *, int, int, int, int, int, int, int, float *, float *, const KvPrefix &, hipStream_t) {}
 };
 
 template <>
@@ -166,9 +167,14 @@ struct Dispatch<bf16_t> {
         }
         return true;
     }
-    static bool store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int H, int Hkv, int dh, bf16_t *k_cache,
+    // whether the refreshed entries of the approximate cache can be taken from the transposed values (bit 4 of the debug switch: not)
+    static bool store_outside_fits(psd_handle *h, const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int N, int dh, const bf16_t *k_cache,
+                                   const bf16_t *vt_cache, const KvPrefix &at) {
+        return N % 8 == 0 && !(h->plain_mask & (2 | 16)) && kv_store_outside_fits(qkv, ld_qkv, vT, dh, k_cache, vt_cache, at);
+    }
+    static void store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int H, int Hkv, int dh, bf16_t *k_cache,
                               bf16_t *vt_cache, const KvPrefix &at, hipStream_t st) {
-        return launch_kv_store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st);
+        launch_kv_store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st);
     }
 };
 
@@ -211,13 +217,28 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         const bool fused = wk == wq + (int64_t)H * dh * d && wv == wk + (int64_t)Hkv * dh * d &&
                            (!c.qkv_bias || (lw.bk == lw.bq + H * dh && lw.bv == lw.bk + Hkv * dh));
         const int block_len = c.attention == PSD_ATTN_BLOCK_CAUSAL ? L : 0;
+        // approximate cache: where this layer's keys / values of every position outside the block go
+        KvPrefix at;
+        T *k_cache = nullptr, *vt_cache = nullptr;
+        bool outside = false;      // (values from vT; otherwise they are read row-major out of qkv, and the projection has to leave them there)
+        if (store) {
+            const KvLayout lay = kv_layout(c, store->capacity);
+            k_cache = (T *)store->base + (int64_t)li * (lay.k_elems + lay.vt_elems);
+            vt_cache = k_cache + lay.k_elems;
+            at.ld_k = (int)lay.ld_k;
+            at.ld_vt = (int)lay.ld_vt;
+            at.stride_k = at.stride_vt = lay.per_seq;
+            at.seq_rows = seq_rows;
+            at.len = 0;
+            outside = Dispatch<T>::store_outside_fits(h, qkv, ld_qkv, vT, N, dh, k_cache, vt_cache, at);
+        }
         bool rotated = false;
         if (fused) {
             KvDest own;
             own.vT = N % 8 == 0 ? (bf16_t *)vT : nullptr;   // (the attention of the other lengths reads V row-major)
             own.ld_vt = (int)vt_row_stride(N);
             own.vt_seq = (int64_t)Hkv * dh * own.ld_vt;
-            rotated = ld_qkv == qkv_w &&
+            rotated = ld_qkv == qkv_w && (!store || !own.vT || outside) &&
                       Dispatch<T>::qkv_fused(h, a, wq, ntok, N, 0, H, Hkv, dh, c.qkv_bias ? lw.bq : nullptr, qkv, ld_qkv, own, block_len, st, next_o);
             if (!rotated) Dispatch<T>::gemm(h, a, d, wq, nullptr, d, ntok, qkv_w, d, epi_qkv, lw.bq, qkv, nullptr, ld_qkv, nullptr, st, next_o);
         } else {
@@ -227,20 +248,13 @@ int32_t forward_hidden_impl(psd_handle *h, const int32_t *tokens, const int32_t 
         }
         const bool transposed = Dispatch<T>::rope_attention(h, qkv, ld_qkv, vT, S, N, 0, H, Hkv, dh, o, KvPrefix(), block_len, st, rotated);
         if (store) {
-            // approximate cache: freeze this layer's keys / values of every position outside the block, prefix first
-            const KvLayout lay = kv_layout(c, store->capacity);
-            T *k_cache = (T *)store->base + (int64_t)li * (lay.k_elems + lay.vt_elems), *vt_cache = k_cache + lay.k_elems;
-            KvPrefix at;
-            at.ld_k = (int)lay.ld_k;
-            at.ld_vt = (int)lay.ld_vt;
-            at.stride_k = at.stride_vt = lay.per_seq;
-            at.seq_rows = seq_rows;
-            at.len = 0;
             const int b0 = block_start.common;     // (a common block start: checked by run_forward_hidden)
             // one launch of 16-byte copies where the attention read the values key-contiguous (8B shape, 512 tokens: rotary, attention and
             // copies 53 us a layer, 26 with it and the projection's own rotary); else (lengths that are no multiple of 8, the debug paths) V
             // is row-major in qkv
-            if (!transposed || !Dispatch<T>::store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st)) {
+            if (outside && transposed) {
+                Dispatch<T>::store_outside(qkv, ld_qkv, vT, S, N, b0, L, H, Hkv, dh, k_cache, vt_cache, at, st);
+            } else {
                 launch_kv_store<T>(qkv, ld_qkv, S, N, 0, b0, H, Hkv, dh, k_cache, vt_cache, at, st);
                 at.len = b0;
                 launch_kv_store<T>(qkv, ld_qkv, S, N, b0 + L, N - b0 - L, H, Hkv, dh, k_cache, vt_cache, at, st);

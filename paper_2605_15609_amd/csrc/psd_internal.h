@@ -24,7 +24,8 @@ struct psd_handle {
     std::vector<Layer> layers;
     int w_down_stride;       // row stride of every w_down (elements)
     int device;
-    int plain_mask;          // debug: bit 0 plain GEMM, bit 1 plain attention, bit 2 plain LM-head, bit 3 rotary / V transpose as a separate kernel
+    int plain_mask;          // debug: bit 0 plain GEMM, bit 1 plain attention, bit 2 plain LM-head, bit 3 rotary / V transpose as a separate kernel,
+                             // bit 4 the approximate cache's refreshed entries from the row-major values
     void *lm_head_packed;    // bf16 models whose head runs streamed: fragment-order copy of lm_head owned by the handle
     int32_t *host_counts;    // pinned host staging for psd_decode_block
     int host_counts_cap;
@@ -246,8 +247,9 @@ template <typename T>
 void launch_kv_store(const T *qkv, int ld_qkv, int S, int rows_per_seq, int row_first, int count, int n_heads, int n_kv_heads,
                      int d_head, T *k_cache, T *vt_cache, const KvPrefix &at, hipStream_t st);
 // the entries of all positions outside rows [b0, b0 + L) of every sequence (N rows each, rotated) at cache positions 0 .. N - L - 1, values
-// taken from vT (as the MFMA attention reads them); false, nothing launched: not 16-byte accessible
-bool launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
+// taken from vT (as the MFMA attention reads them); fits: everything is 16-byte accessible
+bool kv_store_outside_fits(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int d_head, const bf16_t *k_cache, const bf16_t *vt_cache, const KvPrefix &at);
+void launch_kv_store_outside(const bf16_t *qkv, int ld_qkv, const bf16_t *vT, int S, int N, int b0, int L, int n_heads, int n_kv_heads, int d_head,
                              bf16_t *k_cache, bf16_t *vt_cache, const KvPrefix &at, hipStream_t st);
 // K-split partial sums that still have to be added to the residual stream h [rows, d]: partial[s] has the
 // same shape, s = 0 .. n-1, `stride` floats apart.  The norm that reads h next adds them (and stores h).

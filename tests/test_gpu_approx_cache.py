@@ -199,3 +199,28 @@ def test_refreshed_entries_are_copies_of_the_keys_and_values(name, N, start, L):
     assert torch.equal(mem[0], mem[2])
     values = mem[0].view(torch.int16)
     assert int((values != 0x7f7f).sum()) >= values.numel() * (N - L) // (2 * ((N - L + 8 + 63) // 64 * 64)) * 0.9
+
+
+@pytest.mark.parametrize("name", list(BF16))
+@pytest.mark.parametrize("N,start,L", [(96, 40, 16), (128, 0, 32), (136, 33, 48), (160, 96, 64), (77, 16, 16)])
+def test_refreshed_entries_from_the_row_major_values(name, N, start, L):
+    """Where the transposed values cannot be copied 16 bytes at a time (debug bit 4 says so) the entries are taken from the row-major
+    ones, and the projection has to leave those behind: with rows of a multiple of 16 its epilogue would write the transposed ones alone.
+    The same bits in the caches and in the call's results, from a workspace that holds something else."""
+    import paper_2605_15609_amd as psd
+    shape = BF16[name]
+    B = 2
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    tokens = np.stack([inp.draw_prompt(shape.vocab, N, 80 + b) for b in range(B)]).astype(np.int32)
+    tokens[:, start:start + L] = shape.mask_id
+    got = []
+    for mask in (0, 16):
+        model.set_plain(mask)
+        model.workspace(1 << 26).fill_(0x3c)
+        cache = psd.KvCache(model, B, N - L)
+        cache.mem.fill_(0x7f)
+        top1, conf = psd.psd_forward_confidence_approx(model, _dev(tokens), start, L, cache, refresh=True)
+        got.append((cache.mem.clone(), top1, conf))
+    model.set_plain(0)
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
