@@ -1249,6 +1249,14 @@ int32_t psd_debug_gemm_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogu
     return PSD_OK;
 }
 
+int32_t psd_debug_head_plan(int32_t rows, int32_t vocab, int32_t d, int32_t *ids, int32_t *width) {
+    if (rows < 1 || vocab < 2 || d < 1 || d % 64 || !ids || !width) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    const HeadPlan p = head_plan(rows, vocab, d);
+    *ids = p.ids;
+    *width = p.rows;
+    return head_streamed(rows, vocab, d) ? 1 : 0;
+}
+
 int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq) {
     if (M < 1 || Nout < 1 || Kin < 1 || rows_per_seq < 1) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
     const int tile = gemm_bf16_qkv_tile(M, Nout, d_head, v_start, rows_per_seq);

@@ -292,8 +292,24 @@ bool head_streamed(int rows, int V, int d) {
 // (V = 32 000, K = 512: 128 rows 25.2 streamed -> 13.4 us, 32 rows 13.0 -> 9.8)
 bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
 
+// The tile of ids x hidden rows.
+// 129 - 192 rows are one column of tiles, 192 rows wide: two columns of 128 fetch the matrix twice and, with 128 ids, need a round more (V 50 304, d 512:
+// 192 rows 43 -> 27 us, d 2560 104 -> 73; V 128 256, d 768: 75 -> 58).  Where two columns are one round all the same (up to 16 384 ids) their tiles
+// stay: they have four LDS stages instead of two (V 8192, d 2048: 24.5 us, 35 as one column).  256x192 against 256x256 from d 2048 on: level or up to 8 % ahead.
+HeadPlan head_plan(int rows, int V, int d) {
+    if (rows <= 192 && head_few_workgroups(V)) {
+        const int slabs = (V + SLAB_SMALL - 1) / SLAB_SMALL;
+        return {SLAB_SMALL, rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 128 || 2 * slabs <= 256 ? 128 : 192};
+    }
+    if (rows > 128 && rows <= 192) return {SLAB_BIG, 192};
+    // 256 hidden rows against 128 a tile, V = 126 464 - 152 064, K = 3584 - 4096: 200 rows 270 -> 226 us, 768 rows 746 -> 617, 8192 rows 6649 -> 5848
+    // = 1.45 PFLOP/s; 320 rows, a partial second tile, 365 against 389; with K = 512 it is ahead only where the tiles come out even
+    return {SLAB_BIG, rows <= 32 ? 32 : rows <= 64 ? 64 : rows > 128 && d >= 2048 ? 256 : 128};
+}
+
 // row operand = W_lm (M := V), column operand = y (Nout := rows).  Two wavefronts share the ids of a tile whatever its width, so a row's
-// exponentials are added in one order for every number of rows.
+// exponentials are added in one order for every number of rows up to 192.  Above that the merge kernel is another one, and small vocabularies
+// change from tiles of 128 ids to 256: the last bits of a confidence can differ across that line.
 static int tiled_partials(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials, Top1Args &t1,
                           hipStream_t st) {
     const int64_t stride = align_up((int64_t)((V + 31) / 32) * rows * 4, 256);
@@ -303,26 +319,25 @@ static int tiled_partials(const bf16_t *y, const bf16_t *W, int rows, int V, int
     t1.psum = (float *)((char *)partials + stride);
     t1.parg = (int32_t *)((char *)partials + 2 * stride);
     t1.cols_total = rows;
-    if (rows <= 192 && head_few_workgroups(V)) {
-        if (rows <= 32)
-            launch_cfg<SLAB_SMALL, 32, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-        else if (rows <= 64)
-            launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-        else
-            launch_cfg<SLAB_SMALL, 128, 2, 2, EPI_TOP1, 4, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-        return (V + SLAB_SMALL - 1) / SLAB_SMALL;
+    const HeadPlan p = head_plan(rows, V, d);
+    auto run = [&](auto launch) { launch(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st, 1, nullptr, QkvArgs(), Warm()); };
+    if (p.ids == SLAB_SMALL) {
+        switch (p.rows) {
+            case 32: run(launch_cfg<SLAB_SMALL, 32, 2, 2, EPI_TOP1, 4, 4>); break;
+            case 64: run(launch_cfg<SLAB_SMALL, 64, 2, 2, EPI_TOP1, 4, 4>); break;
+            case 192: run(launch_cfg<SLAB_SMALL, 192, 2, 2, EPI_TOP1, 2, 2, 2>); break;
+            default: run(launch_cfg<SLAB_SMALL, 128, 2, 2, EPI_TOP1, 4, 4>); break;
+        }
+    } else {
+        switch (p.rows) {
+            case 32: run(launch_cfg<SLAB_BIG, 32, 2, 2, EPI_TOP1, 2, 2, 2>); break;
+            case 64: run(launch_cfg<SLAB_BIG, 64, 2, 2, EPI_TOP1, 2, 2, 2>); break;
+            case 192: run(launch_cfg<SLAB_BIG, 192, 2, 2, EPI_TOP1, 2, 4>); break;
+            case 256: run(launch_cfg<SLAB_BIG, 256, 2, 2, EPI_TOP1, 2, 3>); break;
+            default: run(launch_cfg<SLAB_BIG, 128, 2, 2, EPI_TOP1, 3, 4>); break;
+        }
     }
-    if (rows <= 32)
-        launch_cfg<SLAB_BIG, 32, 2, 2, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    else if (rows <= 64)
-        launch_cfg<SLAB_BIG, 64, 2, 2, EPI_TOP1, 2, 2, 2>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    else if (rows > 128 && d >= 2048)
-        // (256 hidden rows against 128 a tile, V = 126 464 - 152 064, K = 3584 - 4096: 200 rows 270 -> 226 us, 768 rows 746 -> 617, 8192 rows 6649 -> 5848
-        // = 1.45 PFLOP/s; 320 rows, a partial second tile, 365 against 389; with K = 512 it is ahead only where the tiles come out even)
-        launch_cfg<SLAB_BIG, 256, 2, 2, EPI_TOP1, 2, 3>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    else
-        launch_cfg<SLAB_BIG, 128, 2, 2, EPI_TOP1, 3, 4>(W, y, nullptr, V, rows, d, d, d, nullptr, nullptr, nullptr, 0, t1, st);
-    return (V + SLAB_BIG - 1) / SLAB_BIG;
+    return (V + p.ids - 1) / p.ids;
 }
 
 void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,

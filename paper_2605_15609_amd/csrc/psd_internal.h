@@ -412,6 +412,10 @@ struct HeadFinish {
     float *conf;
 };
 bool head_few_workgroups(int V);
+struct HeadPlan {
+    int ids, rows;   // the tile where the pass runs in tiles: vocabulary ids x hidden rows
+};
+HeadPlan head_plan(int rows, int V, int d);
 bool head_streamed(int rows, int V, int d);   // up to 192 rows: the streaming kernel on the packed copy, else tiles
 void launch_head_tiled_finish_bf16(const bf16_t *y, const bf16_t *W, int rows, int V, int d, float scale, int mask_id, void *partials,
                                    const HeadFinish &fin, hipStream_t st);

@@ -297,6 +297,28 @@ def test_fused_head_sampled_rows(label, rows, V, d, path):
         assert abs((1.0 / row_sum[r]) / c[0] - 1.0) < 2e-3, f"{label}: row {r} confidence {1 / row_sum[r]} vs {c[0]}"
 
 
+@pytest.mark.parametrize("rows", [129, 160, 192, 193])
+@pytest.mark.parametrize("V,d", [(129, 64), (16384, 576), (16385, 576), (65024, 128), (65025, 64), (70001, 448)])
+def test_head_tiles_of_one_column(V, d, rows):
+    """129 - 192 hidden rows in one column of tiles or two, ids in tiles of 128 or 256 that no vocabulary here divides (and one that it does), one K stage
+    to nine; 193 rows are past it.  Every row against fp64 logits: fp32 sums of d products are off by at most d * 2^-24 * sum |y w| each, a logit
+    error of e changes the confidence by a factor exp(2 e), and the exponentials add 1e-5."""
+    from paper_2605_15609_amd import binding as B
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + V)
+    y = torch.empty((rows, d), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    W = torch.empty((V, d), dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.05, generator=g)
+    scale, mask_id = 1.7, V // 2
+    row_sum, row_arg = B.kernel_head_confidence_bf16(y, W, scale, mask_id)
+    z = scale * (y.double() @ W.double().T.contiguous())
+    e = scale * d * 2.0 ** -24 * float((y.double().abs() @ W.double().abs().T.contiguous()).max())
+    z[:, mask_id] = -float("inf")
+    best = z.max(-1).values
+    conf = 1.0 / torch.exp(z - best[:, None]).sum(-1)
+    assert float((1.0 / row_sum.double() / conf - 1.0).abs().max()) <= np.expm1(2 * e) + 1e-5
+    assert bool((z.gather(1, row_arg.long()[:, None])[:, 0] >= best - 2 * e).all())
+
+
 def test_head_ties_go_to_the_lowest_token_id_and_mask_is_excluded():
     from paper_2605_15609_amd import binding as B
     d, V = 64, 1000

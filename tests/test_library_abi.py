@@ -158,3 +158,20 @@ def test_prefill_workspace_is_bounded_and_falls_back_to_one_block(lib, monkeypat
     cache = types.SimpleNamespace(mem=torch.empty(1, dtype=torch.uint8), capacity=64)
     psd.psd_kv_prefill(m, torch.zeros((1, 64), dtype=torch.int32), 64, 16, cache)
     assert seen[1] < seen[0] and passed == [seen[1]] == [lib.psd_workspace_bytes(ctypes.byref(m.cfg), 1, 16, 16)]
+
+
+def test_head_plan(lib):
+    """129 - 192 hidden rows: a second column of tiles, which fetches the matrix again, only where both columns together are one round of the 256
+    CUs.  Up to 192 rows the ids of a tile do not depend on the number of rows (the order in which a row's exponentials are added)."""
+    ids, width = ctypes.c_int32(), ctypes.c_int32()
+    for vocab in (100, 5000, 16384, 16385, 32000, 50304, 65024, 65025, 73728, 128256, 256000):
+        for d in (64, 512, 1536, 2048, 4096, 8192):
+            seen = set()
+            for rows in (1, 32, 33, 64, 65, 128, 129, 160, 192):
+                assert lib.psd_debug_head_plan(rows, vocab, d, ctypes.byref(ids), ctypes.byref(width)) in (0, 1)
+                seen.add(ids.value)
+                tiles, columns = -(-vocab // ids.value), -(-rows // width.value)
+                if rows > 128:
+                    assert columns == 1 or tiles * columns <= 256, (vocab, d, rows)
+            assert len(seen) == 1
+    assert lib.psd_debug_head_plan(0, 5000, 512, ctypes.byref(ids), ctypes.byref(width)) < 0
