@@ -297,17 +297,20 @@ def test_fused_head_sampled_rows(label, rows, V, d, path):
         assert abs((1.0 / row_sum[r]) / c[0] - 1.0) < 2e-3, f"{label}: row {r} confidence {1 / row_sum[r]} vs {c[0]}"
 
 
-@pytest.mark.parametrize("rows", [129, 160, 192, 193])
-@pytest.mark.parametrize("V,d", [(129, 64), (16384, 576), (16385, 576), (65024, 128), (65025, 64), (70001, 448)])
-def test_head_tiles_of_one_column(V, d, rows):
+HEAD_TILES = [(V, d, rows) for V, d in [(129, 64), (16384, 576), (16385, 576), (65024, 128), (65025, 64), (70001, 448)] for rows in (129, 160, 192, 193)]
+HEAD_TILES += [(3001, 2048, 257), (32768, 2048, 200), (32769, 2048, 200), (9001, 2112, 1025)]    # above 192 rows, tiles of 128 or 256
+
+
+@pytest.mark.parametrize("V,d,rows", HEAD_TILES)
+def test_head_tiles_against_fp64(V, d, rows):
     """129 - 192 hidden rows in one column of tiles or two, ids in tiles of 128 or 256 that no vocabulary here divides (and one that it does), one K stage
-    to nine; 193 rows are past it.  Every row against fp64 logits: fp32 sums of d products are off by at most d * 2^-24 * sum |y w| each, a logit
+    to nine; above 192 rows, tiles of 128 rows and of 256, partial ones among them.  Every row against fp64 logits: fp32 sums of d products are off by at most d * 2^-24 * sum |y w| each, a logit
     error of e changes the confidence by a factor exp(2 e), and the exponentials add 1e-5."""
     from paper_2605_15609_amd import binding as B
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + V)
     y = torch.empty((rows, d), dtype=torch.bfloat16, device=DEV).normal_(generator=g)
-    W = torch.empty((V, d), dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.05, generator=g)
+    W = torch.empty((V, d), dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g)
     scale, mask_id = 1.7, V // 2
     row_sum, row_arg = B.kernel_head_confidence_bf16(y, W, scale, mask_id)
     z = scale * (y.double() @ W.double().T.contiguous())

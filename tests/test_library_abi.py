@@ -175,3 +175,15 @@ def test_head_plan(lib):
                     assert columns == 1 or tiles * columns <= 256, (vocab, d, rows)
             assert len(seen) == 1
     assert lib.psd_debug_head_plan(0, 5000, 512, ctypes.byref(ids), ctypes.byref(width)) < 0
+
+
+def test_head_plan_of_many_rows(lib):
+    """Above 192 hidden rows: tiles of 256 rows only where they give more than half of the 256 CUs work."""
+    ids, width = ctypes.c_int32(), ctypes.c_int32()
+    widths = set()
+    for vocab in (100, 4096, 8192, 16000, 32768, 32769, 50304, 126464, 152064):
+        for rows in (193, 256, 257, 384, 768, 8192):
+            assert lib.psd_debug_head_plan(rows, vocab, 4096, ctypes.byref(ids), ctypes.byref(width)) == 0
+            widths.add(width.value)
+            assert width.value == (256 if -(-vocab // 256) * -(-rows // 256) > 128 else 128), (vocab, rows)
+    assert widths == {128, 256}
