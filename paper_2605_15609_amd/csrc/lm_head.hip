@@ -301,13 +301,17 @@ HeadPlan head_plan(int rows, int V, int d) {
         const int slabs = (V + SLAB_SMALL - 1) / SLAB_SMALL;
         return {SLAB_SMALL, rows <= 32 ? 32 : rows <= 64 ? 64 : rows <= 128 || 2 * slabs <= 256 ? 128 : 192};
     }
+    const int slabs = (V + SLAB_BIG - 1) / SLAB_BIG;
     if (rows > 128 && rows <= 192) return {SLAB_BIG, 192};
+    // 65 - 128 rows where the 256x128 tiles, one to a CU, need a second round for less than half of the CUs: two columns of 256x64, two tiles to a CU
+    // (73 728 ids, d 512 96 rows 38 -> 32 us, d 1024 50 -> 46, d 1536 63 -> 61, but d 1984 and more level or up to 13 % behind; 86 016 and 92 544 ids, d 1024
+    // 5 % ahead, 100 352 level)
+    if (rows > 64 && rows <= 128 && d <= 1536 && slabs > 256 && slabs <= 384) return {SLAB_BIG, 64};
     // 256 hidden rows against 128 a tile, V = 126 464 - 152 064, K = 3584 - 4096: 200 rows 270 -> 226 us, 768 rows 746 -> 617, 8192 rows 6649 -> 5848
     // = 1.45 PFLOP/s; 320 rows, a partial second tile, 365 against 389; with K = 512 it is ahead only where the tiles come out even.
     // Where they give half of the CUs work or less, 128 rows a tile: V = 4096, d 2048, 256 rows 53 -> 35 us, V = 16 000, d 4096, 384 rows 90 -> 59
     // (94 workgroups 0.69 of the time, 126 0.66, 157 and more 1.1 - 1.4).
-    const int tiles = ((V + SLAB_BIG - 1) / SLAB_BIG) * ((rows + 255) / 256);
-    return {SLAB_BIG, rows <= 32 ? 32 : rows <= 64 ? 64 : rows > 128 && d >= 2048 && tiles > 128 ? 256 : 128};
+    return {SLAB_BIG, rows <= 32 ? 32 : rows <= 64 ? 64 : rows > 128 && d >= 2048 && slabs * ((rows + 255) / 256) > 128 ? 256 : 128};
 }
 
 // row operand = W_lm (M := V), column operand = y (Nout := rows).  Two wavefronts share the ids of a tile whatever its width, so a row's

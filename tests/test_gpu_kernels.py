@@ -298,6 +298,7 @@ def test_fused_head_sampled_rows(label, rows, V, d, path):
 
 
 HEAD_TILES = [(V, d, rows) for V, d in [(129, 64), (16384, 576), (16385, 576), (65024, 128), (65025, 64), (70001, 448)] for rows in (129, 160, 192, 193)]
+HEAD_TILES += [(65537, 192, 65), (98304, 64, 128), (98305, 64, 100)]                              # two columns of 64 rows, and past them
 HEAD_TILES += [(3001, 2048, 257), (32768, 2048, 200), (32769, 2048, 200), (9001, 2112, 1025)]    # above 192 rows, tiles of 128 or 256
 
 

@@ -187,3 +187,13 @@ def test_head_plan_of_many_rows(lib):
             widths.add(width.value)
             assert width.value == (256 if -(-vocab // 256) * -(-rows // 256) > 128 else 128), (vocab, rows)
     assert widths == {128, 256}
+
+
+def test_head_plan_of_narrow_models(lib):
+    """65 - 128 rows, up to 1536 wide: tiles that share a CU where one tile to a CU would leave less than half of the CUs with a second one."""
+    ids, width = ctypes.c_int32(), ctypes.c_int32()
+    for vocab in (65025, 65536, 65537, 73728, 98304, 98305, 128256):
+        for d in (64, 1536, 1600, 2048):
+            for rows in (65, 128):
+                assert lib.psd_debug_head_plan(rows, vocab, d, ctypes.byref(ids), ctypes.byref(width)) in (0, 1)
+                assert width.value == (64 if d <= 1536 and 65536 < vocab <= 98304 else 128), (vocab, d, rows)
