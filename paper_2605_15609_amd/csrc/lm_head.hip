@@ -1,8 +1,8 @@
 // LM-head fused with softmax top-1 (Sec. 3.1: x_hat = argmax_v p(v), c = max_v p(v)).
 //
 // The vocabulary is streamed once: W_lm [V, d] is the ROW operand of the MFMA kernel, the
-// hidden rows y [rows, d] the column operand, so a lane holds 16 vocabulary entries of one
-// hidden row per 32x32 tile (4 per 16x16 tile) and reduces them in registers.  Every workgroup owns a slab of
+// hidden rows y [rows, d] the column operand, so a lane holds 4 vocabulary entries of one
+// hidden row per 16x16 subtile (16 per 32x32 subtile in the streaming kernel) and reduces them in registers.  Every workgroup owns a slab of
 // 256 (or 128) vocabulary ids for a tile of hidden rows and emits one (max, argmax, sum-exp)
 // triple per row; a second tiny kernel merges the slabs in ascending id order, so ties keep
 // the lowest token id and the result does not depend on scheduling.  Full logits never
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64) void head_merge_kernel(const float *__restrict_
 
 
 // ---------------------------------------------------------------------------------------------
-// Streaming head for few hidden rows (<= 192; where it runs: head_streamed): the pass is HBM-bound, so it is built as a pure
+// Streaming head for few hidden rows (the kernel takes 192, the forward runs it up to 128: head_streamed): the pass is HBM-bound, so it is built as a pure
 // stream.  W_lm is kept in a second copy laid out in MFMA-fragment order -- for every block of 32
 // vocabulary rows and 16 k, the 64 lanes' 16-byte operands back to back (1 KB) -- so that a
 // wavefront that owns TMV*32 vocabulary ids reads its share of the matrix as one linear run of
@@ -278,18 +278,21 @@ void launch_head_stream_finish_bf16(const bf16_t *y_packed, const bf16_t *W_pack
                        mask_id, V);
 }
 
-// Which way the pass goes up to 192 rows.  The streaming kernel reads its packed copy of the matrix as one linear run, but its wavefronts fetch the
-// hidden rows again and again and wait for every fetch in order.  The tiles, two workgroups of 256 ids a CU, share them through LDS and are
-// ahead or level at every number of rows (us, streamed -> tiled, with V ids and rows of d): V 126 464, d 4096: 32 rows 190 -> 177,
-// 128 rows 215 -> 191, 160 rows 290 -> 226; V 152 064, d 3584: 246 -> 230, 301 -> 236, 347 -> 278; V 131 072, d 1024: 58 -> 48, 68 -> 60, 98 -> 86;
-// d 3072, 2560 and 1536 level up to 128 rows.  Only where a row of the matrix is 4 KB long does reading it row by row lose (d 2048: 32 rows
-// 106 -> 130, 128 rows 119 -> 138, but 160 rows 166 -> 153); rows of more than 8 KB are not measured and stay with the packed copy.
+// Which way the pass goes.  The streaming kernel reads its packed copy of the matrix as one linear run, but its wavefronts fetch the hidden rows again and
+// again and wait for every fetch in order.  The tiles share them through LDS (us, streamed -> tiled, V ids, rows of d): V 126 464, d 4096: 32 rows 190 -> 177,
+// 128 rows 215 -> 191, 160 rows 290 -> 205; V 152 064, d 3584: 246 -> 230, 301 -> 236, 347 -> 259; V 131 072, d 1024: 58 -> 48, 68 -> 60, 83 -> 66.
+// Swept over 65 025 - 256 000 ids and d 512 - 8192, tiled / streamed:
+//   129 - 192 rows       0.65 - 0.97 at every size: always tiles
+//   up to 128 rows       d 2048, 100 000 - 200 000 ids 0.94 - 1.32 (32 rows 103 -> 130 us at 128 256; rows of 4 KB start in one cache channel, 1984
+//                        and 2112 are level), other vocabularies 0.6 - 1.13; d 6144 0.86 - 1.24; d 5120 and 8192 level up to 131 072 ids (0.91 - 1.12),
+//                        0.74 - 0.98 above; d 4096 1.06 - 1.16 at 69 000 - 98 000 ids, 0.75 - 1.08 elsewhere; other d 0.6 - 1.12
+// so models of d 2048 and of more than 4096 keep the packed copy and stream up to 128 rows.
 bool head_streamed(int rows, int V, int d) {
     return !head_few_workgroups(V) && rows <= 128 && head_stream_supported(rows, d) && (d == 2048 || d > 4096);
 }
 
-// A vocabulary that gives the streaming kernel, 512 ids a workgroup, less than one workgroup for every other CU is spread over tiles of 128 ids
-// (V = 32 000, K = 512: 128 rows 25.2 streamed -> 13.4 us, 32 rows 13.0 -> 9.8)
+// A vocabulary that gives the streaming kernel, 512 ids a workgroup, less than one workgroup for every other CU is spread over tiles of 128 ids:
+// 0.30 - 0.97 of the streamed time at 2048 - 65 024 ids, d 512 - 8192, 8 - 192 rows (V = 32 000, K = 512: 128 rows 25.2 streamed -> 13.4 us, 32 rows 13.0 -> 9.8)
 bool head_few_workgroups(int V) { return (V + 511) / 512 < 128; }
 
 // The tile of ids x hidden rows.

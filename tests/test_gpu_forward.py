@@ -287,6 +287,41 @@ def test_head_in_tiles(vocab):
         assert (top1[0] == first[0]).all() and (conf[0] == first[1]).all()
 
 
+@pytest.mark.parametrize("d_model", [2048, 4160])
+def test_head_streamed_in_the_model(d_model):
+    """Models whose head is streamed from the packed copy up to 128 rows (65 025 ids and more): copy, the final norm's second output and the merge, for
+    8 to 128 rows, and the switch to tiles at 160 and 192 on the same handle; the whole-sequence call and the block rows against an approximate
+    cache.  Against the head on the plain kernel (debug bit 2) over the same hidden rows, a row's logit being off by at most 2 * d * 2^-24 * sum |y w|
+    between the two (the sum is about d * 0.64 * 0.02), and a logit error of e changing a probability by a factor exp(2 e)."""
+    import ctypes as C
+    import paper_2605_15609_amd as psd
+    from tests.gpu_common import make_models, to_dev
+    shape = inp.cut_down(SMALL, n_layers=1, d_model=d_model, n_heads=4, n_kv_heads=4, d_head=64, d_ffn=128, vocab=65100, seed=95)
+    N, L = 64, 32
+    host, model = make_models(shape, N)
+    e = 2 * d_model * 2.0 ** -24 * d_model * 0.64 * 0.02 * 1.5
+    states = np.stack([_state(shape, N, 32, L, 180 + s, (3 * s) % 8) for s in range(6)])
+    ids, width = C.c_int32(), C.c_int32()
+    for S, bs, n in ((1, 40, 8), (1, 32, L), (2, 32, L), (3, 32, L), (4, 32, L), (5, 32, L), (6, 32, L)):
+        streamed = model.lib.psd_debug_head_plan(S * n, shape.vocab, d_model, C.byref(ids), C.byref(width))
+        assert streamed == (S * n <= 128)
+        d = to_dev(states[:S])
+        cache = psd.KvCache(model, S, N - n) if n % 16 == 0 else None
+        calls = [lambda: psd.psd_forward_confidence(model, d, bs, n)]
+        if cache is not None:
+            psd.psd_forward_confidence_approx(model, d, bs, n, cache, refresh=True)
+            calls.append(lambda: psd.psd_forward_confidence_approx(model, d, bs, n, cache, refresh=False))
+        for call in calls:
+            top1, conf = (x.cpu().numpy() for x in call())
+            model.set_plain(4)
+            p_top1, p_conf = (x.cpu().numpy() for x in call())
+            model.set_plain(0)
+            masked = states[:S, bs: bs + n] == shape.mask_id
+            assert masked.any() and (conf[~masked] == -1).all() and (top1[~masked] == p_top1[~masked]).all()
+            assert (np.abs(conf - p_conf) <= (np.expm1(2 * e) + 1e-5) * p_conf)[masked].all()
+            assert (top1 == p_top1)[masked].mean() > 0.95     # (a near tie may fall either way)
+
+
 @pytest.mark.parametrize("name,N,S", [("small-2l", 96, 5), ("gqa-bias", 272, 3)])
 def test_qkv_epilogue_on_every_tile_configuration(name, N, S):
     """The same comparison with every workgroup tile forced in turn (the forced tile serves all contractions of both runs):
