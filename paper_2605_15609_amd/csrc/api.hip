@@ -1249,6 +1249,13 @@ int32_t psd_debug_gemm_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogu
     return PSD_OK;
 }
 
+int32_t psd_debug_gemm_ahead(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue) {
+    if (M <= 128 || Nout < 1 || Kin < 1 || epilogue < 0 || epilogue > 3) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
+    Warm next;
+    next.add(nullptr, 8192, 8192, 8192);   // (described, not read)
+    return gemm_bf16_ahead(gemm_bf16_plan(M, Nout, epilogue, Kin), M, Nout, epilogue, Kin, next).wgs;
+}
+
 int32_t psd_debug_head_plan(int32_t rows, int32_t vocab, int32_t d, int32_t *ids, int32_t *width) {
     if (rows < 1 || vocab < 2 || d < 1 || d % 64 || !ids || !width) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
     const HeadPlan p = head_plan(rows, vocab, d);

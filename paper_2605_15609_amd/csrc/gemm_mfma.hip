@@ -53,8 +53,10 @@ void launch_tile(int tile, Args... args) {
 
 // What the CUs that the last round of tiles leaves idle read ahead of `next`: items are cut to the bytes that they fetch in half of the
 // round (45 GB/s a CU, 2 TB/s together), so that the tiles end last and keep most of the HBM rate (3 TB/s over 60 % of it gave
-// the 7B cached batch 17.6 - 17.9 ms, 4 TB/s over 90 % 17.8, this 17.5, nothing 18.1; 8B prefill 8.47, nothing 8.59).  Above 2048 rows
-// the contractions are bound by the matrix cores, whatever their weights come from.
+// the 7B cached batch 17.6 - 17.9 ms, 4 TB/s over 90 % 17.8, this 17.5, nothing 18.1; 8B prefill 8.47, nothing 8.59).  A launch over
+// more than 2048 rows is bound by the matrix cores, and its tiles need the HBM rate for themselves.  The rows of a launch decide, not
+// those of the contraction: what a cut leaves to its second launch (540 of 6684 rows of the 8B SwiGLU, half of the CUs) reads ahead as any other of
+// its size (8B ragged steps 120.6 ms, without it 121.1, five runs in turn).
 Warm spare_reads(Warm next, int tile, int64_t M, int64_t cols, int Kin) {
     const TileCfg &t = kTiles[tile];
     const int64_t n = ((M + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn);
@@ -174,6 +176,11 @@ SplitPlan gemm_bf16_plan(int64_t M, int Nout, int epi, int Kin) {
     return best;
 }
 
+Warm gemm_bf16_ahead(const SplitPlan &p, int64_t M, int Nout, int epi, int Kin, const Warm &next) {
+    const int64_t cols = Nout - p.cols;
+    return spare_reads(next, p.rows || p.cols ? p.rest : p.tile, M - p.rows, epi == EPI_SWIGLU ? 2 * cols : cols, Kin);
+}
+
 namespace {
 
 template <int EPI>
@@ -184,17 +191,17 @@ void dispatch(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int M, int Nou
     auto part = [&](int tile, int64_t m0, int rows, int c0, int cols, const Warm &ahead) {
         const int64_t o = m0 * ldo + c0, w = (int64_t)c0 * ldw;
         launch_tile<EPI>(tile, A + m0 * lda, W + w, W2 ? W2 + w : W2, rows, cols, Kin, lda, ldw, bias ? bias + c0 : bias, out ? out + o : out,
-                         resid ? resid + o : resid, ldo, Top1Args(), st, 1, (float *)nullptr, QkvArgs(),
-                         spare_reads(ahead, tile, rows, EPI == EPI_SWIGLU ? 2 * (int64_t)cols : cols, Kin));
+                         resid ? resid + o : resid, ldo, Top1Args(), st, 1, (float *)nullptr, QkvArgs(), ahead);
     };
+    const Warm ahead = gemm_bf16_ahead(p, M, Nout, EPI, Kin, next);
     if (p.rows) {
         part(p.tile, 0, (int)p.rows, 0, Nout, Warm());
-        part(p.rest, p.rows, M - (int)p.rows, 0, Nout, next);
+        part(p.rest, p.rows, M - (int)p.rows, 0, Nout, ahead);
     } else if (p.cols) {
         part(p.tile, 0, M, 0, (int)p.cols, Warm());
-        part(p.rest, 0, M, (int)p.cols, Nout - (int)p.cols, next);
+        part(p.rest, 0, M, (int)p.cols, Nout - (int)p.cols, ahead);
     } else {
-        part(p.tile, 0, M, 0, Nout, next);
+        part(p.tile, 0, M, 0, Nout, ahead);
     }
 }
 

@@ -331,6 +331,7 @@ struct SplitPlan {
     int64_t rows = 0, cols = 0;
 };
 SplitPlan gemm_bf16_plan(int64_t M, int Nout, int epi, int Kin);
+Warm gemm_bf16_ahead(const SplitPlan &p, int64_t M, int Nout, int epi, int Kin, const Warm &next);   // what its last launch reads of `next`
 // what launch_gemm_bf16 runs: such an index, or gemm_bf16_tile_count() for the streaming kernel of few rows
 int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo);
 // QKV projection that also applies the rotary embedding to the q / k heads and stores V transposed into vT (what

@@ -197,3 +197,17 @@ def test_head_plan_of_narrow_models(lib):
             for rows in (65, 128):
                 assert lib.psd_debug_head_plan(rows, vocab, d, ctypes.byref(ids), ctypes.byref(width)) in (0, 1)
                 assert width.value == (64 if d <= 1536 and 65536 < vocab <= 98304 else 128), (vocab, d, rows)
+
+
+def test_read_ahead_is_for_launches_of_up_to_2048_rows(lib):
+    """The rows of a contraction's last launch decide: a cut may leave it few of many (6684 x 12288 SwiGLU: 540 rows, 128 CUs to spare)."""
+    rows, cols, cut, ahead = ctypes.c_int64(), ctypes.c_int64(), 0, 0
+    for M in (160, 512, 768, 1024, 1671, 2048, 2049, 2304, 4000, 5000, 6143, 6144, 6684, 8192, 20480):
+        for nout, kin, epi in ((12288, 4096, 3), (4096, 12288, 2), (4096, 4096, 2), (18944, 3584, 3), (3584, 18944, 2), (12288, 4096, 0), (4608, 3584, 1)):
+            wgs = lib.psd_debug_gemm_ahead(M, nout, kin, epi)
+            assert lib.psd_debug_gemm_cut(M, nout, kin, epi, ctypes.byref(rows), ctypes.byref(cols)) == 0
+            assert 0 <= wgs < 256 and (wgs == 0 or 0 < M - rows.value <= 2048), (M, nout, kin, epi)
+            cut += wgs > 0 and rows.value > 0
+            ahead += wgs > 0
+    assert cut >= 1 and ahead >= 10
+    assert lib.psd_debug_gemm_ahead(6684, 12288, 4096, 3) == 128
