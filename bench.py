@@ -74,7 +74,7 @@ class Probes:
         self.psd, self.model, self.w = psd, model, w
         self.lib = psd.load_library()
         self.rows_per_seq = rows_per_seq
-        self.tile = self.lib.psd_kernel_gemm_tile(w.batch * w.n_drafts * rows_per_seq, w.shape.d_ffn, 3)
+        self.tile = self.lib.psd_debug_gemm_plan(w.batch * w.n_drafts * rows_per_seq, w.shape.d_ffn, w.shape.d_model, 3, None)
 
     def begin(self):
         self.model.probe_begin(3, self.tile)
@@ -94,7 +94,7 @@ class Probes:
         tile_name = self.lib.psd_kernel_gemm_tile_name(self.tile).decode()
         stream = self.tile == self.lib.psd_kernel_gemm_tile_count()
         kernel = (f"gemm_stream_kernel, SwiGLU gate/up contraction, {tile_name}" if stream else
-                  f"mfma::gemm_bf16_kernel, SwiGLU gate/up contraction, tile {tile_name}")
+                  f"mfma::gemm_bf16_kernel, SwiGLU gate/up contraction, {'tile ' if self.tile < self.lib.psd_kernel_gemm_tile_count() else ''}{tile_name}")
         shapes = {}
         for rows, times in sorted(by_rows.items()):
             flops = 4.0 * rows * shape.d_model * shape.d_ffn

@@ -466,10 +466,11 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
                              double *flops, void *stream);
 
 /* Kernel timing for roofline accounting.  Between psd_probe_begin and psd_probe_end every
- * launch of the layer-contraction kernel with the given epilogue (0 store, 1 bias,
- * 2 residual, 3 SwiGLU) and workgroup tile configuration (an index below
- * psd_kernel_gemm_tile_count; psd_kernel_gemm_tile_name describes it: tile extent, wavefronts,
- * depths of the two LDS rings; psd_kernel_gemm_tile_count itself: the kernel that streams the weights past up to 128 rows) is bracketed by HIP events on the stream it is launched on (up to
+ * layer contraction with the given epilogue (0 store, 1 bias, 2 residual, 3 SwiGLU) that runs on the given kernel
+ * is bracketed by HIP events on the stream it is launched on.  Kernels: an index below psd_kernel_gemm_tile_count, a
+ * workgroup tile (psd_kernel_gemm_tile_name describes it: tile extent, depths of the two LDS rings);
+ * psd_kernel_gemm_tile_count itself, the one that streams the weights past up to 128 rows; numbers behind it, two
+ * tiles: the contraction runs as two launches, timed as one (up to
  * max_launches; later ones go untimed).  Kind 4 selects the LM-head confidence pass instead
  * (all its kernels, tile ignored), kind 5 every model call (forward + confidence pass) made by
  * psd_decode_block / psd_decode; both can be timed together with one contraction kernel.
@@ -479,13 +480,12 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
  * psd_probe_read (after psd_probe_end) copies the first max_n timed launches one by one: ms[i] their duration and
  * (a[i], b[i]) = (rows, output columns) of a contraction, (rows, 0) of an LM-head pass, (sequences, drafts per
  * sequence: 1 for a stage-1 call, K for a verification call) of a model call; returns how many it wrote.
- * psd_kernel_gemm_tile tells which of them the dispatcher picks for a shape (up to 128 rows of a contraction other than SwiGLU:
- * at a K of 4096). */
+ * psd_kernel_gemm_tile tells which of them the dispatcher picks for a shape at a K of 4096, psd_debug_gemm_plan at any K. */
 int32_t psd_probe_begin(psd_handle *h, int32_t epilogue, int32_t tile, int32_t max_launches);
 int32_t psd_probe_end(psd_handle *h, int32_t epilogue, double *total_ms, int64_t *launches, double *work);
 int32_t psd_probe_read(psd_handle *h, int32_t epilogue, int32_t max_n, float *ms, int64_t *a, int64_t *b);
 int32_t psd_kernel_gemm_tile(int64_t M, int32_t Nout, int32_t epilogue);
-/* Number of tile configurations (valid tile ids are 0 .. count-1) and a static description of one. */
+/* Number of tile configurations (valid tile ids are 0 .. count-1) and a static description of one, or of another kernel number. */
 int32_t psd_kernel_gemm_tile_count(void);
 const char *psd_kernel_gemm_tile_name(int32_t tile);
 

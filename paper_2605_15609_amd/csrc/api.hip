@@ -278,7 +278,7 @@ psd_handle::Probe &probe_of(psd_handle *h, int32_t kind) { return kind == 4 ? h-
 
 int32_t psd_probe_begin(psd_handle *h, int32_t epilogue, int32_t tile, int32_t max_launches) {
     if (!h) PSD_FAIL(PSD_ERR_INVALID_ARG, "handle is NULL");
-    if (epilogue < 0 || epilogue > 5 || tile < 0 || tile > gemm_bf16_tile_count() || max_launches < 1 || max_launches > (1 << 20))
+    if (epilogue < 0 || epilogue > 5 || tile < 0 || tile >= gemm_bf16_kernel_count() || max_launches < 1 || max_launches > (1 << 20))
         PSD_FAIL(PSD_ERR_INVALID_ARG, "bad probe arguments");
     psd_handle::Probe &pr = probe_of(h, epilogue);
     while (pr.ev.size() < (size_t)max_launches * 2) {
@@ -1231,8 +1231,7 @@ int32_t psd_kernel_mfma_rate(const void *operands, int64_t operand_bytes, int32_
 
 int32_t psd_kernel_gemm_tile(int64_t M, int32_t Nout, int32_t epilogue) {
     if (M < 1 || Nout < 1 || epilogue < 0 || epilogue > 3) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
-    if (M <= 128) return gemm_bf16_kernel(M, Nout, 4096, epilogue, nullptr, nullptr, nullptr, Nout);
-    return gemm_bf16_tile(M, Nout, epilogue);
+    return gemm_bf16_kernel(M, Nout, 4096, epilogue, nullptr, nullptr, nullptr, Nout);
 }
 
 int32_t psd_debug_gemm_plan(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int32_t *parts) {

@@ -3,6 +3,8 @@
 // operand.  The workgroup tile is picked per shape so that the grid fills the 256 CUs: big
 // tiles (least LDS traffic per FLOP) when whole rounds of them come out, smaller ones for
 // the short-M stage-1 pass and the narrow O / down projections.
+#include <stdio.h>
+
 #include "gemm_mfma.h"
 
 namespace {
@@ -87,8 +89,20 @@ void gemm_bf16_force_tile(int tile) {
 }
 int gemm_tile_group_m() { return g_group_m; }
 int gemm_bf16_tile_count() { return kNumTiles; }
+// Numbers of what runs: a tile, kNumTiles the streaming kernel, behind it the pairs of tiles of a contraction in two launches
+static int pair_number(int first, int rest) { return kNumTiles + 1 + first * kNumTiles + rest; }
+int gemm_bf16_kernel_count() { return pair_number(kNumTiles - 1, kNumTiles - 1) + 1; }
 const char *gemm_bf16_tile_name(int tile) {
-    return tile >= 0 && tile < kNumTiles ? kTiles[tile].name : tile == kNumTiles ? "all of up to 128 rows, streams the weights" : "?";
+    static const struct Pairs {
+        char name[kNumTiles * kNumTiles][80];
+        Pairs() {
+            for (int i = 0; i < kNumTiles * kNumTiles; ++i)
+                snprintf(name[i], sizeof(name[i]), "two launches, %s and %s", kTiles[i / kNumTiles].name, kTiles[i % kNumTiles].name);
+        }
+    } pairs;
+    if (tile < 0 || tile >= gemm_bf16_kernel_count()) return "?";
+    if (tile == kNumTiles) return "all of up to 128 rows, streams the weights";
+    return tile < kNumTiles ? kTiles[tile].name : pairs.name[tile - pair_number(0, 0)];
 }
 
 // Time of a launch (us).  Every workgroup has a CU to itself, so a launch takes whole rounds of 256 of them: K / 64 stages of the tile's
@@ -304,7 +318,9 @@ static StreamPlan stream_choice(int64_t M, int Nout, int Kin, int epi, const flo
 }
 
 int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo) {
-    return stream_choice(M, Nout, Kin, epi, bias, out, resid, ldo).tiles ? kNumTiles : gemm_bf16_tile(M, Nout, epi, Kin);
+    if (stream_choice(M, Nout, Kin, epi, bias, out, resid, ldo).tiles) return kNumTiles;
+    const SplitPlan p = gemm_bf16_plan(M, Nout, epi, Kin);
+    return p.rows || p.cols ? pair_number(p.tile, p.rest) : p.tile;
 }
 
 void launch_gemm_bf16(const bf16_t *A, const bf16_t *W, const bf16_t *W2, int64_t M, int Nout, int Kin, int lda, int ldw, int epi,

@@ -321,7 +321,7 @@ struct Warm {
     }
 };
 // gemm_mfma.hip (bf16; Nout, Kin multiples of 64)
-// index of the tile configuration the dispatcher picks for a shape; gemm_bf16_tile_name(i) describes configuration i
+// index of the tile configuration the dispatcher picks for a shape in one launch; gemm_bf16_tile_name(i) describes configuration i
 // (workgroup tile, LDS ring depths), 0 <= i < gemm_bf16_tile_count()
 int gemm_bf16_tile(int64_t M, int Nout, int epi, int Kin = 0);   // Kin = 0: not known (matters for residual contractions only)
 int gemm_bf16_tile_count();
@@ -332,7 +332,9 @@ struct SplitPlan {
 };
 SplitPlan gemm_bf16_plan(int64_t M, int Nout, int epi, int Kin);
 Warm gemm_bf16_ahead(const SplitPlan &p, int64_t M, int Nout, int epi, int Kin, const Warm &next);   // what its last launch reads of `next`
-// what launch_gemm_bf16 runs: such an index, or gemm_bf16_tile_count() for the streaming kernel of few rows
+// what launch_gemm_bf16 runs: such an index, gemm_bf16_tile_count() for the streaming kernel of few rows, or a number behind it, below
+// gemm_bf16_kernel_count(), for a pair of tiles in two launches
+int gemm_bf16_kernel_count();
 int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, const bf16_t *out, const float *resid, int ldo);
 // QKV projection that also applies the rotary embedding to the q / k heads and stores V transposed into vT (what
 // launch_rope_transpose_v does in a second pass), bit-identical to the two-pass form.  gemm_bf16_qkv_tile returns the tile

@@ -289,6 +289,24 @@ def test_probes_file_a_launch_under_the_kernel_that_ran(S):
     assert ran == {k: shape.n_layers if k == expect else 0 for k in ran}
 
 
+def test_probes_file_two_launches_as_one_contraction():
+    """A SwiGLU contraction of 3000 rows whose last round of tiles would be partial: one timing under the number of the pair, none under its tiles."""
+    import paper_2605_15609_amd as psd
+    shape = inp.cut_down(BF16["mha-dh64"], n_layers=1, d_model=1024, n_heads=4, n_kv_heads=4, d_ffn=11008, attention="bidirectional")
+    L, N, S = 64, 100, 30
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    hidden = torch.zeros(S * N, shape.d_model, device=DEV).normal_()
+    number, count = model.lib.psd_debug_gemm_plan(S * N, shape.d_ffn, shape.d_model, 3, None), model.lib.psd_kernel_gemm_tile_count()
+    assert number > count
+    pair = number - count - 1
+    for kernel in (number, pair // count, pair % count):
+        model.probe_begin(3, kernel, 64)
+        psd.binding.debug_layer(model, 0, hidden, S, N, L)
+        ms, launches, flops = model.probe_end(3)
+        assert launches == (1 if kernel == number else 0)
+        assert flops == (4.0 * S * N * shape.d_model * shape.d_ffn if kernel == number else 0.0)
+
+
 def test_bf16_cached_call_at_128_and_256_rows_agrees_to_rounding():
     """Block-row calls over at most 128 rows cut the residual contractions along K (a weight stream needs the workgroups),
     larger ones do not: a sequence's fp32 sums, hence its logits, depend on whether 4 or 8 sequences share the call --

@@ -211,3 +211,25 @@ def test_read_ahead_is_for_launches_of_up_to_2048_rows(lib):
             ahead += wgs > 0
     assert cut >= 1 and ahead >= 10
     assert lib.psd_debug_gemm_ahead(6684, 12288, 4096, 3) == 128
+
+
+def test_a_contraction_in_two_launches_has_a_number_of_its_own(lib):
+    """Not that of the tile it would run on in one launch; its name gives both tiles."""
+    rows, cols = ctypes.c_int64(), ctypes.c_int64()
+    count, seen = lib.psd_kernel_gemm_tile_count(), 0
+    tiles = [lib.psd_kernel_gemm_tile_name(t).decode() for t in range(count)]
+    assert len(set(tiles)) == count
+    for M in (200, 512, 1000, 1024, 1671, 2048, 5000, 6144, 6684, 20480):
+        for nout, kin, epi in ((12288, 4096, 3), (4096, 12288, 2), (4096, 4096, 2), (18944, 3584, 3), (3584, 18944, 2), (12288, 4096, 0)):
+            assert lib.psd_debug_gemm_cut(M, nout, kin, epi, ctypes.byref(rows), ctypes.byref(cols)) == 0
+            number = lib.psd_debug_gemm_plan(M, nout, kin, epi, None)
+            name = lib.psd_kernel_gemm_tile_name(number).decode()
+            if rows.value or cols.value:
+                seen += 1
+                assert number > count and name.startswith("two launches, ")
+                assert any(name == f"two launches, {a} and {b}" for a in tiles[:2] for b in tiles), name
+            else:
+                assert 0 <= number < count and name == tiles[number]
+            if kin == 4096:
+                assert lib.psd_kernel_gemm_tile(M, nout, epi) == number
+    assert seen >= 5
