@@ -58,6 +58,7 @@ namespace mfma {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int EPI_TOP1 = 4;
 constexpr int EPI_QKV = 5;
@@ -109,6 +110,16 @@ __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, I..
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
     static_for(f, std::make_integer_sequence<int, N>());
+}
+// The bf16 epilogues go through LDS.  A lone wavefront a SIMD waits out the latency of every read, so a thread takes up to `most` of its `per` units
+// at a time, all reads before the first store (one unit at a time the QKV projection was up to 10 % behind eight wavefronts a workgroup:
+// 8192 rows, K = 1024, 3072 outputs 57 -> 63 us, with batches 60; 1536 outputs 34 -> 37, 35; 4096 rows, K = 2048, 6144 outputs 91 -> 97, 92; 2048 rows, K = 4096,
+// 12288 outputs 160 -> 163, 158).
+constexpr int batch_of(int per, int most) {
+    int b = 1;
+    for (int i = 2; i <= most; ++i)
+        if (per % i == 0) b = i;
+    return b;
 }
 // of n events spread over `span` steps, the first one at step t or later
 constexpr int event_at(int t, int n, int span) { return (t * n + span - 1) / span < n ? (t * n + span - 1) / span : n; }
@@ -347,6 +358,25 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
         for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
 #undef PSD_GEMM_SYNC
 
+    constexpr int NT = NW * 64, LDC = BN_OUT * 2 + 16;   // LDC: bytes per row of the tile staged row-major (bf16 outputs)
+    // the staged tile to `out`, 16 bytes per lane
+    auto store_rows = [&]() {
+        constexpr int W8 = BN_OUT / 8, PER = BM * W8 / NT, BATCH = batch_of(PER, 8);
+        static_assert(BM * W8 % NT == 0, "whole units per thread");
+        for (int u0 = tid; u0 < PER * NT; u0 += BATCH * NT) {
+            u32x4 x[BATCH];
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                const int u = u0 + e * NT;
+                x[e] = *reinterpret_cast<const u32x4 *>(lds + u / W8 * LDC + u % W8 * 16);
+            }
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                const int u = u0 + e * NT, m = m0 + u / W8, n = n0 + u % W8 * 8;
+                if (m < M && n < Nout) *reinterpret_cast<u32x4 *>(out + (int64_t)m * ldo + n) = x[e];
+            }
+        }
+    };
     if constexpr (EPI == EPI_TOP1) {
         // per column j: (max, lowest argmax, sum exp) over this tile's rows; rows ascend with (i, v)
         // inside a lane, so a strict comparison keeps the lowest index on ties
@@ -404,8 +434,6 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
             t1.parg[o] = arg;
         }
     } else if constexpr (EPI == EPI_QKV) {
-        constexpr int NT = NW * 64;
-        constexpr int LDC = BN * 2 + 16;   // bytes per row of the row-major staging tile
         constexpr int LDT = BM * 2 + 8;    // bytes per column of the column-major one
         static_assert(BM * LDC <= (NSA * BM + NSB * BN) * ROW_BYTES && BN * LDT <= (NSA * BM + NSB * BN) * ROW_BYTES, "staging tile fits the rings");
         __syncthreads();                   // every wavefront is done with the operand rings
@@ -426,32 +454,38 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
                 }
             }
             __syncthreads();
-            if (n0 >= qa.v_start) {
-                for (int u = tid; u < BM * (BN / 8); u += NT) {
-                    const int c8 = u % (BN / 8), row = u / (BN / 8);
-                    const int m = m0 + row, n = n0 + c8 * 8;
-                    if (m < M && n < Nout)
-                        *reinterpret_cast<uint4 *>(out + (int64_t)m * ldo + n) = *reinterpret_cast<const uint4 *>(lds + row * LDC + c8 * 16);
+            if (n0 >= qa.v_start) return store_rows();
+            // A unit is 8 pair indices of one head of one row, BN / 16 units to a row.
+            constexpr int ROW_UNITS = BN / 16, PER = BM * ROW_UNITS / NT, BATCH = batch_of(PER, 4);
+            static_assert(BM * ROW_UNITS % NT == 0, "whole units per thread");
+            const int half = qa.d_head >> 1, pick = half == 64 ? 3 : 2;   // 8 or 4 units to a head
+            for (int u0 = tid; u0 < PER * NT; u0 += BATCH * NT) {
+                uint4 a[BATCH], b[BATCH];
+                float4 c0[BATCH], c1[BATCH], s0[BATCH], s1[BATCH];
+#pragma unroll
+                for (int e = 0; e < BATCH; ++e) {
+                    const int u = u0 + e * NT, row = u / ROW_UNITS, c = u % ROW_UNITS, g = c & ((1 << pick) - 1);
+                    const unsigned char *src = lds + row * LDC + ((c >> pick) * qa.d_head + g * 8) * 2;
+                    a[e] = *reinterpret_cast<const uint4 *>(src);
+                    b[e] = *reinterpret_cast<const uint4 *>(src + half * 2);
+                    const int64_t t = (int64_t)(qa.pos0 + (m0 + row) % qa.N) * half + g * 8;   // (rows past M: a position of the sequence, not stored)
+                    c0[e] = *reinterpret_cast<const float4 *>(qa.cos_t + t);
+                    c1[e] = *reinterpret_cast<const float4 *>(qa.cos_t + t + 4);
+                    s0[e] = *reinterpret_cast<const float4 *>(qa.sin_t + t);
+                    s1[e] = *reinterpret_cast<const float4 *>(qa.sin_t + t + 4);
                 }
-                return;
-            }
-            const int half = qa.d_head >> 1, groups = half >> 3, heads = BN / qa.d_head;
-            const int units = BM * heads * groups;   // 8 pair indices of one head of one row each
-            for (int u = tid; u < units; u += NT) {
-                const int g = u % groups, hd = (u / groups) % heads, row = u / (groups * heads);
-                const int m = m0 + row, n = n0 + hd * qa.d_head + g * 8;
-                if (m >= M || n >= Nout) continue;
-                const unsigned char *src = lds + row * LDC + (hd * qa.d_head + g * 8) * 2;
-                const uint4 a = *reinterpret_cast<const uint4 *>(src), b = *reinterpret_cast<const uint4 *>(src + half * 2);
-                const int64_t t = (int64_t)(qa.pos0 + m % qa.N) * half + g * 8;
-                const float4 c0 = *reinterpret_cast<const float4 *>(qa.cos_t + t), c1 = *reinterpret_cast<const float4 *>(qa.cos_t + t + 4);
-                const float4 s0 = *reinterpret_cast<const float4 *>(qa.sin_t + t), s1 = *reinterpret_cast<const float4 *>(qa.sin_t + t + 4);
-                uint4 ra, rb;
-                rope_rotate8(a, b, c0, c1, s0, s1, ra, rb);
-                bf16_t *dst = out + (int64_t)m * ldo + n;
-                if (qa.k_dst && n >= qa.k_start) dst = qa.k_dst + (m / qa.N) * qa.k_seq + (int64_t)(m % qa.N) * qa.ld_k + (n - qa.k_start);
-                *reinterpret_cast<uint4 *>(dst) = ra;
-                *reinterpret_cast<uint4 *>(dst + half) = rb;
+#pragma unroll
+                for (int e = 0; e < BATCH; ++e) {
+                    const int u = u0 + e * NT, row = u / ROW_UNITS, c = u % ROW_UNITS, g = c & ((1 << pick) - 1);
+                    const int m = m0 + row, n = n0 + (c >> pick) * qa.d_head + g * 8;
+                    if (m >= M || n >= Nout) continue;
+                    uint4 ra, rb;
+                    rope_rotate8(a[e], b[e], c0[e], c1[e], s0[e], s1[e], ra, rb);
+                    bf16_t *dst = out + (int64_t)m * ldo + n;
+                    if (qa.k_dst && n >= qa.k_start) dst = qa.k_dst + (m / qa.N) * qa.k_seq + (int64_t)(m % qa.N) * qa.ld_k + (n - qa.k_start);
+                    *reinterpret_cast<uint4 *>(dst) = ra;
+                    *reinterpret_cast<uint4 *>(dst + half) = rb;
+                }
             }
         } else {
             // ---- V heads: stage column-major, store transposed.  Inside every group of 16 keys the slots hold keys 0-3, 8-11, 4-7, 12-15.
@@ -466,16 +500,26 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
                         *reinterpret_cast<uint16_t *>(lds + col * LDT + (wm * WTM + i * MI + lrow) * 2) = from_float<bf16_t>(acc[i][j][v] + bn).bits;
                 }
             __syncthreads();
-            constexpr int G16 = BM / 16;
-            for (int u = tid; u < BN * G16 * 2; u += NT) {
-                const int h = u & 1, g = (u >> 1) % G16, col = u / (2 * G16);
-                const int m = m0 + g * 16, n = n0 + col;
-                if (m >= M || n >= Nout) continue;
-                const unsigned char *src = lds + col * LDT + (g * 16 + 4 * h) * 2;
-                const uint2 lo = *reinterpret_cast<const uint2 *>(src), hi = *reinterpret_cast<const uint2 *>(src + 16);
-                const int sq = m / qa.N, i0 = m % qa.N;   // N % 16 == 0: the 16 keys belong to one sequence
-                bf16_t *dst = qa.vT + sq * qa.vt_seq + (int64_t)(n - qa.v_start) * qa.ld_vt + i0 + 8 * h;
-                *reinterpret_cast<uint4 *>(dst) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            constexpr int G16 = BM / 16, PER = BN * G16 * 2 / NT, BATCH = batch_of(PER, 8);
+            static_assert(BN * G16 * 2 % NT == 0, "whole units per thread");
+            for (int u0 = tid; u0 < PER * NT; u0 += BATCH * NT) {
+                uint2 lo[BATCH], hi[BATCH];
+#pragma unroll
+                for (int e = 0; e < BATCH; ++e) {
+                    const int u = u0 + e * NT, h = u & 1, g = (u >> 1) % G16, col = u / (2 * G16);
+                    const unsigned char *src = lds + col * LDT + (g * 16 + 4 * h) * 2;
+                    lo[e] = *reinterpret_cast<const uint2 *>(src);
+                    hi[e] = *reinterpret_cast<const uint2 *>(src + 16);
+                }
+#pragma unroll
+                for (int e = 0; e < BATCH; ++e) {
+                    const int u = u0 + e * NT, h = u & 1, g = (u >> 1) % G16, col = u / (2 * G16);
+                    const int m = m0 + g * 16, n = n0 + col;
+                    if (m >= M || n >= Nout) continue;
+                    const int sq = m / qa.N, i0 = m % qa.N;   // N % 16 == 0: the 16 keys belong to one sequence
+                    bf16_t *dst = qa.vT + sq * qa.vt_seq + (int64_t)(n - qa.v_start) * qa.ld_vt + i0 + 8 * h;
+                    *reinterpret_cast<uint4 *>(dst) = make_uint4(lo[e].x, lo[e].y, hi[e].x, hi[e].y);
+                }
             }
         }
     } else if constexpr (EPI == EPI_RESIDUAL) {
@@ -531,7 +575,6 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
         };
         // bf16 outputs.  Where rows allow 16-byte accesses the tile is staged in LDS (the operand rings are free; rows padded by 16 bytes)
         // and stored with 16 bytes per lane.
-        constexpr int BNO = BN_OUT, LDC = BNO * 2 + 16, NT = NW * 64;
         static_assert(BM * LDC <= (NSA * BM + NSB * BN) * ROW_BYTES, "staging tile fits the rings");
         const bool wide = (ldo & 7) == 0 && (Nout & 7) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0;   // uniform
         if (wide) {
@@ -548,12 +591,7 @@ __global__ __launch_bounds__(WGM * WGN * 64, WPS) void gemm_bf16_kernel(const bf
                         make_uint2(pack_bf16x2(value(i, j, 0, bn[0]), value(i, j, 1, bn[1])), pack_bf16x2(value(i, j, 2, bn[2]), value(i, j, 3, bn[3])));
             }
             __syncthreads();
-            for (int u = tid; u < BM * (BNO / 8); u += NT) {
-                const int c8 = u % (BNO / 8), row = u / (BNO / 8);
-                const int m = m0 + row, n = n0 + c8 * 8;
-                if (m < M && n < Nout)
-                    *reinterpret_cast<uint4 *>(out + (int64_t)m * ldo + n) = *reinterpret_cast<const uint4 *>(lds + row * LDC + c8 * 16);
-            }
+            store_rows();
         } else {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
