@@ -236,11 +236,13 @@ int32_t psd_debug_force_gemm_tile(int32_t tile);
  * psd_probe_begin numbers it, and in *parts (may be NULL) the parts along K that a cached call cuts a residual contraction into;
  * psd_debug_qkv_cut the first column that the QKV projection of whole sequences leaves to a second launch (0: one launch).
  * psd_debug_gemm_cut: the other contractions over more than 128 rows; *rows / *cols of the first of two launches (both 0: one launch).
+ * psd_debug_qkv_fused: 1 where the QKV projection of packed weights rotates and transposes in its epilogue (into a KV cache or not), 0 in two passes.
  * psd_debug_gemm_ahead: the workgroups that the last launch of such a contraction adds to read the next weights ahead.
  * psd_debug_head_plan: the LM-head pass of a bf16 model over `rows` hidden rows; *ids x *width the tile, returns 1 where the forward streams a
  * packed copy of the matrix instead, 0 otherwise. */
 int32_t psd_debug_gemm_plan(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int32_t *parts);
 int32_t psd_debug_gemm_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue, int64_t *rows, int64_t *cols);
+int32_t psd_debug_qkv_fused(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq, int32_t into_cache);
 int32_t psd_debug_gemm_ahead(int64_t M, int32_t Nout, int32_t Kin, int32_t epilogue);
 int32_t psd_debug_head_plan(int32_t rows, int32_t vocab, int32_t d, int32_t *ids, int32_t *width);
 int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq);

@@ -134,6 +134,7 @@ def load_library():
         "psd_debug_force_gemm_tile": (i32, [i32]),
         "psd_debug_gemm_plan": (i32, [i64, i32, i32, i32, C.POINTER(i32)]),
         "psd_debug_gemm_cut": (i32, [i64, i32, i32, i32, C.POINTER(i64), C.POINTER(i64)]),
+        "psd_debug_qkv_fused": (i32, [i64, i32, i32, i32, i32, i32, i32]),
         "psd_debug_gemm_ahead": (i32, [i64, i32, i32, i32]),
         "psd_debug_head_plan": (i32, [i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]),
         "psd_debug_qkv_cut": (i32, [i64, i32, i32, i32, i32, i32]),

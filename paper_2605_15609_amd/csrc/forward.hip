@@ -114,14 +114,14 @@ struct Dispatch<bf16_t> {
     }
     // The QKV projection of [M = S * N, d] rows with wq | wk | wv as one matrix, rotary and (kv.vT) the V transpose in its
     // epilogue; false (nothing launched) when the matrix-core attention will not run on its output, the shape has no
-    // tile that holds whole heads, or a debug switch (plain_mask bit 3) asks for the two-pass form.
+    // tile that holds whole heads, the two-pass form is faster (few rows), or a debug switch (plain_mask bit 3) asks for it.
     static bool qkv_fused(psd_handle *h, const bf16_t *A, const void *W, int64_t M, int N, int pos0, int H, int Hkv, int dh,
                           const float *bias, bf16_t *qkv, int ld_qkv, const KvDest &kv, int block_len, hipStream_t st, const Warm &next = Warm()) {
         if ((h->plain_mask & (1 | 2 | 8)) || (block_len > 0 && block_len < N)) return false;
         if (h->probe.enabled && (h->probe.epi == EPI_STORE || h->probe.epi == EPI_BIAS)) return false;   // that probe times the plain store
         const int d = h->cfg.d_model, qkv_w = (H + 2 * Hkv) * dh;
         const int tile = gemm_bf16_qkv_tile(M, qkv_w, dh, (H + Hkv) * dh, kv.vT ? N : 16);
-        if (tile < 0) return false;
+        if (tile < 0 || gemm_bf16_qkv_in_two(M, qkv_w, d, dh, kv.k != nullptr)) return false;
         launch_gemm_bf16_qkv(A, (const bf16_t *)W, M, qkv_w, d, d, d, bias, qkv, ld_qkv, dh, (H + Hkv) * dh, N, pos0, h->rope_cos,
                              h->rope_sin, kv, tile, st, next);
         return true;

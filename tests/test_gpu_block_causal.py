@@ -267,6 +267,29 @@ def test_bf16_cached_call_does_not_depend_on_the_batch(name, L, blocks, batches)
         assert torch.equal(out[S][: few * L], out[few]), f"{S} sequences: other bits than with {few}"
 
 
+@pytest.mark.parametrize("P", [16, 32, 64, 96, 112])
+def test_prompt_entries_do_not_depend_on_the_form_of_the_projection(P):
+    """Heads of 128 and few of them: prompts of up to 96 rows project in two passes, a batch of eight in one.  The first layer's keys and values (its input
+    does not depend on the number of rows) bit for bit, and what lies behind the prompt stays as it was."""
+    import paper_2605_15609_amd as psd
+    shape = inp.cut_down(BF16["gqa-bias-dh128"], d_model=2048, n_heads=4, n_kv_heads=1, d_ffn=256, seed=47)
+    L, S, N = 16, 8, 160
+    model = psd.Model.from_host(inp.draw_model(shape, N), DEV)
+    width = (shape.n_heads + 2 * shape.n_kv_heads) * shape.d_head
+    fused = [model.lib.psd_debug_qkv_fused(rows, width, shape.d_model, shape.d_head, width - shape.n_kv_heads * shape.d_head, P, 1) for rows in (P, S * P)]
+    assert fused == [0 if P <= 96 else 1, 1]
+    d = _dev(np.stack([_state(shape, N, P, L, 0, 130 + s, 3)[0] for s in range(S)]))
+    caches = {}
+    for n in (1, S):
+        caches[n] = psd.KvCache(model, n, N)
+        caches[n].mem.fill_(0x7f)
+        psd.psd_kv_prefill(model, d[:n].contiguous(), P, L, caches[n])
+    first_layer = 2 * shape.n_kv_heads * shape.d_head * (N + (N + 63) // 64 * 64)
+    one, all_ = (caches[n].mem[:first_layer].view(torch.int16) for n in (1, S))
+    assert torch.equal(one, all_)
+    assert int((one != 0x7f7f).sum()) >= 0.95 * 2 * P * shape.n_kv_heads * shape.d_head
+
+
 @pytest.mark.parametrize("S", [1, 5])
 def test_probes_file_a_launch_under_the_kernel_that_ran(S):
     """The SwiGLU contractions of a cached call over 32 rows stream the weights, those over 160 rows run on a tile: each is timed
