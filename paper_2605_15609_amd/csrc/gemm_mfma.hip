@@ -58,13 +58,22 @@ void launch_tile(int tile, Args... args) {
 // the 7B cached batch 17.6 - 17.9 ms, 4 TB/s over 90 % 17.8, this 17.5, nothing 18.1; 8B prefill 8.47, nothing 8.59).  A launch over
 // more than 2048 rows is bound by the matrix cores, and its tiles need the HBM rate for themselves.  The rows of a launch decide, not
 // those of the contraction: what a cut leaves to its second launch (540 of 6684 rows of the 8B SwiGLU, half of the CUs) reads ahead as any other of
-// its size (8B ragged steps 120.6 ms, without it 121.1, five runs in turn).
+// its size.
+// Nothing is read ahead where that and the weights that the round fetches itself exceed 200 MB: the last-level cache holds 256, so one pushes the other
+// out again and the round has lost its HBM rate for nothing.  Three or four layers, nothing ahead / everything / this rule (us): d 6144, d_ffn 24 576, 136 rows 1612 / 1707
+// / 1612; d 7168, d_ffn 18 432, 192 rows 1426 / 1479 / 1423; d 5120, d_ffn 25 600, 512 rows 1875 / 1939 / 1864; d 4096, d_ffn 14 336, 384 rows 976 / 954 / 940; d 2560, d_ffn 9728,
+// 192 rows 573 / 541 / 541.  Over 12 layer shapes of d 2048 - 8192 at 136 - 2048 rows it is within 0.2 % of the best of these on average, and at most 1 % (noise
+// is 1 - 2 % there) behind nothing ahead at any; with 240 or 270 MB, or with reads cut to what is left of 200 or 256, up to 1.6 % more than with it.
 Warm spare_reads(Warm next, int tile, int64_t M, int64_t cols, int Kin) {
     const TileCfg &t = kTiles[tile];
     const int64_t n = ((M + t.bm - 1) / t.bm) * ((cols + t.bn - 1) / t.bn);
     const int idle = (int)((256 - n % 256) % 256);
     const double rate = idle * 45e3 < 2e6 ? idle * 45e3 : 2e6;     // bytes per us
     int64_t left = idle < 16 || M > 2048 ? 0 : (int64_t)(rate * (Kin / mfma::BK) * t.stage * 0.5) / 1024;    // KB
+    int64_t want = 0;
+    for (int i = 0; i < next.n; ++i) want += (int64_t)next.rows[i] * next.kb[i];
+    const double own = (double)cols * Kin * 2 / 1024 * (n % 256) / n;    // KB of weights that the last round fetches
+    if (own + (want < left ? want : left) > 200e6 / 1024) left = 0;
     for (int i = 0; i < next.n; ++i) {
         const int64_t fit = left / next.rows[i];
         if (next.kb[i] > fit) next.kb[i] = (int)fit;

@@ -213,6 +213,14 @@ def test_read_ahead_is_for_launches_of_up_to_2048_rows(lib):
     assert lib.psd_debug_gemm_ahead(6684, 12288, 4096, 3) == 128
 
 
+def test_read_ahead_leaves_the_last_level_cache_to_the_launch(lib):
+    """Where the last round of tiles fetches so many weights itself that 200 MB would be exceeded, nothing is read ahead; a short last round fetches few."""
+    for M, nout, kin, epi in ((136, 6144, 24576, 2), (136, 18432, 6144, 0), (384, 14336, 4096, 3), (136, 18432, 7168, 3)):
+        assert lib.psd_debug_gemm_ahead(M, nout, kin, epi) == 0, (M, nout, kin, epi)
+    for M, nout, kin, epi in ((136, 4096, 12288, 2), (136, 2048, 8192, 2), (768, 18944, 3584, 3), (768, 25600, 5120, 3)):
+        assert lib.psd_debug_gemm_ahead(M, nout, kin, epi) > 0, (M, nout, kin, epi)
+
+
 def test_a_contraction_in_two_launches_has_a_number_of_its_own(lib):
     """Not that of the tile it would run on in one launch; its name gives both tiles."""
     rows, cols = ctypes.c_int64(), ctypes.c_int64()
