@@ -1271,7 +1271,8 @@ int32_t psd_debug_qkv_cut(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, 
 
 int32_t psd_debug_qkv_fused(int64_t M, int32_t Nout, int32_t Kin, int32_t d_head, int32_t v_start, int32_t rows_per_seq, int32_t into_cache) {
     if (M < 1 || Nout < 1 || Kin < 1 || rows_per_seq < 1) PSD_FAIL(PSD_ERR_INVALID_ARG, "bad arguments");
-    return gemm_bf16_qkv_tile(M, Nout, d_head, v_start, rows_per_seq) >= 0 && !gemm_bf16_qkv_in_two(M, Nout, Kin, d_head, into_cache != 0);
+    const int tile = gemm_bf16_qkv_tile(M, Nout, d_head, v_start, rows_per_seq);
+    return tile >= 0 && !gemm_bf16_qkv_in_two(M, Nout, Kin, tile, into_cache != 0);
 }
 
 int32_t psd_kernel_gemm_tile_count(void) { return gemm_bf16_tile_count(); }

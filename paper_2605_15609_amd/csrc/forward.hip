@@ -121,7 +121,7 @@ struct Dispatch<bf16_t> {
         if (h->probe.enabled && (h->probe.epi == EPI_STORE || h->probe.epi == EPI_BIAS)) return false;   // that probe times the plain store
         const int d = h->cfg.d_model, qkv_w = (H + 2 * Hkv) * dh;
         const int tile = gemm_bf16_qkv_tile(M, qkv_w, dh, (H + Hkv) * dh, kv.vT ? N : 16);
-        if (tile < 0 || gemm_bf16_qkv_in_two(M, qkv_w, d, dh, kv.k != nullptr)) return false;
+        if (tile < 0 || gemm_bf16_qkv_in_two(M, qkv_w, d, tile, kv.k != nullptr)) return false;
         launch_gemm_bf16_qkv(A, (const bf16_t *)W, M, qkv_w, d, d, d, bias, qkv, ld_qkv, dh, (H + Hkv) * dh, N, pos0, h->rope_cos,
                              h->rope_sin, kv, tile, st, next);
         return true;

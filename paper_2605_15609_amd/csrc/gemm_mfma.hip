@@ -269,13 +269,14 @@ int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_pe
     return qkv_tile(M, Nout, d_head, v_start);
 }
 
-// Few rows under heads of 128: one round of tiles of whole heads, each of which walks all of K alone, against a stream over the weights and a launch that
+// Few rows in one round of tiles of 128 columns or more (heads of 128), or in two of 64 columns (more than 256 heads of 64): tiles that walk all of K alone, against a stream over the weights and a launch that
 // rotates, transposes and, for a KV cache, stores.  Fitted to both forms over 18 layer shapes of d 512 - 8192, 16 - 96 rows (us; 6.2 ns per K; 0.13 per
 // MB of weights up to 64 rows, 0.24 above; 7 for the launches behind the stream where they store into caches, 3 where not): the choice is within
 // 0.2 us of the faster form on average, within 6.4 everywhere.  7B shape (3584 -> 4608), 32 rows: fused 10.5 - 11 us a layer behind, MHA of 4096 at 96 rows
-// 6 ahead.  From 97 rows on and with heads of 64 (tiles of 64 columns) the fused form is level or ahead.
-bool gemm_bf16_qkv_in_two(int64_t M, int Nout, int Kin, int d_head, bool into_cache) {
-    if (g_force_tile >= 0 || M > 96 || d_head != 128) return false;
+// 6 ahead; 96 heads of 64, d 6144, 48 and 49 rows 16 and 18 behind.  From 97 rows on and in one round of 64 columns the fused form is level or ahead.
+bool gemm_bf16_qkv_in_two(int64_t M, int Nout, int Kin, int tile, bool into_cache) {
+    const TileCfg &t = kTiles[tile];
+    if (g_force_tile >= 0 || M > 96 || (t.bn < 128 && (M + t.bm - 1) / t.bm * ((Nout + t.bn - 1) / t.bn) <= 256)) return false;
     const double mb = (double)Nout * Kin * 2e-6;
     return 0.0062 * Kin > mb * (M <= 64 ? 0.13 : 0.24) + (into_cache ? 7 : 3);
 }

@@ -341,8 +341,8 @@ int gemm_bf16_kernel(int64_t M, int Nout, int Kin, int epi, const float *bias, c
 // to pass on, or -1 when the shape has no tile that holds whole heads of one kind (then the two-pass form runs).
 // rows_per_seq: rows of A per sequence (a multiple of 16 where V is transposed; 16 stands for any length where it is not); v_start: first V column; pos0: position of a sequence's row 0.
 int gemm_bf16_qkv_tile(int64_t M, int Nout, int d_head, int v_start, int rows_per_seq);
-// whether few rows take the two-pass form all the same, being faster
-bool gemm_bf16_qkv_in_two(int64_t M, int Nout, int Kin, int d_head, bool into_cache);
+// whether few rows take the two-pass form all the same, being faster than `tile`
+bool gemm_bf16_qkv_in_two(int64_t M, int Nout, int Kin, int tile, bool into_cache);
 int gemm_bf16_qkv_cut(int64_t M, int Nout, int d_head, int v_start, int tile);   // first column of its second launch, 0: one launch
 // Where the keys and the transposed values of that projection go: k = NULL: keys next to the queries in qkv, otherwise
 // straight into the sequences' KV caches (row i of sequence s at k[s * k_seq + i * ld_k], columns from k_start on); values at

@@ -247,7 +247,8 @@ def test_a_contraction_in_two_launches_has_a_number_of_its_own(lib):
     ((4608, 3584, 128, 4096), (16, 32, 64, 96), (0, 1), 0), ((4608, 3584, 128, 4096), (112, 128, 144, 512), (0, 1), 1),     # 28 / 4 heads
     ((6144, 4096, 128, 5120), (16, 96), (0, 1), 0), ((7168, 5120, 128, 6144), (32, 96), (0, 1), 0), ((10240, 8192, 128, 9216), (16, 64), (0, 1), 0),
     ((12288, 4096, 128, 8192), (80, 96), (0, 1), 1), ((12288, 4096, 128, 8192), (16, 64), (0,), 0), ((15360, 5120, 128, 10240), (80, 96), (1,), 1),
-    ((3072, 1024, 64, 2048), (16, 96), (0, 1), 1), ((1536, 512, 64, 1024), (16, 96), (0, 1), 1), ((5120, 4096, 64, 4608), (48, 96), (0, 1), 1)])
+    ((3072, 1024, 64, 2048), (16, 96), (0, 1), 1), ((1536, 512, 64, 1024), (16, 96), (0, 1), 1), ((5120, 4096, 64, 4608), (48, 96), (0, 1), 1),
+    ((18432, 6144, 64, 12288), (16, 48, 64), (0,), 0), ((9216, 6144, 64, 7680), (80, 96), (0, 1), 1)])
 def test_few_rows_of_the_qkv_projection_take_the_faster_form(lib, shape, rows, into_cache, fused):
     """As measured on both forms; what is within a microsecond or two of level is not listed."""
     nout, kin, d_head, v_start = shape
