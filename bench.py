@@ -35,7 +35,7 @@ SWIGLU_TRAFFIC = {
     "source": "profiles/config5_hbm_traffic_pmc.md and profiles/config3_hbm_traffic_pmc.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, "
               "copy-calibrated; FETCH_SIZE counts what the L2s request from the fabric, Infinity-Cache hits included)",
     "d_model": 4096, "d_ffn": 12288,
-    "rows": {163840: (50.06 + 4.09) * 1e9, 20480: (6.05 + 0.51) * 1e9, 2048: (577.2 + 48.8) * 2 ** 20, 512: (224.2 + 12.0) * 2 ** 20},
+    "rows": {163840: (48.71 + 4.03) * 1e9, 20480: (6.07 + 0.50) * 1e9, 2048: (576.5 + 48.0) * 2 ** 20, 512: (224.2 + 12.0) * 2 ** 20},
 }
 
 
